@@ -18,7 +18,7 @@
 //   * Partial tiles go to the workspace in MFMA-fragment order; a reduction kernel sums the
 //     slices, applies alpha/beta and writes both triangles (the mirror through an LDS
 //     transpose), so H is exactly symmetric; for cross every tile is written as it is.
-// fp32 path (small fp32 inputs): a plain LDS-tiled fp32 FMA kernel over the full matrix.
+// fp32 path (small fp32 inputs): fp32 MFMA tiles, the tokens split over a workgroup's waves.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -643,53 +643,129 @@ __global__ __launch_bounds__(256) void cross_reduce(KQ_GRAM_REDUCE_ARGS) {
 #undef KQ_GRAM_DMA_ARGS
 #undef KQ_GRAM_REDUCE_ARGS
 
-// Plain fp32 A^T B for fp32 inputs (B = A for the covariance): 64 x 64 tiles, 4 x 4 outputs per
-// thread.
-__global__ __launch_bounds__(256) void syrk_f32(const float* __restrict__ A,
-                                                const float* __restrict__ B, int64_t n_rows,
-                                                int64_t d, int64_t lda, float* __restrict__ H,
-                                                int64_t ldh, float alpha, float beta) {
-  __shared__ float sa[16][64];
-  __shared__ float sb[16][64];
-  const int tid = threadIdx.x;
-  const int64_t i0 = int64_t(blockIdx.y) * 64, j0 = int64_t(blockIdx.x) * 64;
-  const int ti = (tid >> 4) * 4, tj = (tid & 15) * 4;
-  float acc[4][4] = {};
-  for (int64_t t0 = 0; t0 < n_rows; t0 += 16) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int idx = tid + 256 * k;
-      const int r = idx >> 6, c = idx & 63;
-      const int64_t t = t0 + r;
-      sa[r][c] = (t < n_rows && i0 + c < d) ? A[t * lda + i0 + c] : 0.f;
-      sb[r][c] = (t < n_rows && j0 + c < d) ? B[t * lda + j0 + c] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float a[4], b[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        a[e] = sa[r][ti + e];
-        b[e] = sb[r][tj + e];
-      }
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = fmaf(a[x], b[y], acc[x][y]);
-    }
-    __syncthreads();
+// fp32 A^T B (B = A for the covariance) on the fp32 matrix cores, for fp32 inputs. There is no
+// workspace on this path, so the tokens are split inside the workgroup: one TM x TM output tile
+// per workgroup, its NW waves each over a contiguous share of the tokens, straight from memory
+// into the MFMA operands (an operand of v_mfma_f32_32x32x2f32 is two 128-byte row pieces, so
+// neither LDS nor a transpose is needed), and the NW partial tiles summed through LDS in a fixed
+// order. The covariance computes the tiles of one triangle and writes both.
+// Bound: latency at small d (a plain 64 x 64-tile FMA kernel took the 2048 tokens one 16-token
+// stage at a time on d^2 / 4096 workgroups, 304 us at d = 256), the operands' L1 traffic beyond.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+template <int TM>
+struct GramF32 {
+  static constexpr int NB = TM == 64 ? 2 : 1;      // MFMA blocks per tile edge
+  static constexpr int NW = TM == 64 ? 8 : 16;     // waves (token shares)
+  static constexpr int KT = TM == 16 ? 4 : 2;      // tokens per MFMA
+  static constexpr int UN = 8;                     // MFMA steps loaded ahead
+  static constexpr int E = TM * TM;                // partial tile, floats
+};
+
+template <int TM, bool CROSS>
+__global__ __launch_bounds__(64 * GramF32<TM>::NW) void gram_f32(
+    const float* __restrict__ A, const float* __restrict__ B, int64_t n_rows, int64_t d,
+    int64_t lda, int T, float* __restrict__ H, int64_t ldh, float alpha, float beta) {
+  using C = GramF32<TM>;
+  constexpr int BE = TM == 16 ? 16 : 32;  // MFMA block edge
+  extern __shared__ float red[];          // [NW][E]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int bi, bj;
+  if (CROSS) {
+    bi = int(blockIdx.x) / T, bj = int(blockIdx.x) % T;
+  } else {  // blockIdx.x = bj (bj + 1) / 2 + bi, bi <= bj
+    const int64_t lin = blockIdx.x;
+    int64_t j = int64_t((sqrt(8.0 * double(lin) + 1.0) - 1.0) * 0.5);
+    while (j * (j + 1) / 2 > lin) --j;
+    while ((j + 1) * (j + 2) / 2 <= lin) ++j;
+    bj = int(j), bi = int(lin - j * (j + 1) / 2);
   }
+  const int64_t i0 = int64_t(bi) * TM, j0 = int64_t(bj) * TM;
+  const int64_t share = cdiv(cdiv(n_rows, C::NW), C::KT) * C::KT;
+  const int64_t t_beg = share * wave < n_rows ? share * wave : n_rows;
+  const int64_t t_end = t_beg + share < n_rows ? t_beg + share : n_rows;
+  const int lm = lane & (BE - 1), lk = lane / BE;
+  // columns past d read the last one: they only reach outputs that are not stored
+  const float* pa[C::NB];
+  const float* pb[C::NB];
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+  for (int b = 0; b < C::NB; ++b) {
+    const int64_t ci = i0 + BE * b + lm, cj = j0 + BE * b + lm;
+    pa[b] = A + (ci < d ? ci : d - 1);
+    pb[b] = B + (cj < d ? cj : d - 1);
+  }
+  f32x16_t acc[C::NB][C::NB] = {};
+  f32x4_t acc4 = {};
+  auto step = [&](const float (&av)[C::NB], const float (&bv)[C::NB]) {
+    if constexpr (TM == 16) {
+      acc4 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[0], bv[0], acc4, 0, 0, 0);
+    } else {
 #pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      const int64_t i = i0 + ti + x, j = j0 + tj + y;
-      if (i < d && j < d) {
-        float* h = H + i * ldh + j;
-        *h = beta == 0.f ? alpha * acc[x][y] : alpha * acc[x][y] + beta * *h;
-      }
+      for (int x = 0; x < C::NB; ++x)
+#pragma unroll
+        for (int y = 0; y < C::NB; ++y)
+          acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[x], bv[y], acc[x][y], 0, 0, 0);
     }
+  };
+  int64_t t = t_beg;
+  for (; t + C::UN * C::KT <= t_end; t += C::UN * C::KT) {
+    float av[C::UN][C::NB], bv[C::UN][C::NB];
+#pragma unroll
+    for (int u = 0; u < C::UN; ++u)
+#pragma unroll
+      for (int b = 0; b < C::NB; ++b) {
+        const int64_t o = (t + u * C::KT + lk) * lda;
+        av[u][b] = pa[b][o];
+        bv[u][b] = pb[b][o];
+      }
+#pragma unroll
+    for (int u = 0; u < C::UN; ++u) step(av[u], bv[u]);
+  }
+  for (; t < t_end; t += C::KT) {  // the last tokens: both operands zero past the end
+    float av[C::NB], bv[C::NB];
+    const bool in = t + lk < t_end;
+    const int64_t o = (in ? t + lk : t_end - 1) * lda;
+#pragma unroll
+    for (int b = 0; b < C::NB; ++b) {
+      const float x = pa[b][o], y = pb[b][o];
+      av[b] = in ? x : 0.f;
+      bv[b] = in ? y : 0.f;
+    }
+    step(av, bv);
+  }
+  float* my = red + wave * C::E;  // [row i][column j] of the tile
+  if constexpr (TM == 16) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) my[(4 * lk + r) * TM + lm] = acc4[r];
+  } else {
+#pragma unroll
+    for (int x = 0; x < C::NB; ++x)
+#pragma unroll
+      for (int y = 0; y < C::NB; ++y)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          my[(32 * x + 8 * (r >> 2) + 4 * lk + (r & 3)) * TM + 32 * y + lm] = acc[x][y][r];
+  }
+  __syncthreads();
+  auto put = [&](int64_t gi, int64_t gj, float x) {
+    float* h = H + gi * ldh + gj;
+    *h = beta == 0.f ? alpha * x : alpha * x + beta * *h;
+  };
+  for (int e = tid; e < C::E; e += 64 * C::NW) {
+    float x = red[e];
+#pragma unroll
+    for (int w = 1; w < C::NW; ++w) x += red[w * C::E + e];
+    const int64_t gi = i0 + e / TM, gj = j0 + e % TM;
+    if (gi < d && gj < d && (CROSS || gi <= gj)) put(gi, gj, x);
+    if (!CROSS) red[e] = x;  // for the mirror (this thread alone reads and writes entry e)
+  }
+  if (CROSS) return;
+  __syncthreads();
+  for (int e = tid; e < C::E; e += 64 * C::NW) {  // H[j][i] for i < j, coalesced along i
+    const int jj = e / TM, ii = e % TM;
+    const int64_t gi = i0 + ii, gj = j0 + jj;
+    if (gi < d && gj < d && gi < gj) put(gj, gi, red[ii * TM + jj]);
+  }
 }
 
 // H <- beta H (no tokens)
@@ -700,6 +776,35 @@ __global__ void scale_matrix(float* __restrict__ H, int64_t d, int64_t ldh, floa
     float* h = H + i * ldh + j;
     *h = beta == 0.f ? 0.f : beta * *h;
   }
+}
+
+template <int TM, bool CROSS>
+int gram_f32_tiles(const float* A, const float* B, int64_t n_rows, int64_t d, int64_t lda,
+                   float* H, int64_t ldh, float alpha, float beta, hipStream_t s) {
+  using C = GramF32<TM>;
+  const int64_t T = cdiv(d, TM), tiles = CROSS ? T * T : T * (T + 1) / 2;
+  return launch(CROSS ? "cross_f32" : "syrk_f32", gram_f32<TM, CROSS>, dim3(unsigned(tiles)),
+                dim3(64 * C::NW), size_t(C::NW) * C::E * sizeof(float), s, A, B, n_rows, d, lda,
+                int(T), H, ldh, alpha, beta);
+}
+
+// The largest tile that still gives every CU a workgroup: at d = 256 (one triangle) 136 tiles of
+// 16, at d = 1024 528 tiles of 32, from d = 1600 tiles of 64. A larger tile reads its operands
+// fewer times; a smaller one puts more CUs to work.
+int gram_f32_launch(const float* A, const float* B, bool cross, int64_t n_rows, int64_t d,
+                    int64_t lda, float* H, int64_t ldh, float alpha, float beta, hipStream_t s) {
+  auto tiles = [&](int64_t tm) {
+    const int64_t T = cdiv(d, tm);
+    return cross ? T * T : T * (T + 1) / 2;
+  };
+  const int64_t cus = device_cus();
+#define KQ_GRAM_F32(TM)                                                                       \
+  (cross ? gram_f32_tiles<TM, true>(A, B, n_rows, d, lda, H, ldh, alpha, beta, s)             \
+         : gram_f32_tiles<TM, false>(A, B, n_rows, d, lda, H, ldh, alpha, beta, s))
+  if (tiles(64) >= cus) return KQ_GRAM_F32(64);
+  if (tiles(32) >= cus) return KQ_GRAM_F32(32);
+  return KQ_GRAM_F32(16);
+#undef KQ_GRAM_F32
 }
 
 struct CovPlan {
@@ -833,10 +938,9 @@ int cov_launch(const void* A, const void* B, int dtype, int64_t n_rows, int64_t 
                   0, s, H, d, ldh, beta);
   }
   if (dtype == KRONQ_FP32) {
-    const unsigned g = unsigned(cdiv(d, 64));
     const float* a = static_cast<const float*>(A);
-    return launch(B ? "cross_f32" : "syrk_f32", syrk_f32, dim3(g, g), dim3(256), 0, s, a,
-                  B ? static_cast<const float*>(B) : a, n_rows, d, lda, H, ldh, alpha, beta);
+    return gram_f32_launch(a, B ? static_cast<const float*>(B) : a, B != nullptr, n_rows, d, lda,
+                           H, ldh, alpha, beta, s);
   }
   return gram_bf16(static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B), n_rows, d,
                    lda, H, ldh, alpha, beta, ws, max_cus, s);
