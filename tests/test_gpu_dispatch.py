@@ -37,3 +37,48 @@ def test_cov_fp32_tiles(n, d, cross):
         assert np.all(np.abs(to_np(H) - ref) <= (n + 4) * 2.0 ** -24 * size)
         if not cross and beta == 0.0:
             assert np.array_equal(to_np(H), to_np(H).T)
+
+
+# ------------------------------------------------------- packed-code GEMV: widths and batches
+# one group of columns (seven waves without work), group counts that leave waves short of a tile,
+# the LDS limit (4 x 8192), several row blocks per workgroup, ragged last row block
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("d_out,d_in,group,batch", [
+    (1, 128, 128, 1), (17, 128, 128, 3), (33, 1152, 1152, 2), (40, 4224, 384, 3),
+    (48, 8192, 256, 4), (8200, 256, 128, 4), (50, 8192, 128, 1), (20, 28672, 128, 1)])
+def test_online_gemv_widths(d_out, d_in, group, batch, bits):
+    rng = np.random.default_rng(d_out + d_in + bits)
+    codes = rng.integers(0, 2 ** bits, size=(d_out, d_in)).astype(np.uint8)
+    scales = (rng.random((d_out, d_in // group)) + 0.5).astype(np.float32)
+    zeros = rng.integers(0, 2 ** bits, size=(d_out, d_in // group)).astype(np.float32)
+    x = rng.standard_normal((batch, d_in)).astype(np.float32)
+    x[:, ::97] *= 50.0  # outliers set their group's exponent
+    note(f"gemv {d_out}x{d_in} group={group} batch={batch} bits={bits}")
+    packed = K.kronq_pack_codes(torch.from_numpy(codes).to(DEV), bits)
+    if d_in * bits // 32 % 4:
+        pytest.skip("rows of packed codes are not 16-byte aligned")
+    y = K.kronq_online_matvec(packed, torch.from_numpy(scales).to(DEV),
+                              torch.from_numpy(zeros).to(DEV), bits, group, d_in, None, None, None,
+                              None, torch.from_numpy(x).to(DEV), flags=0)
+    torch.cuda.synchronize()
+    w = (codes.reshape(d_out, -1, group) - zeros[..., None].astype(np.float64)) * scales[..., None]
+    w = w.reshape(d_out, d_in)
+    ref = x.astype(np.float64) @ w.T
+    # digits: 2^-30 of a group's largest x' per element; fp32 sums over d_in / 128 groups and two
+    # roundings per term, of terms whose sizes add up to |x| (q + z) s
+    size = np.abs(x.astype(np.float64)) @ ((codes.reshape(d_out, -1, group)
+                                            + np.abs(zeros)[..., None] + 128.0 * (bits == 8))
+                                           * scales[..., None]).reshape(d_out, d_in).T
+    assert np.all(np.abs(to_np(y) - ref) <= (d_in // 128 + 8) * 2.0 ** -24 * size)
+
+
+def test_online_gemv_nonfinite_input():
+    """A NaN in one vector reaches all of its outputs and none of another vector's."""
+    packed = torch.zeros(32, 256 * 4 // 32, dtype=torch.int32, device=DEV)
+    sc, ze = torch.ones(32, 2, device=DEV), torch.ones(32, 2, device=DEV)
+    x = torch.ones(2, 256, device=DEV)
+    x[1, 7] = float("nan")
+    note("gemv NaN")
+    y = to_np(K.kronq_online_matvec(packed, sc, ze, 4, 128, 256, None, None, None, None, x,
+                                    flags=0))
+    assert np.all(y[0] == -256.0) and np.all(np.isnan(y[1]))
