@@ -184,28 +184,24 @@ enum GemmFlags : int {
   GEMM_UPPER_C = 64,    // only output tiles that touch the upper triangle (i <= j)
   GEMM_A_UPPER = 128,   // A is upper triangular: skip k < row-tile start
 };
-// C -= A B (+ A2 B2), A fp32 [M x K] (k contiguous), B given as the bf16 three-term split of
-// B^T (Bh + Bl, [N x K], k contiguous); likewise A2 [M x K2], B2; K % 32 == 0, K2 % 32 == 0
-struct Bf16x3Pair {
-  const float* A = nullptr;
-  int64_t lda = 0;
+// An operand pair of C += (Ah + Al)(Bh + Bl)^T (three bf16 products), both split beforehand into
+// bf16 high and low parts in MFMA-fragment order; aks / bks: 16-k units per 32-row group
+struct FragPair {
+  const uint16_t* Ah = nullptr;
+  const uint16_t* Al = nullptr;
+  int64_t aks = 0;
   const uint16_t* Bh = nullptr;
   const uint16_t* Bl = nullptr;
-  int64_t ldb = 0;
-  int64_t K = 0;
+  int64_t bks = 0;
+  int64_t K = 0;  // a multiple of 64
 };
-int gemm_bf16x3_sub(int64_t M, int64_t N, const Bf16x3Pair& p1, const Bf16x3Pair& p2, float* C,
-                    int64_t ldc, hipStream_t s, const char* name);
-// C -= (Ah + Al)(Bh + Bl)^T (three bf16 products) for operands split beforehand, [row][k]
-int gemm_bf16x3_presplit_sub(int64_t M, int64_t N, int64_t K, const uint16_t* Ah,
-                             const uint16_t* Al, int64_t lda, const uint16_t* Bh,
-                             const uint16_t* Bl, int64_t ldb, float* C, int64_t ldc,
-                             hipStream_t s, const char* name);
-// Th + Tl = sign * U^T split into bf16 high and low parts, [d x d] with row stride ldt
-// (sign = -1 when neg)
-int split_transpose_launch(const float* U, int64_t ldu, int64_t d, uint16_t* Th, uint16_t* Tl,
-                           int64_t ldt, hipStream_t s, bool neg = false, uint16_t* Fh = nullptr,
-                           uint16_t* Fl = nullptr);
+// C += the products of p1 and (when its K > 0) p2; the rows of the operands' last 32-row groups
+// exist up to M and N
+int gemm_frag_add(int64_t M, int64_t N, const FragPair& p1, const FragPair& p2, float* C,
+                  int64_t ldc, hipStream_t s, const char* name);
+// Fh + Fl = U^T split into bf16 high and low parts, in fragment order (d a multiple of 64)
+int split_transpose_launch(const float* U, int64_t ldu, int64_t d, uint16_t* Fh, uint16_t* Fl,
+                           hipStream_t s, const char* name);
 
 // Position of element (r, k) of a bf16 matrix kept in MFMA-fragment order for the operands of
 // v_mfma_f32_32x32x16_bf16: 32 rows x 16 k form one 1 KB unit in which lane

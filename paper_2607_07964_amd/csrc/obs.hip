@@ -1,40 +1,50 @@
 // Lazy-block column-wise OBS with group quantisation (eq. obs_update; Prop. 1 eq. kronq_update
 // with or without the drift correction P; Alg. 2).
 //
-// Per block of 128 columns:
-//   * sweep kernel: rows are independent given U, so each row is one 8-lane group of a wave
-//     (8 rows per wave, 32 rows per workgroup; with the drift correction 16-lane groups) and
-//     each lane keeps 16 (8) consecutive columns of the block in registers. Column j: the
-//     owning lane quantises it and forms the scaled error e_j = (w_j - w_hat_j) / U_jj, a DPP
-//     broadcast (two for 8-lane groups, one per half of a 16-lane DPP row) hands e_j to the
-//     rest of the group, and every lane applies it to its columns with U[j, its columns] read from the workgroup's
-//     LDS copy of the 128 x 128 block of U (upper triangular, so columns already done are left
-//     alone). With the drift correction a second broadcast hands out w_j as it stood before
-//     quantisation and every lane adds w_j P[j, its columns] from an LDS copy of the block of P
-//     (strictly upper). Codes, errors, the pre-quantisation values (drift) and dequantised
-//     values are written from registers at the end.
-//   * group parameters: a group of 128 columns takes them from the row's 128 values at the
-//     start of its block, inside the sweep kernel; a wider group (256, ..., d_in: the paper's
-//     per-channel grid is group = d_in) takes them from the row's current values over the whole
-//     group, in a reduction kernel launched when the sweep reaches the group's first block.
-//   * trailing updates, lazily in two levels: after each block, W[:, rest of its lazy group of
-//     (up to) 4 blocks] -= E_b U[b, rest of group] (K = 128); after the last block of a lazy
-//     group, W[:, beyond] -= E_group U[group, beyond] (K = 512). With the drift correction the
-//     same passes also add W_b P[b, ...], as a second K range of the same product. Every column
-//     receives the update of every earlier block before it is swept, as in the one-level scheme,
-//     with a quarter of the passes over W. The lazy group is shortened when needed so that a
-//     wide quantisation group lies inside one lazy group or starts one (its columns are then
-//     current when its parameters are taken). The products run on the bf16 matrix cores with
-//     the fp32-accurate three-term split (gemm_bf16x3.hip); U^T and -P^T are split once per
-//     layer.
+// Rows are independent given U. A sweep launch takes one lazy group of up to 4 blocks of 128
+// columns. Four waves share 32 rows of a block, each holding one 32-column tile of it in the
+// accumulator layout of the 32 x 32 matrix instructions (lane l and l + 32 share row l; of each
+// four columns in turn one half holds them), so that most updates are matrix instructions on the
+// registers the sweep works in:
+//   * pending: what the block owes to the lazy group's earlier blocks, sum_k E[row, k] U[k, col]
+//     over the K <= 384 columns swept before it (and X P with the drift correction), on the
+//     bf16 matrix cores from operands split into bf16 high and low parts and kept in
+//     MFMA-fragment order;
+//   * group parameters: a group of 128 columns takes them from the row's current 128 values; a
+//     wider group (256, ..., d_in: the paper's per-channel grid is group = d_in) in a reduction
+//     kernel launched when the sweep reaches the group's first block;
+//   * the columns: the wave that holds the tile sweeps it, four columns at a time (a quad). Both
+//     halves of the wave hold the quad's four values, quantise them one after another
+//     (e_j = (w_j - w_hat_j) / U_jj reaches the quad's later columns by FMAs) and apply the four
+//     errors to the next quad, taken from the half that holds it by v_permlane32_swap; the rest
+//     of the tile gets the rank-4 update from two v_mfma_f32_32x32x2f32. The errors go through
+//     LDS, one barrier a quad, to the waves of the later tiles, which apply the same update to
+//     theirs while the sweep goes on, and to the wave that writes the tile's results. With the
+//     drift correction w_j P[j, :], w_j as it stood before quantisation, is added the same way.
+// After the lazy group one product on the bf16 matrix cores updates everything beyond it
+// (gemm3_frag_add, K = 512). Every column receives all updates of earlier columns before its own
+// sweep, so this equals the paper's one-block-at-a-time update up to summation order.
+//
+// What bounds it: the chain of 128 quantisations a block. A wave that also updated the three
+// later tiles and wrote the results took 870 cycles a quad (fp32 matrix instructions hold up the
+// wave that issues them: 128 cycles a tile and quad); eight lanes a row with 16 columns in each
+// lane, one DPP broadcast and 16 FMAs a column, 26 us a block at 4096 rows and 103 us at 28672.
+// As it stands a block takes 20k cycles of sweep (625 a quad) and 4k to 12k of loads and pending
+// products before it: the sweeps of a 4096 x 4096 layer 0.56 ms (0.83 ms before), 28672 x 8192
+// 2.47 ms (6.6 ms before), 4096 x 4096 with P 0.69 ms (0.77 ms, and 0.41 ms of separate updates
+// within the lazy groups).
+//
 // The quantiser (reading of the paper's "quant"): xmin = min(0, min w), xmax = max(0, max w),
 // (-1, 1) when both are 0; scale = float32((xmax - xmin) / (2^b - 1)) in float64;
 // zero = rint(-xmin / scale); q = clamp(rint(w / scale) + zero, 0, 2^b - 1);
 // w_hat = float32(scale * (q - zero)). The code must be the one of the exact quotient w / scale
 // rounded half to even: the kernel forms t = w * (1 / scale) in fp32 (relative error below
-// 2.4e-7) and takes rint(t) unless t lies within 1e-6 (|t| + 1) of a half-integer, where it
-// falls back to the IEEE float64 division. w_hat in fp32 equals the float64 form exactly
-// (scale and q - zero are exact fp32 operands of one correctly rounded product).
+// 2.4e-7) and takes rint(t); when some t of a quad lies within 1e-6 (2^b + 1) of a half-integer
+// (beyond |t| = 2^b the code is clamped whatever t is) the quad is quantised again with the side
+// of the half-integer h decided by the sign of fma(-h, scale, w), which is exact. w_hat in fp32
+// equals the float64 form exactly (scale and q - zero are exact fp32 operands of one correctly
+// rounded product).
+#include <type_traits>
 #include <utility>
 
 #include "kq_common.hpp"
@@ -43,157 +53,28 @@ namespace kq {
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+#define KQ_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 
-// round-to-nearest-even fp32 -> bf16 bits (finite inputs)
-__device__ __forceinline__ uint32_t bf16_rne(float x) {
-  const uint32_t u = __float_as_uint(x);
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+constexpr int OB = 128;                  // block (and the smallest group)
+constexpr int LZMAX = 4;                 // blocks per lazy group (at most)
+constexpr int EKS = LZMAX * OB / 16;     // 16-k units per 32-row group of the split errors
+
+// a and b rounded to bf16 in one dword
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  const bf16x2_t v = __builtin_convertvector(f32x2_t{a, b}, bf16x2_t);
+  return __builtin_bit_cast(uint32_t, v);
 }
-
-constexpr int OB = 128;          // block (and the smallest group)
-constexpr int LZMAX = 4;         // blocks per lazy group of the P = 0 sweep (at most)
-// Lanes per row of the sweep kernel, a template parameter: 8 (16 columns per lane, 8 rows per
-// wave) or 16 (8 columns per lane, 4 rows per wave). 8 lanes halve the instructions per row,
-// which matters when the rows are many and the sweep is throughput-bound (d_out = 28672, or on
-// part of the chip beside the H_G covariance); 16 lanes give twice the waves for a small d_out,
-// whose sweep is latency-bound on the whole chip (d_out = 4096 alone: 20.6 against 26.2 us per
-// block). The drift correction uses 16: its second broadcast and P block would not fit the
-// registers of 16 columns.
-template <int L>
-struct SweepLayout {
-  static constexpr int LPR = L;          // lanes per row
-  static constexpr int CPL = OB / L;     // columns per lane
-  static constexpr int RPW = 64 / L;     // rows per wave
-  static constexpr int RPG = 4 * RPW;    // rows per workgroup (4 waves)
-};
-constexpr int GRP = 4;           // blocks per group of the two-level lazy update (at most)
-
-// v broadcast from lane `src` of each LPR-lane row group to the whole group (DPP row_newbcast
-// over a 16-lane DPP row; for 8-lane groups one per half of it, selected by the bank mask)
-template <int LPR, int src>
-__device__ __forceinline__ float row_bcast(float v) {
-  const int x = __float_as_int(v);
-  if constexpr (LPR == 16) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0x150 + src, 0xF, 0xF, false));
-  } else {
-    static_assert(LPR == 8, "row groups of 8 or 16 lanes");
-    const int lo = __builtin_amdgcn_update_dpp(x, x, 0x150 + src, 0xF, 0x3, false);
-    return __int_as_float(__builtin_amdgcn_update_dpp(lo, x, 0x150 + 8 + src, 0xF, 0xC, false));
+// four values as bf16 high and low parts, two dwords each
+__device__ __forceinline__ void split4(const float (&v)[4], uint32_t (&h)[2], uint32_t (&l)[2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    h[i] = pack_bf16(v[2 * i], v[2 * i + 1]);
+    l[i] = pack_bf16(v[2 * i] - __uint_as_float(h[i] << 16),
+                     v[2 * i + 1] - __uint_as_float(h[i] & 0xFFFF0000u));
   }
-}
-
-// an empty asm statement that reads and writes every element: its value must exist here
-template <int N>
-__device__ __forceinline__ void pin_regs(float (&w)[N]) {
-  static_assert(N % 4 == 0, "groups of four");
-#pragma unroll
-  for (int h = 0; h < N / 4; ++h)
-    asm volatile("" : "+v"(w[4 * h]), "+v"(w[4 * h + 1]), "+v"(w[4 * h + 2]), "+v"(w[4 * h + 3]));
-}
-
-struct SweepArgs {
-  const float* ub;    // U block in LDS, [OB][OB]
-  const float* pb;    // P block in LDS (drift only)
-  const float* rinv;  // 1 / U_jj
-  int sub, cb;
-  float scale, inv_s, fzero, fmaxq;
-  double dscale;
-};
-
-// one column of the sweep: j = CPL * OWN + S (compile-time). uc / rc hold U[j, this lane's
-// columns] and 1 / U_jj, read from LDS during the previous column; this column issues the reads
-// for column j + 1 first, so that their latency is hidden behind its own work.
-template <bool DRIFT, int L, int OWN, int S>
-__device__ __forceinline__ void sweep_col(float (&w)[SweepLayout<L>::CPL],
-                                          float (&ev)[SweepLayout<L>::CPL],
-                                          float (&xv)[SweepLayout<L>::CPL],
-                                          uint32_t (&qc)[SweepLayout<L>::CPL],
-                                          float (&uc)[SweepLayout<L>::CPL], float& rc,
-                                          const SweepArgs& a) {
-  constexpr int LPR = SweepLayout<L>::LPR, CPL = SweepLayout<L>::CPL;
-  constexpr int j = OWN * CPL + S;
-  float un[CPL];
-  float rn = 0.f;
-  if constexpr (j + 1 < OB) {
-#pragma unroll
-    for (int h = 0; h < CPL / 4; ++h) {
-      const float4 u = *reinterpret_cast<const float4*>(a.ub + (j + 1) * OB + a.cb + 4 * h);
-      un[4 * h] = u.x, un[4 * h + 1] = u.y, un[4 * h + 2] = u.z, un[4 * h + 3] = u.w;
-    }
-    rn = a.rinv[j + 1];
-  }
-  __builtin_amdgcn_sched_barrier(0);  // the reads go out before this column's work
-  const float x = w[S];
-  const float t = x * a.inv_s;
-  float qf = __builtin_rintf(t);
-  const bool tie = fabsf(t - floorf(t) - 0.5f) <= 1e-6f * (fabsf(t) + 1.f);
-  if (tie && a.sub == OWN) qf = float(__builtin_rint(double(x) / a.dscale));
-  const float q = fminf(fmaxf(qf + a.fzero, 0.f), a.fmaxq);
-  const float wh = a.scale * (q - a.fzero);
-  const float e = (x - wh) * rc;
-  if (a.sub == OWN) {
-    ev[S] = e;
-    qc[S] = uint32_t(q);
-    if (DRIFT) xv[S] = x;
-  }
-  const float eb = row_bcast<LPR, OWN>(e);
-  // the next column's update first: it is the one the next quantisation waits for
-  constexpr int nxt = (S + 1) % CPL;
-  w[nxt] = fmaf(-eb, uc[nxt], w[nxt]);
-#pragma unroll
-  for (int c = 0; c < CPL; ++c)
-    if (c != nxt) w[c] = fmaf(-eb, uc[c], w[c]);
-  if (DRIFT) {  // + w_j P[j, its columns], w_j as it stood before quantisation
-    const float xb = row_bcast<LPR, OWN>(x);
-#pragma unroll
-    for (int h = 0; h < CPL / 4; ++h) {
-      const float4 pv = *reinterpret_cast<const float4*>(a.pb + j * OB + a.cb + 4 * h);
-      w[4 * h + 0] = fmaf(xb, pv.x, w[4 * h + 0]);
-      w[4 * h + 1] = fmaf(xb, pv.y, w[4 * h + 1]);
-      w[4 * h + 2] = fmaf(xb, pv.z, w[4 * h + 2]);
-      w[4 * h + 3] = fmaf(xb, pv.w, w[4 * h + 3]);
-    }
-  }
-  // the column's updates are applied here, as soon as e_j exists: left to itself the compiler
-  // sinks each column's FMAs to just before that column is quantised, which turns them into
-  // one long chain of dependent FMAs on the sweep's critical path (and keeps every e_j and U
-  // value live in registers). An empty asm that reads and writes every w pins them here.
-  pin_regs(w);
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) uc[c] = un[c];
-  rc = rn;
-}
-
-template <bool DRIFT, int L, int OWN, int... S>
-__device__ __forceinline__ void sweep_lane_cols(std::integer_sequence<int, S...>,
-                                                float (&w)[SweepLayout<L>::CPL],
-                                                float (&ev)[SweepLayout<L>::CPL],
-                                                float (&xv)[SweepLayout<L>::CPL],
-                                                uint32_t (&qc)[SweepLayout<L>::CPL],
-                                                float (&uc)[SweepLayout<L>::CPL], float& rc,
-                                                const SweepArgs& a) {
-  (sweep_col<DRIFT, L, OWN, S>(w, ev, xv, qc, uc, rc, a), ...);
-}
-
-template <bool DRIFT, int L, int... OWN>
-__device__ __forceinline__ void sweep_all(std::integer_sequence<int, OWN...>,
-                                          float (&w)[SweepLayout<L>::CPL],
-                                          float (&ev)[SweepLayout<L>::CPL],
-                                          float (&xv)[SweepLayout<L>::CPL],
-                                          uint32_t (&qc)[SweepLayout<L>::CPL],
-                                          const SweepArgs& a) {
-  float uc[SweepLayout<L>::CPL];
-  constexpr int CPL = SweepLayout<L>::CPL;
-#pragma unroll
-  for (int h = 0; h < CPL / 4; ++h) {  // U row 0
-    const float4 u = *reinterpret_cast<const float4*>(a.ub + a.cb + 4 * h);
-    uc[4 * h] = u.x, uc[4 * h + 1] = u.y, uc[4 * h + 2] = u.z, uc[4 * h + 3] = u.w;
-  }
-  float rc = a.rinv[0];
-  (sweep_lane_cols<DRIFT, L, OWN>(std::make_integer_sequence<int, CPL>{}, w, ev, xv, qc, uc,
-                                  rc, a),
-   ...);
 }
 
 // (scale, zero) of a group from its range, the same float64 steps as the oracle's reading
@@ -239,229 +120,472 @@ __global__ __launch_bounds__(256) void obs_group_params(const float* __restrict_
   }
 }
 
-// Pending updates of this block (the P = 0 sweep): the workgroup's rows of
-// W[:, c0 : c0 + OB] still owe sum_k E[row, k] U[kp0 + k, c0 + n] over the kpend columns of the
-// lazy group swept before this block. One 32 x 32 MFMA block per wave (its 32 of the block's
-// 128 columns, rows row0 .. row0 + 31), K in steps of 16, on the bf16 matrix cores with the
-// three-term split: the earlier blocks' errors (Efh, Efl) and U^T (Ufh, Ufl) come split and in
-// MFMA-fragment order (split_frag_index), so that each fragment load of a wave is one contiguous
-// kilobyte (row-major operands cost 32 cache lines per load, which made this step take as long
-// as the column sweep itself). K runs in 64-wide steps whose 16 fragment loads are requested one
-// step ahead of the step's 12 MFMAs, and the three products accumulate separately (three
-// independent MFMA chains, summed at the end). The result lands in dl[row - row0][column].
-constexpr int EKS = LZMAX * OB / 16;  // 16-k units per 32-row group of the errors
-__device__ __forceinline__ void pending_update(const uint16_t* __restrict__ Efh,
-                                               const uint16_t* __restrict__ Efl,
-                                               const uint16_t* __restrict__ Ufh,
-                                               const uint16_t* __restrict__ Ufl, int64_t d_in,
-                                               int64_t kp0, int kpend, int64_t c0,
-                                               int64_t row0, int64_t d_out, int wave, int lane,
-                                               float (*dl)[OB + 4]) {
-  constexpr int KS = 64;  // k per step
-  const int l32 = lane & 31, lhi = lane >> 5;
-  const int64_t ra = row0 + l32 < d_out ? row0 + l32 : d_out - 1;  // rows past the end: unused
-  const int64_t eo = split_frag_index(ra, 8 * lhi, EKS);
-  const uint16_t* eh = Efh + eo;
-  const uint16_t* el = Efl + eo;
-  const int64_t uo = split_frag_index(c0 + wave * 32 + l32, kp0 + 8 * lhi, d_in / 16);
-  const uint16_t* bh = Ufh + uo;
-  const uint16_t* bl = Ufl + uo;
-  f32x16_t hh = {}, lh = {}, hl = {};
-  bf16x8_t f0[4][KS / 16], f1[4][KS / 16];  // [eh, el, uh, ul][k step of 16]
-  auto load = [&](bf16x8_t (&f)[4][KS / 16], int k0) {
+// LDS image of a 128 x 128 block of U (or P): its ten 32 x 32 tiles (I <= J), row by row (the two
+// rows a matrix operand reads at once lie in different banks)
+__device__ __forceinline__ int utile(int I, int J) { return (I * (9 - I) / 2 + J - I) * 1024; }
+constexpr int UTILES = 10;
+
+// a block of U into LDS in that image, one kilobyte (8 rows of a tile) per wave and load
+template <int NW>
+__device__ __forceinline__ void stage_block(const float* __restrict__ src, int64_t ld, float* dst,
+                                            int wave, int lane) {
 #pragma unroll
-    for (int ks = 0; ks < KS / 16; ++ks) {
+  for (int i = 0; i < UTILES * 4 / NW; ++i) {
+    const int u = wave + NW * i, tile = u >> 2;  // tile, quarter u % 4
+    const int I = tile < 4 ? 0 : tile < 7 ? 1 : tile < 9 ? 2 : 3;
+    const int J = tile - I * (9 - I) / 2 + I;
+    const int j = 32 * I + 8 * (u & 3) + (lane >> 3), c = 32 * J + 4 * (lane & 7);
+    __builtin_amdgcn_global_load_lds(src + int64_t(j) * ld + c, KQ_LDS(dst + u * 256), 16, 0, 0);
+  }
+}
+
+// acc += sum_k U[kp + k, col m] E[row, k], k < K (a multiple of 128), for one tile of 32 columns
+// and 32 rows: a wave's fragment loads are contiguous kilobytes, requested one step of KS k ahead
+// of the step's products; the three split products accumulate in three independent chains (with
+// KS = 32, where more waves share the registers and the matrix cores, in one). (The
+// scheduling barriers keep each step's loads ahead of the other step's products; left to itself
+// the compiler interleaves them and each product waits for a load issued just before. The load
+// after the last step re-reads it, in bounds: a skipped load would make the wait before the
+// products a full one on every step.)
+template <int KS>
+__device__ __forceinline__ void pending_update(const uint16_t* __restrict__ eh,
+                                               const uint16_t* __restrict__ el,
+                                               const uint16_t* __restrict__ uh,
+                                               const uint16_t* __restrict__ ul, int K,
+                                               f32x16_t& acc) {
+  constexpr int S = KS / 16;
+  constexpr bool SPLIT = KS == 64;
+  bf16x8_t f0[4][S], f1[4][S];  // [eh, el, uh, ul][k step of 16]
+  f32x16_t lh = {}, hl = {};
+  auto load = [&](bf16x8_t (&f)[4][S], int k0) {
+#pragma unroll
+    for (int ks = 0; ks < S; ++ks) {
       const int kk = (k0 + 16 * ks) * 32;  // next 16-k unit: 512 elements on
       f[0][ks] = *reinterpret_cast<const bf16x8_t*>(eh + kk);
       f[1][ks] = *reinterpret_cast<const bf16x8_t*>(el + kk);
-      f[2][ks] = *reinterpret_cast<const bf16x8_t*>(bh + kk);
-      f[3][ks] = *reinterpret_cast<const bf16x8_t*>(bl + kk);
+      f[2][ks] = *reinterpret_cast<const bf16x8_t*>(uh + kk);
+      f[3][ks] = *reinterpret_cast<const bf16x8_t*>(ul + kk);
     }
   };
-  auto mfmas = [&](const bf16x8_t (&f)[4][KS / 16]) {
+  auto mfmas = [&](const bf16x8_t (&f)[4][S]) {
 #pragma unroll
-    for (int ks = 0; ks < KS / 16; ++ks) {
-      lh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[1][ks], f[2][ks], lh, 0, 0, 0);
-      hl = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[0][ks], f[3][ks], hl, 0, 0, 0);
-      hh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[0][ks], f[2][ks], hh, 0, 0, 0);
+    for (int ks = 0; ks < S; ++ks) {
+      f32x16_t& l = SPLIT ? lh : acc;
+      f32x16_t& h = SPLIT ? hl : acc;
+      l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[3][ks], f[0][ks], l, 0, 0, 0);
+      h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[2][ks], f[1][ks], h, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[2][ks], f[0][ks], acc, 0, 0, 0);
     }
   };
-  // kpend is a multiple of 128: steps in pairs, the loads of each step one step ahead. The
-  // load after the last pair is issued too (it re-reads the last step, in bounds): a skipped
-  // load would make the wait before the second half's MFMAs a full one on every pair.
-  // (The scheduling barriers keep each step's loads ahead of the other step's MFMAs; left to
-  // itself the compiler interleaves them and each MFMA waits for a load issued just before.)
   load(f0, 0);
-  for (int k0 = 0; k0 < kpend; k0 += 2 * KS) {
+  for (int k0 = 0; k0 < K; k0 += 2 * KS) {
     load(f1, k0 + KS);
     __builtin_amdgcn_sched_barrier(0);
     mfmas(f0);
     __builtin_amdgcn_sched_barrier(0);
-    load(f0, k0 + 2 * KS < kpend ? k0 + 2 * KS : kpend - KS);
+    load(f0, k0 + 2 * KS < K ? k0 + 2 * KS : K - KS);
     __builtin_amdgcn_sched_barrier(0);
     mfmas(f1);
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r)
-    dl[8 * (r >> 2) + 4 * lhi + (r & 3)][wave * 32 + l32] = (lh[r] + hl[r]) + hh[r];
+    if (SPLIT) acc[r] += lh[r] + hl[r];
 }
 
-template <bool DRIFT, int L>
-__global__ __launch_bounds__(256) void obs_sweep(
-    float* __restrict__ W, int64_t d_out, int64_t ldw, const float* __restrict__ U, int64_t ldu,
-    const float* __restrict__ P, int64_t ldp, int64_t c0, int bits, uint8_t* __restrict__ codes,
-    int64_t ldq, float* __restrict__ scales, float* __restrict__ zeros, int64_t ldsz, int64_t gi,
-    int given, float* __restrict__ E, int64_t lde, float* __restrict__ Xq, int64_t ldxq,
-    float* __restrict__ W_hat, int64_t ldwh, uint16_t* __restrict__ Eh,
-    uint16_t* __restrict__ El, int64_t ldes, uint16_t* __restrict__ Efh,
-    uint16_t* __restrict__ Efl, const uint16_t* __restrict__ Ufh,
-    const uint16_t* __restrict__ Ufl, int64_t d_in, int64_t kp0, int kpend) {
-  __shared__ __attribute__((aligned(16))) float ub[OB * OB];  // U[c0 + j][c0 + k]
-  __shared__ __attribute__((aligned(16))) float pb[DRIFT ? OB * OB : 4];  // P[c0 + j][c0 + k]
-  __shared__ float rinv[OB];                                   // 1 / U_jj
-  constexpr int LPR = SweepLayout<L>::LPR, CPL = SweepLayout<L>::CPL;
-  constexpr int RPW = SweepLayout<L>::RPW, RPG = SweepLayout<L>::RPG;
-  // pending update: 32 rows (one MFMA block; with 16 rows per workgroup the second half is
-  // computed and left unused)
-  __shared__ __attribute__((aligned(16))) float dl[DRIFT ? 1 : 32][OB + 4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int sub = lane & (LPR - 1), cb = sub * CPL;
-  const int64_t row = int64_t(blockIdx.x) * RPG + wave * RPW + lane / LPR;
-  const bool live = row < d_out;
-  const int64_t rr = live ? row : d_out - 1;  // rows past the end recompute the last row
+// LDS writes of this wave done, then the workgroup barrier (global stores stay in flight)
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
 
-  // the U (and P) block: every load requested before the first store (a load-store pair per
-  // iteration would wait out one memory latency per iteration)
+// Where a row's results of a block go (a lane's row; rows past the end repeat the last row, value
+// for value)
+struct SweepOut {
+  float *w, *wh, *err;  // W, W_hat and the errors (the last two or NULL) at the block's column 0
+  uint8_t* codes;
+  uint16_t *eh, *el;    // -errors, split, in fragment order
+  uint16_t *xh, *xl;    // pre-quantisation values, the same (drift)
+};
+
+struct SweepIn {
+  const float* ub;    // U block in LDS (utile)
+  const float* pb;    // P block in LDS (drift)
+  const float4* rec;  // the quads' records in LDS (QuadU)
+  float4* pub;        // this row group's published quads: [2 tiles][8][NP][32 rows]
+  float scale, inv_s, lo, hi, fzero, near;  // near: 0.5 - the distance that asks for the exact side
+  int l32, half;
+};
+
+// What a quad needs of U (and P) in every lane, one record of float4s in LDS per quad, read a
+// quad ahead: slots 0, 1 hold U[j, k] of the quad's own columns (01 02 03 12 | 13 23), slot 2 the
+// 1 / U_jj, slots 3 .. 6 the rows' entries in the next quad's columns; 7, 8 and 9 .. 12 the same
+// of P.
+constexpr int REC = 8, RECD = 16;  // float4 per record (without, with P)
+template <bool DRIFT>
+struct QuadU {
+  float4 a, b, rc, nx[4];
+  float4 pa, pb, pnx[DRIFT ? 4 : 1];
+};
+__device__ __forceinline__ float comp(const float4& v, int i) {
+  return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
+}
+__device__ __forceinline__ float in_quad(const float4& a, const float4& b, int k, int i) {
+  return k == 0 ? comp(a, i - 1) : k == 1 ? (i == 2 ? a.w : b.x) : b.y;
+}
+
+template <bool DRIFT>
+__device__ __forceinline__ void read_quad(QuadU<DRIFT>& u, const float4* r, bool next) {
+  u.a = r[0], u.b = r[1], u.rc = r[2];
+  if (next) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) u.nx[k] = r[3 + k];
+  }
+  if (DRIFT) {
+    u.pa = r[7], u.pb = r[8];
+    if (next) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u.pnx[DRIFT ? k : 0] = r[9 + k];
+    }
+  }
+}
+
+// row j = 4 q + k of the block into quad q's record (k = 0 .. 3), from memory
+__device__ __forceinline__ void write_rec(const float* __restrict__ row, int q, int k, float* rec,
+                                          int slot, bool diag) {
+  const float4 in = *reinterpret_cast<const float4*>(row + 4 * q);
+  const float4 nx = q < 31 ? *reinterpret_cast<const float4*>(row + 4 * q + 4) : in;
+  if (k == 0) rec[4 * slot] = in.y, rec[4 * slot + 1] = in.z, rec[4 * slot + 2] = in.w;
+  if (k == 1) rec[4 * slot + 3] = in.z, rec[4 * slot + 4] = in.w;
+  if (k == 2) rec[4 * slot + 5] = in.w;
+  if (diag) rec[8 + k] = 1.f / comp(in, k);
+  reinterpret_cast<float4*>(rec)[slot + (diag ? 3 : 2) + k] = nx;
+}
+
+// quantise the quad's four columns: t by the reciprocal, or (EXACT) the side of the nearest
+// half-integer by an exact residual
+template <bool DRIFT, bool EXACT>
+__device__ __forceinline__ float quant4(const float (&x0)[4], const QuadU<DRIFT>& u,
+                                        const SweepIn& a, float (&x)[4], float (&ne)[4],
+                                        float (&qz)[4]) {
+  float far = 0.f;  // largest distance from the nearest integer
+#pragma unroll
+  for (int k = 0; k < 4; ++k) x[k] = x0[k];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float t = x[k] * a.inv_s;
+    float r = __builtin_rintf(t);
+    const float d = t - r;
+    if (EXACT) {
+      const float h = r + copysignf(0.5f, d);            // the half-integer next to t
+      const float res = fmaf(-h, a.scale, x[k]);         // exact sign of x / scale - h
+      const float up = h + 0.5f, dn = h - 0.5f;
+      const float even = 2.f * __builtin_rintf(0.5f * h);  // h +- 0.5, whichever is even
+      r = res > 0.f ? up : res < 0.f ? dn : res == 0.f ? even : r;
+    } else {
+      far = fmaxf(far, fabsf(d));
+    }
+    qz[k] = __builtin_amdgcn_fmed3f(r, a.lo, a.hi);      // q - zero
+    ne[k] = (a.scale * qz[k] - x[k]) * comp(u.rc, k);
+#pragma unroll
+    for (int i = k + 1; i < 4; ++i) {
+      x[i] = fmaf(ne[k], in_quad(u.a, u.b, k, i), x[i]);
+      if (DRIFT) x[i] = fmaf(x[k], in_quad(u.pa, u.pb, k, i), x[i]);
+    }
+  }
+  return far;
+}
+
+// the low half's value of four registers in every lane (hi: the upper half's)
+__device__ __forceinline__ void half_bcast(const float (&v)[4], bool hi, float (&o)[4]) {
+  float a[4], b[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = v[i], b[i] = v[i];
+  // (one wait state between the copies and the swaps, for all four)
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %4\n\tv_permlane32_swap_b32 %1, %5\n\t"
+      "v_permlane32_swap_b32 %2, %6\n\tv_permlane32_swap_b32 %3, %7"
+      : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]),
+        "+v"(b[3]));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) o[i] = hi ? b[i] : a[i];
+}
+
+// published values of a quad: -errors, q - zero (and x with the drift correction)
+template <bool DRIFT>
+constexpr int NP = DRIFT ? 3 : 2;
+template <bool DRIFT>
+__device__ __forceinline__ float4* pub_at(const SweepIn& a, int t, int q) {
+  return a.pub + ((t & 1) * 8 + q) * NP<DRIFT> * 32;
+}
+
+// the tile t sweep, by the wave that holds it
+template <bool DRIFT>
+__device__ __forceinline__ void sweep_tile(f32x16_t& acc, int t, const SweepIn& a) {
+  const float* ut = a.ub + utile(t, t) + a.half * 32 + a.l32;
+  const float* pt = DRIFT ? a.pb + utile(t, t) + a.half * 32 + a.l32 : nullptr;
+  const float4* rec = a.rec + t * 8 * (DRIFT ? RECD : REC);
+  QuadU<DRIFT> u;
+  read_quad<DRIFT>(u, rec, true);
+  float s[4];  // the quad's values, in both halves
   {
-    constexpr int NV = OB * OB / 4 / 256;
-    float4 uv[NV];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int idx = tid + 256 * i, j = idx / (OB / 4), k4 = (idx % (OB / 4)) * 4;
-      uv[i] = *reinterpret_cast<const float4*>(U + (c0 + j) * ldu + c0 + k4);
-    }
-#pragma unroll
-    for (int i = 0; i < NV; ++i) reinterpret_cast<float4*>(ub)[tid + 256 * i] = uv[i];
-    if (DRIFT) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int idx = tid + 256 * i, j = idx / (OB / 4), k4 = (idx % (OB / 4)) * 4;
-        uv[i] = *reinterpret_cast<const float4*>(P + (c0 + j) * ldp + c0 + k4);
-      }
-#pragma unroll
-      for (int i = 0; i < NV; ++i) reinterpret_cast<float4*>(pb)[tid + 256 * i] = uv[i];
-    }
+    const float held[4] = {acc[0], acc[1], acc[2], acc[3]};
+    half_bcast(held, false, s);
   }
-  if (tid < OB) rinv[tid] = 1.f / U[(c0 + tid) * ldu + c0 + tid];
-  float w[CPL];
 #pragma unroll
-  for (int h = 0; h < CPL / 4; ++h) {
-    const float4 v = *reinterpret_cast<const float4*>(W + rr * ldw + c0 + cb + 4 * h);
-    w[4 * h] = v.x, w[4 * h + 1] = v.y, w[4 * h + 2] = v.z, w[4 * h + 3] = v.w;
-  }
-  if constexpr (!DRIFT) {
-    if (kpend > 0) {  // uniform over the launch
-      pending_update(Efh, Efl, Ufh, Ufl, d_in, kp0, kpend, c0, int64_t(blockIdx.x) * RPG, d_out,
-                     wave, lane, dl);
-      __syncthreads();
-      const int rl = wave * RPW + lane / LPR;
+  for (int q = 0; q < 8; ++q) {
+    // this quad's update operands and the next quad's record; the reads go out before this
+    // quad's work
+    float ua[2], pa[2];
+    QuadU<DRIFT> un;
+    if (q < 6) {
 #pragma unroll
-      for (int h = 0; h < CPL / 4; ++h) {
-        const float4 v = *reinterpret_cast<const float4*>(&dl[rl][cb + 4 * h]);
-        w[4 * h] -= v.x, w[4 * h + 1] -= v.y, w[4 * h + 2] -= v.z, w[4 * h + 3] -= v.w;
+      for (int h = 0; h < 2; ++h) {
+        ua[h] = ut[(4 * q + 2 * h) * 32];
+        if (DRIFT) pa[h] = pt[(4 * q + 2 * h) * 32];
       }
     }
-  }
-  float scale, fzero;
-  if (given) {  // a wider group: parameters taken at its first block by obs_group_params
-    scale = scales[rr * ldsz + gi];
-    fzero = zeros[rr * ldsz + gi];
-  } else {  // group = block: parameters from the row's current 128 values
-    float xmin = 0.f, xmax = 0.f;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      xmin = fminf(xmin, w[c]);
-      xmax = fmaxf(xmax, w[c]);
-    }
-#pragma unroll
-    for (int o = 1; o < LPR; o <<= 1) {
-      xmin = fminf(xmin, __shfl_xor(xmin, o, LPR));
-      xmax = fmaxf(xmax, __shfl_xor(xmax, o, LPR));
-    }
-    grid_params(xmin, xmax, bits, scale, fzero);
-  }
-  __syncthreads();
-
-  float ev[CPL], xv[CPL];
-  uint32_t qc[CPL];
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) ev[c] = 0.f, xv[c] = 0.f, qc[c] = 0u;
-  const SweepArgs args{ub,          pb,    rinv, sub, cb, scale, 1.f / scale, fzero,
-                       float((1 << bits) - 1), double(scale)};
-  sweep_all<DRIFT, L>(std::make_integer_sequence<int, LPR>{}, w, ev, xv, qc, args);
-
-  if (!live) return;
-  if (sub == 0 && !given) {
-    scales[row * ldsz + gi] = scale;
-    zeros[row * ldsz + gi] = fzero;
-  }
-  float wh[CPL];
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) wh[c] = scale * (float(qc[c]) - fzero);
-#pragma unroll
-  for (int h = 0; h < CPL / 4; ++h) {
-    const float4 hv = make_float4(wh[4 * h], wh[4 * h + 1], wh[4 * h + 2], wh[4 * h + 3]);
-    *reinterpret_cast<float4*>(W + row * ldw + c0 + cb + 4 * h) = hv;
-    if (W_hat) *reinterpret_cast<float4*>(W_hat + row * ldwh + c0 + cb + 4 * h) = hv;
-    if (E)
-      *reinterpret_cast<float4*>(E + row * lde + cb + 4 * h) =
-          make_float4(ev[4 * h], ev[4 * h + 1], ev[4 * h + 2], ev[4 * h + 3]);
-    if (!DRIFT) {  // the errors split into bf16 high and low parts for the products after it
-      uint32_t hi[2], lo[2];
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const uint32_t h0 = bf16_rne(ev[4 * h + 2 * e]), h1 = bf16_rne(ev[4 * h + 2 * e + 1]);
-        const uint32_t l0 = bf16_rne(ev[4 * h + 2 * e] - __uint_as_float(h0 << 16));
-        const uint32_t l1 = bf16_rne(ev[4 * h + 2 * e + 1] - __uint_as_float(h1 << 16));
-        hi[e] = h0 | (h1 << 16);
-        lo[e] = l0 | (l1 << 16);
+    if (q < 7) read_quad<DRIFT>(un, rec + (q + 1) * (DRIFT ? RECD : REC), q < 6);
+    __builtin_amdgcn_sched_barrier(0);
+    float x[4], ne[4], qz[4];
+    const float far = quant4<DRIFT, false>(s, u, a, x, ne, qz);
+    if (__builtin_expect(__any(far >= a.near), 0)) quant4<DRIFT, true>(s, u, a, x, ne, qz);
+    float4* pub = pub_at<DRIFT>(a, t, q);
+    // the low half writes the errors, the upper half q - zero
+    float4 v;
+    v.x = a.half ? qz[0] : ne[0], v.y = a.half ? qz[1] : ne[1];
+    v.z = a.half ? qz[2] : ne[2], v.w = a.half ? qz[3] : ne[3];
+    pub[a.half * 32 + a.l32] = v;
+    if (DRIFT && a.half) pub[64 + a.l32] = make_float4(x[0], x[1], x[2], x[3]);
+    if (q < 7) {
+      // the next quad from the half that holds it, with this quad's errors; then the rest of
+      // the tile
+      const int r = 4 * ((q + 1) >> 1);
+      const float held[4] = {acc[r], acc[r + 1], acc[r + 2], acc[r + 3]};
+      half_bcast(held, (q + 1) & 1, s);
+      if (q < 6) {
+        const float e0 = a.half ? ne[1] : ne[0], e1 = a.half ? ne[3] : ne[2];
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ua[0], e0, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ua[1], e1, acc, 0, 0, 0);
+        if (DRIFT) {
+          const float x0 = a.half ? x[1] : x[0], x1 = a.half ? x[3] : x[2];
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[0], x0, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[1], x1, acc, 0, 0, 0);
+        }
       }
-      *reinterpret_cast<uint2*>(Eh + row * ldes + cb + 4 * h) = make_uint2(hi[0], hi[1]);
-      *reinterpret_cast<uint2*>(El + row * ldes + cb + 4 * h) = make_uint2(lo[0], lo[1]);
-      // and in fragment order for the in-kernel updates of the later blocks of the lazy group
-      // (column kpend + cb + 4 h of the group; four bf16 never straddle an 8-k fragment)
-      const int64_t f = split_frag_index(row, kpend + cb + 4 * h, EKS);
-      *reinterpret_cast<uint2*>(Efh + f) = make_uint2(hi[0], hi[1]);
-      *reinterpret_cast<uint2*>(Efl + f) = make_uint2(lo[0], lo[1]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s[i] = fmaf(ne[k], comp(u.nx[k], i), s[i]);
+          if (DRIFT) s[i] = fmaf(x[k], comp(u.pnx[DRIFT ? k : 0], i), s[i]);
+        }
+      u = un;
     }
-    if (DRIFT)
-      *reinterpret_cast<float4*>(Xq + row * ldxq + cb + 4 * h) =
-          make_float4(xv[4 * h], xv[4 * h + 1], xv[4 * h + 2], xv[4 * h + 3]);
-    reinterpret_cast<uint32_t*>(codes + row * ldq + c0 + cb)[h] =
-        qc[4 * h] | (qc[4 * h + 1] << 8) | (qc[4 * h + 2] << 16) | (qc[4 * h + 3] << 24);
+    lds_barrier();
   }
 }
 
-// Blocks per lazy group for a quantisation group of `group` columns: a group's parameters need
-// its columns current when the sweep reaches it, which holds when it lies inside one lazy group
-// or starts one. 0 when the group is not supported. (Drift path: the near updates are applied
-// after every block, so the whole lazy group is current.)
+// results of the pair of quads 2 p, 2 p + 1 of tile t: the low half writes the first, the upper
+// half the second
+template <bool DRIFT>
+__device__ __forceinline__ void write_pair(int t, int p, const SweepIn& a, const SweepOut& o) {
+  const float4* pub = pub_at<DRIFT>(a, t, 2 * p + a.half) + a.l32;
+  const float4 e4 = pub[0], z4 = pub[32];
+  const int c = 32 * t + 8 * p + 4 * a.half;  // the quad's first column
+  const int f = (2 * t + (p >> 1)) * 512 + (p & 1) * 256 + 4 * a.half;  // in fragment order
+  const float4 w4 =
+      make_float4(a.scale * z4.x, a.scale * z4.y, a.scale * z4.z, a.scale * z4.w);
+  *reinterpret_cast<float4*>(o.w + c) = w4;
+  if (o.wh) *reinterpret_cast<float4*>(o.wh + c) = w4;
+  if (o.err) *reinterpret_cast<float4*>(o.err + c) = make_float4(-e4.x, -e4.y, -e4.z, -e4.w);
+  *reinterpret_cast<uint32_t*>(o.codes + c) =
+      uint32_t(z4.x + a.fzero) | (uint32_t(z4.y + a.fzero) << 8) |
+      (uint32_t(z4.z + a.fzero) << 16) | (uint32_t(z4.w + a.fzero) << 24);
+  uint32_t hi[2], lo[2];
+  const float e[4] = {e4.x, e4.y, e4.z, e4.w};
+  split4(e, hi, lo);
+  *reinterpret_cast<uint2*>(o.eh + f) = make_uint2(hi[0], hi[1]);
+  *reinterpret_cast<uint2*>(o.el + f) = make_uint2(lo[0], lo[1]);
+  if (DRIFT) {
+    const float4 x4 = pub[64];
+    const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+    split4(x, hi, lo);
+    *reinterpret_cast<uint2*>(o.xh + f) = make_uint2(hi[0], hi[1]);
+    *reinterpret_cast<uint2*>(o.xl + f) = make_uint2(lo[0], lo[1]);
+  }
+}
+
+// the tile t sweep as seen by another wave: the update of its own tile (mine > t), and the
+// results when it is the tile's writer
+template <bool DRIFT>
+__device__ __forceinline__ void follow_tile(f32x16_t& acc, int t, int mine, bool writer,
+                                            const SweepIn& a, const SweepOut& o) {
+  const bool upd = mine > t;  // uniform over the wave
+  const int at = utile(t, upd ? mine : t) + a.half * 32 + a.l32;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    float ua[2], pa[2];
+    if (upd) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        ua[h] = a.ub[at + (4 * q + 2 * h) * 32];
+        if (DRIFT) pa[h] = a.pb[at + (4 * q + 2 * h) * 32];
+      }
+    }
+    lds_barrier();  // quad q is published
+    if (upd) {
+      const float4* pub = pub_at<DRIFT>(a, t, q) + a.l32;
+      const float4 e = pub[0];
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ua[0], a.half ? e.y : e.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ua[1], a.half ? e.w : e.z, acc, 0, 0, 0);
+      if (DRIFT) {
+        const float4 x = pub[64];
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[0], a.half ? x.y : x.x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[1], a.half ? x.w : x.z, acc, 0, 0, 0);
+      }
+    }
+    if (writer && (q & 1)) write_pair<DRIFT>(t, q >> 1, a, o);
+  }
+}
+
+struct SweepArgs {
+  float* W;
+  int64_t d_out, ldw;
+  const float* U;
+  int64_t ldu;
+  const float* P;
+  int64_t ldp, c_first;  // first column of the lazy group
+  int nblocks, bits;
+  uint8_t* codes;
+  int64_t ldq;
+  float *scales, *zeros;
+  int64_t ldsz;
+  int group;
+  float *err, *W_hat;
+  int64_t ldo;  // of err and W_hat
+  int cus;
+  uint16_t *Efh, *Efl, *Xfh, *Xfl;
+  const uint16_t *Ufh, *Ufl, *Pfh, *Pfl;
+  int64_t d_in;
+};
+
+// One lazy group for RG x 32 rows per workgroup, four waves per 32 rows. RG = 2 halves the LDS a
+// row takes (the U block is shared), so that a CU holds 128 rows: taken when RG = 1 would need
+// more than two workgroups a CU (see obs_launch).
+template <bool DRIFT, int RG>
+__global__ __launch_bounds__(256 * RG, DRIFT ? RG : 2 * RG) void obs_sweep(SweepArgs g) {
+  __shared__ __attribute__((aligned(16))) float ub[UTILES * 1024];
+  __shared__ __attribute__((aligned(16))) float pb[DRIFT ? UTILES * 1024 : 4];
+  __shared__ float4 rec[32 * (DRIFT ? RECD : REC)];
+  __shared__ float4 pub[RG * 16 * NP<DRIFT> * 32];
+  __shared__ float2 mm[RG][4][32];  // a tile's range of each row
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), rg = wave >> 2;
+  // This wave's tile. The waves of a SIMD (wave % 4; of both row groups, and of the workgroup
+  // that shares the CU, dispatched a round of CUs later) sweep at different times.
+  const int mine = (wave + 2 * rg + int(blockIdx.x / g.cus)) & 3;
+  const int64_t row0 = (int64_t(blockIdx.x) * RG + rg) * 32;
+  const bool active = row0 < g.d_out;  // uniform over the wave
+  const int64_t rf = active ? row0 : 0;  // (a row group past the end works on the first)
+#pragma unroll 1
+  for (int b = 0; b < g.nblocks; ++b) {
+    // an opaque copy of the thread index per block: the lane-dependent addresses are formed
+    // here, not hoisted out of the loop into (spilled) registers
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int64_t row = rf + l32 < g.d_out ? rf + l32 : g.d_out - 1;
+    const int64_t eo = split_frag_index(rf + l32, 8 * half, EKS);  // this lane as an operand
+    const int64_t es = split_frag_index(rf + l32, 0, EKS);         // its row as written
+    const int64_t c0 = g.c_first + int64_t(b) * OB;
+    stage_block<4 * RG>(g.U + c0 * g.ldu + c0, g.ldu, ub, wave, lane);
+    if (DRIFT) stage_block<4 * RG>(g.P + c0 * g.ldp + c0, g.ldp, pb, wave, lane);
+    if (tid < (DRIFT ? 256 : 128)) {
+      const int q = (tid & 127) >> 2, k = tid & 3;
+      float* r = reinterpret_cast<float*>(rec + q * (DRIFT ? RECD : REC));
+      if (tid < 128)
+        write_rec(g.U + (c0 + 4 * q + k) * g.ldu + c0, q, k, r, 0, true);
+      else if (DRIFT)
+        write_rec(g.P + (c0 + 4 * q + k) * g.ldp + c0, q, k, r, 7, false);
+    }
+    f32x16_t acc = {};
+    {
+      float4 w[4];
+      const float* wr = g.W + row * g.ldw + c0 + 32 * mine + 4 * half;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = *reinterpret_cast<const float4*>(wr + 8 * i);
+      if (b > 0) {
+        const int64_t uo =
+            split_frag_index(c0 + 32 * mine + l32, g.c_first + 8 * half, g.d_in / 16);
+        constexpr int KS = RG == 1 ? 64 : 32;
+        pending_update<KS>(g.Efh + eo, g.Efl + eo, g.Ufh + uo, g.Ufl + uo, b * OB, acc);
+        if (DRIFT) pending_update<KS>(g.Xfh + eo, g.Xfl + eo, g.Pfh + uo, g.Pfl + uo, b * OB, acc);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        acc[4 * i] += w[i].x, acc[4 * i + 1] += w[i].y;
+        acc[4 * i + 2] += w[i].z, acc[4 * i + 3] += w[i].w;
+      }
+    }
+    if (g.group == OB) {
+      float xmin = 0.f, xmax = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        xmin = fminf(xmin, acc[r]);
+        xmax = fmaxf(xmax, acc[r]);
+      }
+      xmin = fminf(xmin, __shfl_xor(xmin, 32));
+      xmax = fmaxf(xmax, __shfl_xor(xmax, 32));
+      if (!half) mm[rg][mine][l32] = make_float2(xmin, xmax);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of the U block is in LDS
+    __syncthreads();
+    const int64_t gi = c0 / g.group;
+    float scale, fzero;
+    if (g.group > OB) {  // taken at the group's first block by obs_group_params
+      scale = g.scales[row * g.ldsz + gi];
+      fzero = g.zeros[row * g.ldsz + gi];
+    } else {
+      float xmin = 0.f, xmax = 0.f;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float2 m = mm[rg][t][l32];
+        xmin = fminf(xmin, m.x);
+        xmax = fmaxf(xmax, m.y);
+      }
+      grid_params(xmin, xmax, g.bits, scale, fzero);
+      if (mine == 3 && active) {
+        g.scales[row * g.ldsz + gi] = scale;
+        g.zeros[row * g.ldsz + gi] = fzero;
+      }
+    }
+    const float maxq = float((1 << g.bits) - 1);
+    const SweepIn in{ub, pb, rec, pub + rg * 16 * NP<DRIFT> * 32, scale, 1.f / scale, -fzero,
+                     maxq - fzero, fzero, 0.5f - 1e-6f * (maxq + 2.f), l32, half};
+    const int64_t f = es + int64_t(b) * (OB / 16) * 512;
+    const SweepOut out{g.W + row * g.ldw + c0,
+                       g.W_hat ? g.W_hat + row * g.ldo + c0 : nullptr,
+                       g.err ? g.err + row * g.ldo + c0 : nullptr,
+                       g.codes + row * g.ldq + c0,
+                       g.Efh + f,
+                       g.Efl + f,
+                       DRIFT ? g.Xfh + f : nullptr,
+                       DRIFT ? g.Xfl + f : nullptr};
+#pragma unroll 1
+    for (int t = 0; t < 4; ++t) {
+      if (mine == t)
+        sweep_tile<DRIFT>(acc, t, in);
+      else  // the writer: the wave that has just swept its own tile (for tile 0 the last one)
+        follow_tile<DRIFT>(acc, t, mine, active && mine == ((t + 3) & 3), in, out);
+    }
+    __syncthreads();  // the errors are visible to the workgroup, the U block is free
+  }
+}
+
+// Blocks per lazy group. Pending updates reach a block only when the sweep gets there, so a
+// quantisation group's columns are all current at its first block only if that block starts a
+// lazy group (then every earlier update has been applied to everything after it): the lazy group
+// divides the quantisation group (up to LZMAX blocks); a group of one block, or the whole row
+// (parameters from the initial row), allows LZMAX. 0 when the group is not supported.
 int lazy_blocks(int64_t d_in, int group) {
-  if (group < OB || group % OB != 0 || d_in % group != 0) return 0;
-  const int m = group / OB;
-  if (GRP % m == 0 || m % GRP == 0 || group == d_in) return GRP;
-  for (int k = GRP - 1; k > 1; --k)
-    if (m % k == 0) return k;
-  return 1;
-}
-
-// Blocks per lazy group of the P = 0 sweep, whose pending updates reach a block only when the
-// sweep gets there: a quantisation group's columns are all current at its first block only if
-// that block starts a lazy group (then every earlier update has been applied to everything after
-// it). So the lazy group divides the quantisation group (up to LZMAX blocks); a group of one
-// block, or the whole row (parameters from the initial row), allows LZMAX.
-int lazy_blocks_pending(int64_t d_in, int group) {
   if (group < OB || group % OB != 0 || d_in % group != 0) return 0;
   const int m = group / OB;
   if (m == 1 || group == d_in) return LZMAX;
@@ -474,138 +598,69 @@ int lazy_blocks_pending(int64_t d_in, int group) {
 
 int obs_group_ok(int64_t d_in, int group) { return lazy_blocks(d_in, group); }
 
+// the split errors of a lazy group (and pre-quantisation values) and the split U^T (and P^T), in
+// fragment order
 size_t obs_ws_bytes(int64_t d_out, int64_t d_in, bool drift) {
   if (d_out <= 0 || d_in <= 0) return 0;
-  const size_t split_u = 2 * align256(size_t(d_in) * size_t(d_in) * sizeof(uint16_t));
-  if (!drift)  // split errors of a lazy group and split U^T, row-major and in fragment order
-    return 2 * align256(size_t(d_out) * LZMAX * OB * sizeof(uint16_t)) +
-           2 * align256(size_t(cdiv(d_out, 32) * 32) * LZMAX * OB * sizeof(uint16_t)) +
-           2 * split_u + 256;
-  // errors and pre-quantisation values of a lazy group, split U^T and -P^T
-  return 2 * (align256(size_t(d_out) * GRP * OB * sizeof(float)) + split_u) + 256;
+  const size_t rows = size_t(cdiv(d_out, 32) * 32);
+  const size_t one = 2 * align256(rows * LZMAX * OB * sizeof(uint16_t)) +
+                     2 * align256(size_t(d_in) * size_t(d_in) * sizeof(uint16_t));
+  return (drift ? 2 : 1) * one + 256;
 }
-
-namespace {
-
-// P = 0: one sweep launch per block, which first applies the updates the block still owes to
-// the earlier blocks of its lazy group (pending_update), then one trailing product per lazy
-// group for everything after it.
-int obs_launch_pending(float* W, int64_t d_out, int64_t d_in, int64_t ldw, const float* U,
-                       int64_t ldu, int bits, int group, uint8_t* codes, float* scales,
-                       float* zeros, float* err, float* W_hat, void* ws, hipStream_t s) {
-  const int64_t nblk = d_in / OB, ldsz = d_in / group;
-  const int lz = lazy_blocks_pending(d_in, group);
-  KQ_REQUIRE(lz > 0, KRONQ_ERR_UNSUPPORTED, "group %d not supported for d_in %lld", group,
-             (long long)d_in);
-  // 16 lanes per row only for a small d_out: beside the H_G covariance the sweep has part of
-  // the chip, where the 16-lane layout's twice as many workgroups (one per CU) take two rounds
-  // (8B q_proj layer: 11.31-11.39 ms per layer with 8 lanes, 11.46-11.48 with 16)
-  const bool lanes16 = d_out <= 2048;
-  const unsigned grid =
-      unsigned(cdiv(d_out, lanes16 ? SweepLayout<16>::RPG : SweepLayout<8>::RPG));
-  Carver cv(ws);
-  // the lazy group's errors, split into bf16 high and low parts [row][LZMAX * OB]
-  const int64_t ldes = LZMAX * OB;
-  uint16_t* Eh = cv.take<uint16_t>(size_t(d_out) * ldes);
-  uint16_t* El = cv.take<uint16_t>(size_t(d_out) * ldes);
-  uint16_t* Uth = cv.take<uint16_t>(size_t(d_in) * size_t(d_in));
-  uint16_t* Utl = cv.take<uint16_t>(size_t(d_in) * size_t(d_in));
-  // the same two, in MFMA-fragment order, for the sweep's in-kernel updates
-  uint16_t* Efh = cv.take<uint16_t>(size_t(cdiv(d_out, 32) * 32) * ldes);
-  uint16_t* Efl = cv.take<uint16_t>(size_t(cdiv(d_out, 32) * 32) * ldes);
-  uint16_t* Ufh = cv.take<uint16_t>(size_t(d_in) * size_t(d_in));
-  uint16_t* Ufl = cv.take<uint16_t>(size_t(d_in) * size_t(d_in));
-  KQ_TRY(split_transpose_launch(U, ldu, d_in, Uth, Utl, d_in, s, false, Ufh, Ufl));
-  for (int64_t g0 = 0; g0 < nblk; g0 += lz) {
-    const int64_t gend = g0 + lz < nblk ? g0 + lz : nblk;
-    for (int64_t b = g0; b < gend; ++b) {
-      const int64_t c0 = b * OB, gi = c0 / group, eo = (b - g0) * OB;
-      const int given = group > OB;
-      if (given && c0 % group == 0)
-        KQ_TRY(launch("obs_group_params", obs_group_params, dim3(unsigned(cdiv(d_out, 4))),
-                      dim3(256), 0, s, static_cast<const float*>(W), d_out, ldw, c0,
-                      int64_t(group), bits, scales, zeros, ldsz, gi));
-      KQ_TRY(launch("obs_sweep", lanes16 ? obs_sweep<false, 16> : obs_sweep<false, 8>,
-                    dim3(grid), dim3(256), 0, s, W, d_out, ldw, U, ldu,
-                    static_cast<const float*>(nullptr), int64_t(0), c0, bits, codes, d_in,
-                    scales, zeros, ldsz, gi, given, err ? err + c0 : static_cast<float*>(nullptr),
-                    d_in, static_cast<float*>(nullptr), int64_t(0), W_hat, d_in, Eh + eo, El + eo,
-                    ldes, Efh, Efl, static_cast<const uint16_t*>(Ufh),
-                    static_cast<const uint16_t*>(Ufl), d_in, g0 * OB, int(eo)));
-    }
-    const int64_t rem = d_in - gend * OB;  // beyond the lazy group
-    if (rem > 0) {
-      // W[:, gend*OB :] -= E_group U[g0*OB : gend*OB, gend*OB :]
-      const int64_t K = (gend - g0) * OB, off = gend * OB * d_in + g0 * OB;
-      KQ_TRY(gemm_bf16x3_presplit_sub(d_out, rem, K, Eh, El, ldes, Uth + off, Utl + off, d_in,
-                                      W + gend * OB, ldw, s, "obs_trailing_update"));
-    }
-  }
-  return KRONQ_OK;
-}
-
-}  // namespace
 
 int obs_launch(float* W, int64_t d_out, int64_t d_in, int64_t ldw, const float* U, int64_t ldu,
                int bits, int group, const float* P, int64_t ldp, uint8_t* codes, float* scales,
                float* zeros, float* err, float* W_hat, void* ws, hipStream_t s) {
-  if (P == nullptr)
-    return obs_launch_pending(W, d_out, d_in, ldw, U, ldu, bits, group, codes, scales, zeros,
-                              err, W_hat, ws, s);
-  // the drift correction: two-level lazy updates, near ones after every block
+  const bool drift = P != nullptr;
   const int64_t nblk = d_in / OB, ldsz = d_in / group;
   const int lz = lazy_blocks(d_in, group);
   KQ_REQUIRE(lz > 0, KRONQ_ERR_UNSUPPORTED, "group %d not supported for d_in %lld", group,
              (long long)d_in);
-  const unsigned grid = unsigned(cdiv(d_out, SweepLayout<16>::RPG));
   Carver cv(ws);
-  float* Ews = cv.take<float>(size_t(d_out) * GRP * OB);
-  uint16_t* Uth = cv.take<uint16_t>(size_t(d_in) * size_t(d_in));
-  uint16_t* Utl = cv.take<uint16_t>(size_t(d_in) * size_t(d_in));
-  float* Xws = cv.take<float>(size_t(d_out) * GRP * OB);
-  uint16_t* Pth = cv.take<uint16_t>(size_t(d_in) * size_t(d_in));
-  uint16_t* Ptl = cv.take<uint16_t>(size_t(d_in) * size_t(d_in));
-  // U^T and -P^T split once into bf16 high and low parts: the B operands of the trailing
-  // updates
-  KQ_TRY(split_transpose_launch(U, ldu, d_in, Uth, Utl, d_in, s));
-  KQ_TRY(split_transpose_launch(P, ldp, d_in, Pth, Ptl, d_in, s, true));
-  const int64_t ldx = GRP * OB;
+  const size_t fe = size_t(cdiv(d_out, 32) * 32) * LZMAX * OB, fu = size_t(d_in) * size_t(d_in);
+  SweepArgs a{};
+  a.W = W, a.d_out = d_out, a.ldw = ldw, a.U = U, a.ldu = ldu, a.P = P, a.ldp = ldp;
+  a.bits = bits, a.codes = codes, a.ldq = d_in, a.scales = scales, a.zeros = zeros;
+  a.ldsz = ldsz, a.group = group, a.err = err, a.W_hat = W_hat, a.ldo = d_in, a.d_in = d_in;
+  a.Efh = cv.take<uint16_t>(fe), a.Efl = cv.take<uint16_t>(fe);
+  uint16_t* ufh = cv.take<uint16_t>(fu);
+  uint16_t* ufl = cv.take<uint16_t>(fu);
+  KQ_TRY(split_transpose_launch(U, ldu, d_in, ufh, ufl, s, "obs_split_u"));
+  a.Ufh = ufh, a.Ufl = ufl;
+  if (drift) {
+    a.Xfh = cv.take<uint16_t>(fe), a.Xfl = cv.take<uint16_t>(fe);
+    uint16_t* pfh = cv.take<uint16_t>(fu);
+    uint16_t* pfl = cv.take<uint16_t>(fu);
+    KQ_TRY(split_transpose_launch(P, ldp, d_in, pfh, pfl, s, "obs_split_p"));
+    a.Pfh = pfh, a.Pfl = pfl;
+  }
+  // 32 rows a workgroup while the chip holds all of them (two workgroups per CU, one with the
+  // drift correction's P block), else 64. Measured (whole solve): 4096 x 4096 757 us with 32
+  // rows, 910 with 64; 14336 x 4096 1592 and 1662; 28672 x 8192 10.57 and 10.32 ms; with P 4096 x
+  // 4096 1.98 and 2.15 ms, 14336 x 4096 3.74 and 3.32 ms.
+  a.cus = device_cus();
+  const int64_t g32 = cdiv(d_out, 32);
+  const int rg = g32 <= int64_t(a.cus) * (drift ? 1 : 2) ? 1 : 2;
+  const dim3 grid(unsigned(cdiv(g32, rg))), block(unsigned(256 * rg));
+  auto kern = drift ? (rg == 1 ? obs_sweep<true, 1> : obs_sweep<true, 2>)
+                    : (rg == 1 ? obs_sweep<false, 1> : obs_sweep<false, 2>);
   for (int64_t g0 = 0; g0 < nblk; g0 += lz) {
     const int64_t gend = g0 + lz < nblk ? g0 + lz : nblk;
-    float* Eg = err ? err + g0 * OB : Ews;
-    const int64_t lde = err ? d_in : GRP * OB;
-    for (int64_t b = g0; b < gend; ++b) {
-      const int64_t c0 = b * OB;
-      float* Eb = Eg + (b - g0) * OB;
-      float* Xb = Xws + (b - g0) * OB;
-      const int64_t gi = c0 / group;
-      const int given = group > OB;
-      if (given && c0 % group == 0)
-        KQ_TRY(launch("obs_group_params", obs_group_params, dim3(unsigned(cdiv(d_out, 4))),
-                      dim3(256), 0, s, static_cast<const float*>(W), d_out, ldw, c0,
-                      int64_t(group), bits, scales, zeros, ldsz, gi));
-      KQ_TRY(launch("obs_sweep", obs_sweep<true, 16>, dim3(grid), dim3(256), 0, s, W, d_out, ldw, U,
-                    ldu, P, ldp, c0, bits, codes, d_in, scales, zeros, ldsz, gi, given, Eb, lde,
-                    Xb, ldx, W_hat, d_in, static_cast<uint16_t*>(nullptr),
-                    static_cast<uint16_t*>(nullptr), int64_t(0), static_cast<uint16_t*>(nullptr),
-                    static_cast<uint16_t*>(nullptr), static_cast<const uint16_t*>(nullptr),
-                    static_cast<const uint16_t*>(nullptr), d_in, int64_t(0), 0));
-      const int64_t near = (gend - b - 1) * OB;  // rest of the lazy group
-      if (near > 0) {
-        // W[:, c0+OB : gend*OB] -= E_b U[c0 : c0+OB, c0+OB : gend*OB] - X_b P[...]
-        Bf16x3Pair pu{Eb, lde, Uth + (c0 + OB) * d_in + c0, Utl + (c0 + OB) * d_in + c0, d_in,
-                      OB};
-        Bf16x3Pair pp{Xb, ldx, Pth + (c0 + OB) * d_in + c0, Ptl + (c0 + OB) * d_in + c0, d_in,
-                      OB};
-        KQ_TRY(gemm_bf16x3_sub(d_out, near, pu, pp, W + c0 + OB, ldw, s, "obs_trailing_update"));
-      }
-    }
+    a.c_first = g0 * OB;
+    a.nblocks = int(gend - g0);
+    if (group > OB && a.c_first % group == 0)
+      KQ_TRY(launch("obs_group_params", obs_group_params, dim3(unsigned(cdiv(d_out, 4))),
+                    dim3(256), 0, s, static_cast<const float*>(W), d_out, ldw, a.c_first,
+                    int64_t(group), bits, scales, zeros, ldsz, a.c_first / group));
+    KQ_TRY(launch("obs_sweep", kern, grid, block, 0, s, a));
     const int64_t rem = d_in - gend * OB;  // beyond the lazy group
     if (rem > 0) {
-      const int64_t K = (gend - g0) * OB, off = gend * OB * d_in + g0 * OB;
-      Bf16x3Pair pu{Eg, lde, Uth + off, Utl + off, d_in, K};
-      Bf16x3Pair pp{Xws, ldx, Pth + off, Ptl + off, d_in, K};
-      KQ_TRY(gemm_bf16x3_sub(d_out, rem, pu, pp, W + gend * OB, ldw, s, "obs_trailing_update"));
+      // W[:, gend*OB :] += (-E_group) U[g0*OB : gend*OB, gend*OB :] (+ X_group P[...])
+      const int64_t K = (gend - g0) * OB, off = split_frag_index(gend * OB, g0 * OB, d_in / 16);
+      const FragPair pu{a.Efh, a.Efl, EKS, a.Ufh + off, a.Ufl + off, d_in / 16, K};
+      FragPair pp{};
+      if (drift) pp = FragPair{a.Xfh, a.Xfl, EKS, a.Pfh + off, a.Pfl + off, d_in / 16, K};
+      KQ_TRY(gemm_frag_add(d_out, rem, pu, pp, W + gend * OB, ldw, s, "obs_trailing_update"));
     }
   }
   return KRONQ_OK;

@@ -82,3 +82,67 @@ def test_online_gemv_nonfinite_input():
     y = to_np(K.kronq_online_matvec(packed, sc, ze, 4, 128, 256, None, None, None, None, x,
                                     flags=0))
     assert np.all(y[0] == -256.0) and np.all(np.isnan(y[1]))
+
+
+# ------------------------------------------------------------------ sweep: row groups and ties
+def _solve(W, U, bits, group, P=None, err=False):
+    d_out, d_in = W.shape
+    Wd, Ud = (torch.from_numpy(np.ascontiguousarray(a)).to(DEV) for a in (W, U))
+    codes = torch.empty(d_out, d_in, dtype=torch.uint8, device=DEV)
+    sc, ze = (torch.empty(d_out, d_in // group, device=DEV) for _ in range(2))
+    E, Wh = torch.empty_like(Wd), torch.empty_like(Wd)
+    if P is None:
+        K.kronq_obs_quantize_layer(Wd, Ud, bits, codes, sc, ze, E if err else None, Wh, group)
+    else:
+        K.kronq_obs_quantize_layer_drift(Wd, Ud, torch.from_numpy(np.ascontiguousarray(P)).to(DEV), bits, codes, sc, ze,
+                                         E if err else None, Wh, group)
+    torch.cuda.synchronize()
+    return {k: to_np(v) for k, v in dict(codes=codes, scales=sc, zeros=ze, W=Wd, w_hat=Wh,
+                                         err=E).items()}
+
+
+# one and two row groups per workgroup (beyond 64 and, with P, 32 rows per CU), a ragged last
+# group of 32 rows, an idle second row group; lazy groups of 1 to 4 blocks, partly filled
+@pytest.mark.parametrize("d_out,d_in,group,drift", [
+    (1, 128, 128, False), (33, 640, 128, True), (31, 768, 384, False), (64, 1280, 1280, True),
+    (70, 1280, 640, False), (16417, 256, 128, False), (8225, 256, 128, True),
+    (20000, 384, 384, False)])
+def test_sweep_row_groups(d_out, d_in, group, drift):
+    rng = np.random.default_rng(d_out + d_in)
+    X = rng.standard_normal((4 * d_in, d_in))
+    U = O.inverse_cholesky_factor(O.damp(X.T @ X)).astype(np.float32)
+    P = None
+    if drift:
+        P = (np.triu(rng.standard_normal((d_in, d_in)), 1) * 0.02).astype(np.float32)
+    W = (rng.standard_normal((d_out, d_in)) * 0.02).astype(np.float32)
+    note(f"sweep {d_out}x{d_in} group={group} drift={drift}")
+    got = _solve(W, U, 4, group, P, err=True)
+    ref = O.obs_blocked(W, U, 4, group, 128, P=P)
+    # fp32 rounding moves near ties; all that follows in such a row moves with them
+    same = np.all(got["codes"] == ref["codes"], axis=1)
+    assert np.mean(got["codes"] == ref["codes"]) > 0.9999 and np.mean(same) > 0.99
+    assert np.allclose(got["scales"][same], ref["scales"][same], rtol=1e-5)
+    assert np.array_equal(got["zeros"][same], ref["zeros"][same])
+    assert rel_frob(got["err"][same], ref["err"][same]) < 1e-4
+    assert np.array_equal(got["W"], got["w_hat"])
+    g = np.repeat(np.arange(d_in // group), group)
+    deq = got["scales"][:, g] * (got["codes"].astype(np.float32) - got["zeros"][:, g])
+    assert np.array_equal(got["w_hat"], deq)
+
+
+def test_sweep_exact_ties():
+    """Values on and one ulp beside the half-integers of a power-of-two and of another scale, with
+    U = I (no compensation): the codes are those of the exact quotient, ties to even."""
+    rng = np.random.default_rng(5)
+    rows, bits = 96, 4
+    scale = np.where(np.arange(rows) % 2 == 0, 0.25, rng.uniform(0.1, 0.3, rows)).astype(np.float32)
+    n = rng.integers(0, 15, size=(rows, 128))
+    W = ((n + 0.5).astype(np.float64) * scale[:, None]).astype(np.float32)
+    kick = rng.integers(-1, 2, size=W.shape)
+    W = np.where(kick > 0, np.nextafter(W, np.float32(9)), W)
+    W = np.where(kick < 0, np.nextafter(W, np.float32(0)), W).astype(np.float32)
+    W[:, 0], W[:, 1] = 0.0, (15.0 * scale.astype(np.float64)).astype(np.float32)
+    note("sweep exact ties")
+    got = _solve(W, np.eye(128, dtype=np.float32), bits, 128)
+    ref = O.obs_blocked(W, np.eye(128), bits, 128, 128)
+    assert np.array_equal(got["codes"], ref["codes"])
