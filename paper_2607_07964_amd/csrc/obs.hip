@@ -44,6 +44,7 @@
 // of the half-integer h decided by the sign of fma(-h, scale, w), which is exact. w_hat in fp32
 // equals the float64 form exactly (scale and q - zero are exact fp32 operands of one correctly
 // rounded product).
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -599,13 +600,14 @@ int lazy_blocks(int64_t d_in, int group) {
 int obs_group_ok(int64_t d_in, int group) { return lazy_blocks(d_in, group); }
 
 // the split errors of a lazy group (and pre-quantisation values) and the split U^T (and P^T), in
-// fragment order
+// fragment order; without P never less than four planes of U's size, which a caller may count on
 size_t obs_ws_bytes(int64_t d_out, int64_t d_in, bool drift) {
   if (d_out <= 0 || d_in <= 0) return 0;
   const size_t rows = size_t(cdiv(d_out, 32) * 32);
   const size_t one = 2 * align256(rows * LZMAX * OB * sizeof(uint16_t)) +
                      2 * align256(size_t(d_in) * size_t(d_in) * sizeof(uint16_t));
-  return (drift ? 2 : 1) * one + 256;
+  const size_t floor = drift ? 0 : 4 * align256(size_t(d_in) * size_t(d_in) * sizeof(uint16_t));
+  return std::max((drift ? 2 : 1) * one, floor) + 256;
 }
 
 int obs_launch(float* W, int64_t d_out, int64_t d_in, int64_t ldw, const float* U, int64_t ldu,
