@@ -192,11 +192,22 @@ int gemm_frag_add(int64_t M, int64_t N, const FragPair& p1, const FragPair& p2, 
   if (M <= 0 || N <= 0 || p1.K + p2.K <= 0) return KRONQ_OK;
   KQ_REQUIRE(p1.K % (2 * BK) == 0 && p2.K % (2 * BK) == 0, KRONQ_ERR_INVALID_ARG,
              "gemm_frag_add: K %% 64 must be 0");
-  const bool big = cdiv(M, 128) * cdiv(N, 128) >= 192;
-  const int64_t t = big ? 128 : 64;
-  return launch(name, big ? gemm3_frag_add<128> : gemm3_frag_add<64>,
-                dim3(unsigned(cdiv(N, t)), unsigned(cdiv(M, t))), dim3(256), 0, s, M, N, p1, p2, C,
-                ldc);
+  // the largest tile that fills three quarters of the chip: 256 x 256 (one workgroup a CU) reads
+  // its operands half as often as 128 x 128 (two a CU)
+  const int64_t cus = device_cus();
+  const int tile = cdiv(M, 256) * cdiv(N, 256) * 4 >= cus * 3   ? 256
+                   : cdiv(M, 128) * cdiv(N, 128) * 4 >= cus * 3 ? 128
+                                                                : 64;
+  if (tile > 64) {
+    FragJob j{};
+    j.Ph = p1.Ah, j.Pl = p1.Al, j.pks = p1.aks, j.Qh = p1.Bh, j.Ql = p1.Bl, j.qks = p1.bks;
+    j.M = M, j.N = N, j.K = p1.K, j.K2 = p2.K;
+    j.P2h = p2.Ah, j.P2l = p2.Al, j.Q2h = p2.Bh, j.Q2l = p2.Bl;
+    j.alpha = 1.f, j.C = C, j.ldc = ldc, j.add = true;
+    return gemm_frag_bf16(j, tile, s, name);
+  }
+  return launch(name, gemm3_frag_add<64>, dim3(unsigned(cdiv(N, 64)), unsigned(cdiv(M, 64))),
+                dim3(256), 0, s, M, N, p1, p2, C, ldc);
 }
 
 }  // namespace kq

@@ -184,8 +184,59 @@ enum GemmFlags : int {
   GEMM_UPPER_C = 64,    // only output tiles that touch the upper triangle (i <= j)
   GEMM_A_UPPER = 128,   // A is upper triangular: skip k < row-tile start
 };
-// An operand pair of C += (Ah + Al)(Bh + Bl)^T (three bf16 products), both split beforehand into
-// bf16 high and low parts in MFMA-fragment order; aks / bks: 16-k units per 32-row group
+// ---- products of operands split into two 16-bit planes in MFMA-fragment order -----------------
+enum FragFlags : int {
+  FRAG_P_LOWER = 1,   // P[m][k] = 0 for k > m
+  FRAG_P_UPPER = 2,   // P[m][k] = 0 for k < m
+  FRAG_Q_LOWER = 4,   // Q[n][k] = 0 for k > n
+  FRAG_Q_UPPER = 8,   // Q[n][k] = 0 for k < n
+  FRAG_LOWER = 16,    // only the tiles that touch n <= m
+  FRAG_UPPER = 32,    // only the tiles that touch n >= m
+};
+// D = alpha P Q^T (+ P2 Q2^T over K2): P [M x K] and Q [N x K] as planes (pks, qks: 16-k units per
+// 32-row group, the planes' rows padded to whole groups and K to whole units with zeros).
+// C[m][n] = D (or += D with add), times punit[m] qunit[n] when given; or, with Oh (fp16 planes
+// only), the planes of D^T: row n, k = m, oks units per group.
+struct FragJob {
+  const uint16_t *Ph, *Pl;
+  int64_t pks;
+  const uint16_t *Qh, *Ql;
+  int64_t qks;
+  int64_t M, N, K;
+  const uint16_t *P2h, *P2l, *Q2h, *Q2l;
+  int64_t K2;
+  int flags;
+  float alpha;
+  float* C;
+  int64_t ldc;
+  bool add;
+  const float *punit, *qunit;
+  uint16_t *Oh, *Ol;
+  int64_t oks;
+};
+// tile: 256 or 128
+int gemm_frag_bf16(const FragJob& j, int tile, hipStream_t s, const char* name);
+// one or two independent products in one launch
+int gemm_frag_f16(const FragJob* jobs, int n, int tile, hipStream_t s, const char* name);
+
+// fp16 planes of the fp32 matrix src [rows x cols] (16-byte aligned rows), or of its transpose,
+// times scale or divided by unit[row] (unit[column] of src when trans); powers of two
+enum SplitTri : int { SPLIT_FULL = 0, SPLIT_LOWER, SPLIT_UPPER, SPLIT_STRICT_UPPER };
+struct SplitJob {
+  const float* src;
+  int64_t ld, rows, cols;
+  int tri;     // the part of src that is read; zeros elsewhere
+  bool trans;
+  float scale;
+  const float* unit;
+  uint16_t *Oh, *Ol;
+  int64_t ks;  // 16-k units per 32-row group of the planes
+};
+// up to three matrices in one launch
+int split_planes_launch(const SplitJob* jobs, int n, hipStream_t s, const char* name);
+
+// An operand pair of C += (Ah + Al)(Bh + Bl)^T on 64 x 64 tiles, for outputs too small for the
+// tiles above (bf16 planes); aks / bks: 16-k units per 32-row group
 struct FragPair {
   const uint16_t* Ah = nullptr;
   const uint16_t* Al = nullptr;
@@ -195,8 +246,7 @@ struct FragPair {
   int64_t bks = 0;
   int64_t K = 0;  // a multiple of 64
 };
-// C += the products of p1 and (when its K > 0) p2; the rows of the operands' last 32-row groups
-// exist up to M and N
+// C += the products of p1 and (when its K > 0) p2, on the tiles that suit its size
 int gemm_frag_add(int64_t M, int64_t N, const FragPair& p1, const FragPair& p2, float* C,
                   int64_t ldc, hipStream_t s, const char* name);
 // Fh + Fl = U^T split into bf16 high and low parts, in fragment order (d a multiple of 64)

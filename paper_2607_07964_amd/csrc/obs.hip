@@ -21,9 +21,10 @@
 //     LDS, one barrier a quad, to the waves of the later tiles, which apply the same update to
 //     theirs while the sweep goes on, and to the wave that writes the tile's results. With the
 //     drift correction w_j P[j, :], w_j as it stood before quantisation, is added the same way.
-// After the lazy group one product on the bf16 matrix cores updates everything beyond it
-// (gemm3_frag_add, K = 512). Every column receives all updates of earlier columns before its own
-// sweep, so this equals the paper's one-block-at-a-time update up to summation order.
+// Between lazy groups, products on the bf16 matrix cores bring the errors to the columns beyond
+// (gemm_frag_add; see obs_launch for their order). Every column receives all updates of earlier
+// columns before its own sweep, so this equals the paper's one-block-at-a-time update up to
+// summation order.
 //
 // What bounds it: the chain of 128 quantisations a block. A wave that also updated the three
 // later tiles and wrote the results took 870 cycles a quad (fp32 matrix instructions hold up the
@@ -61,7 +62,6 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int OB = 128;                  // block (and the smallest group)
 constexpr int LZMAX = 4;                 // blocks per lazy group (at most)
-constexpr int EKS = LZMAX * OB / 16;     // 16-k units per 32-row group of the split errors
 
 // a and b rounded to bf16 in one dword
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
@@ -494,8 +494,8 @@ __global__ __launch_bounds__(256 * RG, DRIFT ? RG : 2 * RG) void obs_sweep(Sweep
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int64_t row = rf + l32 < g.d_out ? rf + l32 : g.d_out - 1;
-    const int64_t eo = split_frag_index(rf + l32, 8 * half, EKS);  // this lane as an operand
-    const int64_t es = split_frag_index(rf + l32, 0, EKS);         // its row as written
+    const int64_t eo =
+        split_frag_index(rf + l32, g.c_first + 8 * half, g.d_in / 16);  // operand
     const int64_t c0 = g.c_first + int64_t(b) * OB;
     stage_block<4 * RG>(g.U + c0 * g.ldu + c0, g.ldu, ub, wave, lane);
     if (DRIFT) stage_block<4 * RG>(g.P + c0 * g.ldp + c0, g.ldp, pb, wave, lane);
@@ -561,7 +561,7 @@ __global__ __launch_bounds__(256 * RG, DRIFT ? RG : 2 * RG) void obs_sweep(Sweep
     const float maxq = float((1 << g.bits) - 1);
     const SweepIn in{ub, pb, rec, pub + rg * 16 * NP<DRIFT> * 32, scale, 1.f / scale, -fzero,
                      maxq - fzero, fzero, 0.5f - 1e-6f * (maxq + 2.f), l32, half};
-    const int64_t f = es + int64_t(b) * (OB / 16) * 512;
+    const int64_t f = split_frag_index(rf + l32, c0, g.d_in / 16);  // its row as written
     const SweepOut out{g.W + row * g.ldw + c0,
                        g.W_hat ? g.W_hat + row * g.ldo + c0 : nullptr,
                        g.err ? g.err + row * g.ldo + c0 : nullptr,
@@ -599,12 +599,12 @@ int lazy_blocks(int64_t d_in, int group) {
 
 int obs_group_ok(int64_t d_in, int group) { return lazy_blocks(d_in, group); }
 
-// the split errors of a lazy group (and pre-quantisation values) and the split U^T (and P^T), in
-// fragment order; without P never less than four planes of U's size, which a caller may count on
+// the split errors (and pre-quantisation values) and the split U^T (and P^T), in fragment order;
+// without P never less than four planes of U's size, which a caller may count on
 size_t obs_ws_bytes(int64_t d_out, int64_t d_in, bool drift) {
   if (d_out <= 0 || d_in <= 0) return 0;
   const size_t rows = size_t(cdiv(d_out, 32) * 32);
-  const size_t one = 2 * align256(rows * LZMAX * OB * sizeof(uint16_t)) +
+  const size_t one = 2 * align256(rows * size_t(d_in) * sizeof(uint16_t)) +
                      2 * align256(size_t(d_in) * size_t(d_in) * sizeof(uint16_t));
   const size_t floor = drift ? 0 : 4 * align256(size_t(d_in) * size_t(d_in) * sizeof(uint16_t));
   return std::max((drift ? 2 : 1) * one, floor) + 256;
@@ -619,7 +619,7 @@ int obs_launch(float* W, int64_t d_out, int64_t d_in, int64_t ldw, const float* 
   KQ_REQUIRE(lz > 0, KRONQ_ERR_UNSUPPORTED, "group %d not supported for d_in %lld", group,
              (long long)d_in);
   Carver cv(ws);
-  const size_t fe = size_t(cdiv(d_out, 32) * 32) * LZMAX * OB, fu = size_t(d_in) * size_t(d_in);
+  const size_t fe = size_t(cdiv(d_out, 32) * 32) * size_t(d_in), fu = size_t(d_in) * size_t(d_in);
   SweepArgs a{};
   a.W = W, a.d_out = d_out, a.ldw = ldw, a.U = U, a.ldu = ldu, a.P = P, a.ldp = ldp;
   a.bits = bits, a.codes = codes, a.ldq = d_in, a.scales = scales, a.zeros = zeros;
@@ -646,6 +646,14 @@ int obs_launch(float* W, int64_t d_out, int64_t d_in, int64_t ldw, const float* 
   const dim3 grid(unsigned(cdiv(g32, rg))), block(unsigned(256 * rg));
   auto kern = drift ? (rg == 1 ? obs_sweep<true, 1> : obs_sweep<true, 2>)
                     : (rg == 1 ? obs_sweep<false, 1> : obs_sweep<false, 2>);
+  // Trailing products by halving: every earlier lazy group s reaches group g through the product
+  // at the t of s < t <= g with the most trailing zeros, so a column of W is read and written
+  // about log2(groups) times instead of once per earlier lazy group, and most of the work has a
+  // long K. A wide quantisation group takes its parameters from current columns at its first
+  // block t: all of [t, t + 2^v) are current then, so it must be a power of two of lazy groups
+  // (or the whole row, which takes them from the initial row).
+  const int64_t gl = cdiv(group, int64_t(lz) * OB);
+  const bool halving = group == d_in || (gl & (gl - 1)) == 0;
   for (int64_t g0 = 0; g0 < nblk; g0 += lz) {
     const int64_t gend = g0 + lz < nblk ? g0 + lz : nblk;
     a.c_first = g0 * OB;
@@ -655,15 +663,17 @@ int obs_launch(float* W, int64_t d_out, int64_t d_in, int64_t ldw, const float* 
                     dim3(256), 0, s, static_cast<const float*>(W), d_out, ldw, a.c_first,
                     int64_t(group), bits, scales, zeros, ldsz, a.c_first / group));
     KQ_TRY(launch("obs_sweep", kern, grid, block, 0, s, a));
-    const int64_t rem = d_in - gend * OB;  // beyond the lazy group
-    if (rem > 0) {
-      // W[:, gend*OB :] += (-E_group) U[g0*OB : gend*OB, gend*OB :] (+ X_group P[...])
-      const int64_t K = (gend - g0) * OB, off = split_frag_index(gend * OB, g0 * OB, d_in / 16);
-      const FragPair pu{a.Efh, a.Efl, EKS, a.Ufh + off, a.Ufl + off, d_in / 16, K};
-      FragPair pp{};
-      if (drift) pp = FragPair{a.Xfh, a.Xfl, EKS, a.Pfh + off, a.Pfl + off, d_in / 16, K};
-      KQ_TRY(gemm_frag_add(d_out, rem, pu, pp, W + gend * OB, ldw, s, "obs_trailing_update"));
-    }
+    if (gend * OB >= d_in) break;
+    // after lazy group t - 1: with halving, the p = 2^v lazy groups before t update the p after it
+    // (v the number of trailing zeros of t), else the last one everything after it
+    const int64_t t = gend / lz, p = halving ? (t & -t) : 1;
+    const int64_t k0 = (t - p) * lz * OB, K = p * lz * OB, n0 = gend * OB;
+    const int64_t N = halving && K < d_in - n0 ? K : d_in - n0;
+    const int64_t ks = d_in / 16, ea = split_frag_index(0, k0, ks), ub = split_frag_index(n0, k0, ks);
+    const FragPair pu{a.Efh + ea, a.Efl + ea, ks, a.Ufh + ub, a.Ufl + ub, ks, K};
+    FragPair pp{};
+    if (drift) pp = FragPair{a.Xfh + ea, a.Xfl + ea, ks, a.Pfh + ub, a.Pfl + ub, ks, K};
+    KQ_TRY(gemm_frag_add(d_out, N, pu, pp, W + n0, ldw, s, "obs_trailing_update"));
   }
   return KRONQ_OK;
 }

@@ -146,3 +146,26 @@ def test_sweep_exact_ties():
     got = _solve(W, np.eye(128, dtype=np.float32), bits, 128)
     ref = O.obs_blocked(W, np.eye(128), bits, 128, 128)
     assert np.array_equal(got["codes"], ref["codes"])
+
+
+# trailing products: 64-, 128- and 256-edge tiles, halving over a number of lazy groups that is
+# no power of two, one product per lazy group for a wide group that is none either; the oracle
+# takes a sample of the rows (they are independent)
+@pytest.mark.parametrize("d_out,d_in,group,drift", [
+    (300, 1920, 640, False), (290, 2944, 128, True), (5001, 2688, 128, False),
+    (24901, 1152, 128, False), (24901, 1152, 1152, True), (3000, 2048, 1024, False)])
+def test_sweep_trailing_products(d_out, d_in, group, drift):
+    rng = np.random.default_rng(d_out + d_in)
+    X = rng.standard_normal((4 * d_in, d_in))
+    U = O.inverse_cholesky_factor(O.damp(X.T @ X)).astype(np.float32)
+    P = None
+    if drift:
+        P = (np.triu(rng.standard_normal((d_in, d_in)), 1) * 0.01).astype(np.float32)
+    W = (rng.standard_normal((d_out, d_in), dtype=np.float32) * np.float32(0.02))
+    note(f"sweep {d_out}x{d_in} group={group} drift={drift}")
+    got = _solve(W, U, 4, group, P, err=True)
+    rows = np.unique(np.concatenate([[0, d_out - 1], rng.choice(d_out, 200)]))
+    ref = O.obs_blocked(W[rows], U, 4, group, 128, P=P)
+    same = np.all(got["codes"][rows] == ref["codes"], axis=1)
+    assert np.mean(got["codes"][rows] == ref["codes"]) > 0.999 and np.mean(same) > 0.9
+    assert rel_frob(got["err"][rows][same], ref["err"][same]) < 1e-3
