@@ -2,7 +2,8 @@
 //
 // inv(H~) = U^T U with U upper. With J the index reversal, J H~ J = L L^T (ordinary lower
 // Cholesky) gives H~ = (J L J)(J L J)^T, so U = (J L J)^-1 = J L^-1 J. Steps:
-//   1. damping: H~ = H + damp * mean(diag H) * I (in place), M = J H~ J (workspace copy);
+//   1. damping: H~ = H + damp * mean(diag H) * I (in place); M = C J H~ J C (workspace copy), C
+//      the powers of two that bring the diagonal into [1, 4);
 //   2. L and X = L^-1 together, recursively on [[M11, .], [M21, M22]] split at a multiple of 128:
 //        factor and invert M11 (X11 = L11^-1);
 //        L21 = M21 X11^T                  (written to the X21 slot, which is still free);
@@ -11,12 +12,16 @@
 //        factor and invert M22 (X22);
 //        X21 = -X22 T                     (over L21).
 //      Leaves of at most 128 columns are factored and inverted in LDS by one workgroup; every
-//      other step is a fp32 MFMA GEMM, so the large updates have a long K. Three dependent
-//      launches per split: the chain of small ones, not the flops, sets the time at d = 4096;
-//   3. U[i][j] = X[d-1-i][d-1-j] for i <= j, 0 below the diagonal.
+//      other step is a product with a long K: on the fp32 matrix cores, and from order FRAG_MIN
+//      on fp16 planes, three products a term (gemm_frag.hip; fp32 values have 24 significant
+//      bits, the planes 23, and the accumulation in fp32 decides the error of both). Three
+//      dependent launches per split (five with planes): the chain of small ones, not the flops,
+//      sets the time at d = 4096;
+//   3. U[i][j] = c_j X[d-1-i][d-1-j] for i <= j, 0 below the diagonal.
 // A non-positive pivot sets *info to its 1-based column in the original order (first failure).
 #include <algorithm>
 #include <cmath>
+#include <utility>
 
 #include "kq_common.hpp"
 
@@ -26,16 +31,28 @@ namespace {
 constexpr int NB = 128;
 constexpr int DLD = NB + 1;  // LDS leading dimension of the diagonal block
 
-__global__ __launch_bounds__(256) void diag_shift(const float* __restrict__ H, int64_t d,
-                                                  int64_t ldh, float damp, float* __restrict__ shift,
-                                                  int* __restrict__ info) {
-  __shared__ double red[256];
+__global__ __launch_bounds__(1024) void diag_shift(const float* __restrict__ H, int64_t d,
+                                                   int64_t ldh, float damp,
+                                                   float* __restrict__ shift,
+                                                   int* __restrict__ info) {
+  __shared__ double red[1024];
   const int tid = threadIdx.x;
   double s = 0.0;
-  for (int64_t i = tid; i < d; i += 256) s += H[i * ldh + i];
+  // 8 entries a thread in flight at once (each is a cache line of its own)
+  for (int64_t i0 = tid; i0 < d; i0 += 8 * 1024) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int64_t i = i0 + 1024 * k;
+      v[k] = H[(i < d ? i : d - 1) * ldh + (i < d ? i : d - 1)];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (i0 + 1024 * k < d) s += v[k];
+  }
   red[tid] = s;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
+  for (int w = 512; w > 0; w >>= 1) {
     if (tid < w) red[tid] += red[tid + w];
     __syncthreads();
   }
@@ -45,29 +62,41 @@ __global__ __launch_bounds__(256) void diag_shift(const float* __restrict__ H, i
   }
 }
 
+// the damped diagonal, and the power of two c_i = 2^-floor(e / 2), e its exponent, that brings it
+// into [1, 4) (1 for an entry that is not positive and finite)
 __global__ void add_diag(float* __restrict__ H, int64_t d, int64_t ldh,
-                         const float* __restrict__ shift) {
+                         const float* __restrict__ shift, float* __restrict__ cn) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < d) H[i * ldh + i] += *shift;
+  if (i >= d) return;
+  const float v = H[i * ldh + i] + *shift;
+  H[i * ldh + i] = v;
+  cn[i] = v > 0.f && v <= 3.0e38f ? ldexpf(1.f, -(ilogbf(v) >> 1)) : 1.f;
 }
 
-// M[i][j] = H[d-1-i][d-1-j]
+// M[i][j] = c_i' c_j' H[i'][j'], i' = d-1-i, j' = d-1-j: reversed, and normalised to a diagonal in
+// [1, 4) (exact: powers of two). Then |M[i][j]| < 4 and |L[i][j]| < 2, which the 16-bit planes of
+// the large products rely on.
 __global__ void reverse_copy(const float* __restrict__ H, int64_t d, int64_t ldh,
-                             float* __restrict__ M, int64_t ldm) {
+                             const float* __restrict__ cn, float* __restrict__ M, int64_t ldm) {
   const int64_t i = blockIdx.y;
+  const float ci = cn[d - 1 - i];
   for (int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; j < d;
        j += int64_t(gridDim.x) * blockDim.x)
-    M[i * ldm + j] = H[(d - 1 - i) * ldh + (d - 1 - j)];
+    M[i * ldm + j] = H[(d - 1 - i) * ldh + (d - 1 - j)] * ci * cn[d - 1 - j];
 }
 
-// the same with four columns per thread (d divisible by 4; rows 16-byte aligned)
+// the same with four columns per thread (d divisible by 4; rows 16-byte aligned); only the lower
+// triangle, up to the end of its diagonal blocks, is read afterwards
 __global__ void reverse_copy4(const float* __restrict__ H, int64_t d, int64_t ldh,
-                              float* __restrict__ M, int64_t ldm) {
-  const int64_t i = blockIdx.y;
-  for (int64_t j = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) * 4; j < d;
+                              const float* __restrict__ cn, float* __restrict__ M, int64_t ldm) {
+  const int64_t i = blockIdx.y, jend = d < (i | 127) + 1 ? d : (i | 127) + 1;
+  const float ci = cn[d - 1 - i];
+  for (int64_t j = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) * 4; j < jend;
        j += int64_t(gridDim.x) * blockDim.x * 4) {
     const float4 h = *reinterpret_cast<const float4*>(H + (d - 1 - i) * ldh + (d - 4 - j));
-    *reinterpret_cast<float4*>(M + i * ldm + j) = make_float4(h.w, h.z, h.y, h.x);
+    const float4 c = *reinterpret_cast<const float4*>(cn + (d - 4 - j));
+    *reinterpret_cast<float4*>(M + i * ldm + j) =
+        make_float4(h.w * ci * c.w, h.z * ci * c.z, h.y * ci * c.y, h.x * ci * c.x);
   }
 }
 
@@ -94,58 +123,104 @@ __device__ __forceinline__ void mfma_block(float* C, int ldc, const float* A, in
   }
 }
 
-// One 32-column panel of the diagonal-block factorisation (see potrf_diag), by one wave.
-template <int c0>
-__device__ __forceinline__ void panel_factor(float* a, float* colbuf, float* dummy, int64_t kb,
+// v of lane K of each 16-lane row, in the whole row (folds into the FMA that uses it)
+template <int K>
+__device__ __forceinline__ float bcast16(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xF, 0xF, true));
+}
+
+// The panel's state in one wave: v and u are rows 0 .. 15 and 16 .. 31 of the diagonal block, row
+// lane % 16 in every 16-lane row (so that a column's entries can be broadcast within each by DPP),
+// x a row of the panel below or a column of the identity of this lane's own.
+struct PanelRows {
+  float v[16], u[32], x[32], own;  // own: the pivot of column `lane` (lanes 0 .. 31)
+};
+
+// w += ng raw(lane K of the 16-lane row), one instruction with the broadcast as its DPP operand
+// (left to itself the compiler keeps the broadcasts as moves of their own, half as many
+// instructions again). A DPP read of raw needs two wait states after its write: ng depends on raw
+// through four instructions.
+template <int K>
+__device__ __forceinline__ void fmac_bcast(float& w, float raw, float ng) {
+  asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+               : "+v"(w)
+               : "v"(raw), "v"(ng), "i"(K));
+}
+
+// w[k] += ng raw_k for the columns k = J + 1 + K of the panel, raw column J of the block's rows
+template <int J, int N, int... K>
+__device__ __forceinline__ void eliminate(std::integer_sequence<int, K...>, float (&w)[N],
+                                          float ng, const PanelRows& r) {
+  (fmac_bcast<(J + 1 + K) & 15>(w[J + 1 + K], J + 1 + K < 16 ? r.v[J & 15] : r.u[J], ng), ...);
+}
+
+// Column J of the panel: entry k > J of every row loses (w_J / L_JJ) L_kJ = w_J rl rl raw_k, with
+// raw the column before scaling and rl = 1 / L_JJ. On the rows that is the rank-1 update, on the
+// identity's columns the forward substitution, so that x ends as a row of L or a column of the
+// inverse.
+template <int J>
+__device__ __forceinline__ void panel_column(PanelRows& r, int lane) {
+  constexpr bool LO = J < 16;
+  float& at = LO ? r.v[J & 15] : r.u[J];
+  asm volatile("s_nop 1" : "+v"(at));  // (its last write is an asm the compiler does not look into)
+  const float piv = bcast16<J & 15>(at);
+  if (lane == J) r.own = piv;
+  const float rl = __builtin_amdgcn_rsqf(piv);  // pivots are normal or the factor fails
+  const float lu = r.u[J] * rl, lx = r.x[J] * rl, nu = -lu * rl, nx = -lx * rl;
+  if constexpr (LO) {
+    const float lv = r.v[J & 15] * rl, nv = -lv * rl;
+    eliminate<J>(std::make_integer_sequence<int, 15 - (J & 15)>{}, r.v, nv, r);
+    eliminate<J>(std::make_integer_sequence<int, 31 - J>{}, r.x, nx, r);
+    eliminate<J>(std::make_integer_sequence<int, 31 - J>{}, r.u, nu, r);
+    r.v[J & 15] = lv;
+  } else {
+    // the next column's rows first: its pivot waits for them
+    eliminate<J>(std::make_integer_sequence<int, 31 - J>{}, r.u, nu, r);
+    eliminate<J>(std::make_integer_sequence<int, 31 - J>{}, r.x, nx, r);
+  }
+  r.u[J] = lu;
+  r.x[J] = lx;
+}
+template <int... J>
+__device__ __forceinline__ void panel_columns(std::integer_sequence<int, J...>, PanelRows& r,
+                                              int lane) {
+  (panel_column<J>(r, lane), ...);
+}
+
+// Panel p (32 columns) by one of two waves, both of which eliminate the diagonal block: part 0
+// takes the inverse Y_pp and the rows of block p + 1, part 1 those of blocks p + 2 and p + 3.
+__device__ __forceinline__ void factor_panel(float* a, float* y, int p, int part, int64_t kb,
                                              int64_t d, int* info, int lane) {
-  {
-    const int r0 = c0 + lane, r1 = c0 + 64 + lane;
-    const bool ok0 = r0 < NB, ok1 = r1 < NB;  // r1 < NB only for c0 < 64
-    float v0[32], v1[32];
-    int first_bad = 32;  // first column of the panel with a non-positive pivot
-    // lanes past the last row work on a copy of row NB - 1 (never stored): no divergent loads
-    const int q0 = ok0 ? r0 : NB - 1, q1 = ok1 ? r1 : NB - 1;
+  const int c0 = 32 * p, l16 = lane & 15, l32 = lane & 31, hi = lane >> 5;
+  const int bx = p + (part ? 2 + hi : 1);         // this lane's block (part 0: the upper half)
+  const bool rows = part ? bx < 4 : hi && bx < 4;  // x is a row below
+  float* xr = a + (32 * (bx < 4 ? bx : 3) + l32) * DLD + c0;
+  PanelRows r;
 #pragma unroll
-    for (int k = 0; k < 32; ++k) {
-      v0[k] = a[q0 * DLD + c0 + k];
-      v1[k] = c0 < 64 ? a[q1 * DLD + c0 + k] : 0.f;
+  for (int k = 0; k < 32; ++k) {
+    if (k < 16) r.v[k & 15] = a[(c0 + l16) * DLD + c0 + k];
+    r.u[k] = a[(c0 + 16 + l16) * DLD + c0 + k];
+    const float x = xr[k];
+    r.x[k] = rows ? x : (l32 == k ? 1.f : 0.f);
+  }
+  r.own = 1.f;
+  panel_columns(std::make_integer_sequence<int, 32>{}, r, lane);
+  if (rows) {
+#pragma unroll
+    for (int k = 0; k < 32; ++k) xr[k] = r.x[k];
+  }
+  if (part == 0) {
+    if (!hi) {
+#pragma unroll
+      for (int k = 0; k < 32; ++k) y[(c0 + k) * DLD + c0 + l32] = r.x[k];
     }
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      colbuf[lane] = v0[j];  // every lane stores (no branch); entries 0..31 are read
-      float raw[32];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const float4 t = reinterpret_cast<const float4*>(colbuf)[q];
-        raw[4 * q] = t.x, raw[4 * q + 1] = t.y, raw[4 * q + 2] = t.z, raw[4 * q + 3] = t.w;
-      }
-      const float piv = raw[j];
-      if (!(piv > 0.f) && first_bad == 32) first_bad = j;  // also catches NaN; a select
-      const float rl = __builtin_amdgcn_rsqf(piv);  // pivots are normal or the factor fails
-      const float ljj = piv * rl;
-      const float l0 = v0[j] * rl, l1 = v1[j] * rl;
-      // A[i][k] -= L[i][j] L[k][j] = (l_i rl) raw_k
-      const float g0 = l0 * rl, g1 = l1 * rl;
-#pragma unroll
-      for (int k = j + 1; k < 32; ++k) {
-        v0[k] = fmaf(-g0, raw[k], v0[k]);
-        if (c0 < 64) v1[k] = fmaf(-g1, raw[k], v1[k]);
-      }
-      v0[j] = lane > j ? l0 : (lane == j ? ljj : 0.f);
-      v1[j] = l1;
+    // the first non-positive (or NaN) pivot of the panel
+    const uint32_t bad = uint32_t(__ballot(!(r.own > 0.f)));
+    if (lane == 0 && bad != 0u) {
+      const int f = __builtin_ctz(bad);
+      if (kb + c0 + f < d) atomicCAS(info, 0, int(d - (kb + c0 + f)));
     }
-    // unconditional stores (a divergent branch here would make the compiler sink the row
-    // updates into it): rows past the end go to a dummy area of the idle product scratch
-    const int dummy_off = int(dummy - a) + lane * 33;  // same LDS array: an index select
-    float* d0 = a + (ok0 ? r0 * DLD + c0 : dummy_off);
-    float* d1 = a + (ok1 ? r1 * DLD + c0 : dummy_off);
-#pragma unroll
-    for (int k = 0; k < 32; ++k) {
-      d0[k] = v0[k];
-      if (c0 < 64) d1[k] = v1[k];
-    }
-    if (lane == 0 && first_bad < 32 && kb + c0 + first_bad < d)
-      atomicCAS(info, 0, int(d - (kb + c0 + first_bad)));
   }
 }
 
@@ -155,48 +230,28 @@ __device__ __forceinline__ void upd_block(float* a, int bi, int bj, int p, int l
              a + 32 * bj * DLD + 32 * p, DLD, true, 32, -1.f, 1.f, lane);
 }
 
-// Y_pp = L_pp^-1 for the 32 x 32 diagonal block p, one wave: lane c solves column c by forward
-// substitution (a multiplication by the reciprocal of L_ii, not a division)
-__device__ __forceinline__ void inv_block(const float* a, float* y, int p,
-                                          int lane) {
-  const int b0 = 32 * p;
-  if (lane < 32) {
-    float x[32];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      float s = (i == lane) ? 1.f : 0.f;
-#pragma unroll
-      for (int k = 0; k < i; ++k) s = fmaf(-a[(b0 + i) * DLD + b0 + k], x[k], s);
-      x[i] = s * __builtin_amdgcn_rcpf(a[(b0 + i) * DLD + b0 + i]);
-      __builtin_amdgcn_sched_barrier(0);  // read one row of L at a time
-    }
-#pragma unroll
-    for (int i = 0; i < 32; ++i) y[(b0 + i) * DLD + b0 + lane] = x[i];
-  }
-}
-
 // Factor the diagonal block M[kb:kb+bs, kb:kb+bs] (lower) and invert the factor, one workgroup.
 // The block is padded to 128 x 128 with the identity, so a partial block needs no special case.
-// Factorisation, in four 32-column panels:
-//   * panel: wave 0 factors the panel for every row at or below it; lane l keeps rows c0 + l
-//     and c0 + 64 + l (32 panel entries each) in registers. Column j of the panel's diagonal
-//     rows is published once through a 64-float LDS buffer and read back as broadcasts, and the
-//     1 / L_jj scaling is folded into the per-row coefficient, so each column costs one LDS
-//     round trip and one FMA per remaining entry;
-//   * rank-32 updates of the lower 32 x 32 blocks right of the panel (MFMA), the next panel's
-//     block column first; the rest, and the inverse of the panel's diagonal block, run on the
-//     other waves while wave 0 factors the next panel.
-// Inverse Y = L^-1 by recursive doubling, inv([[A, 0], [B, C]]) = [[A^-1, 0], [-C^-1 B A^-1, C^-1]]:
-//   32 x 32 diagonal blocks (one wave each, columns by forward substitution), then 64, then 128.
+// Four panels of 32 columns: two waves eliminate a panel in registers (factor_panel: all of its
+// rows, and the inverse of its diagonal block), then the four waves update the next panel's block
+// column on the fp32 matrix cores; while the next panel runs, the two other waves update the rest
+// and build the inverse Y = L^-1 by inv([[A, 0], [B, C]]) = [[A^-1, 0], [-C^-1 B A^-1, C^-1]],
+// first of the 64-column halves, then of the whole, as far as their parts exist.
 // Writes Linv_kk, with exact zeros above the diagonal, to X (M itself is left as read).
+// Bound: the chain of 128 columns, a reciprocal square root and the FMAs of one wave each, and a
+// quarter of the time the block's way in and out of LDS: 53k cycles, 24 us. A single wave issues
+// about one vector instruction in 6 cycles here, so the instruction count sets a panel's 8.3k
+// cycles; running the next pivot's root beside a column's FMAs gained nothing. (Panels through an
+// LDS buffer, one round
+// trip a column: 30.5 us a block; the diagonal block alone with v_readlane broadcasts, 10k cycles
+// a panel, and the rest by products with its inverse: 29 us.)
 __global__ __launch_bounds__(256) void potrf_diag(const float* __restrict__ M, int64_t ldm,
                                                   int64_t kb, int bs, int64_t d,
                                                   float* __restrict__ X, int* __restrict__ info) {
   __shared__ __attribute__((aligned(16))) float lds[2 * NB * DLD + 64 * 68];
   float* const a = lds;                 // the block, becomes L (lower part meaningful)
   float* const y = lds + NB * DLD;      // Y = L^-1
-  float* const tb = lds + 2 * NB * DLD; // product scratch (a dummy store target in the panels)
-  __shared__ __attribute__((aligned(16))) float colbuf[64];
+  float* const tb = lds + 2 * NB * DLD; // product scratch
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: per-wave branches
   const bool full = bs == NB;
@@ -225,63 +280,57 @@ __global__ __launch_bounds__(256) void potrf_diag(const float* __restrict__ M, i
     y[(o + i) * DLD + o + 32 + j] = 0.f;
   }
   __syncthreads();
-  // Panels with a one-block lookahead: before panel p + 1 its block column gets panel p's
-  // update from all waves; then wave 0 factors panel p + 1 while the other waves apply panel
-  // p's update to the blocks further right and invert the diagonal block of panel p.
-  if (wave == 0) panel_factor<0>(a, colbuf, tb, kb, d, info, lane);
-  __syncthreads();
-  if (wave < 3) upd_block(a, 1 + wave, 1, 0, lane);  // block column 1 from panel 0
-  __syncthreads();
-  if (wave == 0) {
-    panel_factor<32>(a, colbuf, tb, kb, d, info, lane);
-  } else if (wave == 1) {
-    inv_block(a, y, 0, lane);
-  } else if (wave == 2) {
-    upd_block(a, 2, 2, 0, lane);
-    upd_block(a, 3, 3, 0, lane);
-  } else {
-    upd_block(a, 3, 2, 0, lane);
-  }
-  __syncthreads();
-  if (wave < 2) upd_block(a, 2 + wave, 2, 1, lane);  // block column 2 from panel 1
-  __syncthreads();
-  if (wave == 0) {
-    panel_factor<64>(a, colbuf, tb, kb, d, info, lane);
-  } else if (wave == 1) {
-    inv_block(a, y, 1, lane);
-  } else if (wave == 2) {
-    upd_block(a, 3, 3, 1, lane);
-  }
-  __syncthreads();
-  if (wave == 0) upd_block(a, 3, 3, 2, lane);  // block column 3 from panel 2
-  __syncthreads();
-  if (wave == 0) {
-    panel_factor<96>(a, colbuf, tb, kb, d, info, lane);
-  } else if (wave == 1) {
-    inv_block(a, y, 2, lane);
-  }
-  __syncthreads();
-  if (wave == 0) inv_block(a, y, 3, lane);
-  __syncthreads();
-  // 64: Y10 = -Y11 (L10 Y00) for the block pairs at 0 and 64, one wave each
-  if (wave < 2) {
-    const int o = wave * 64;
-    float* T = tb + wave * 32 * 33;
-    mfma_block(T, 33, a + (o + 32) * DLD + o, DLD, y + o * DLD + o, DLD, false, 32, 1.f, 0.f,
-               lane);
-    mfma_block(y + (o + 32) * DLD + o, DLD, y + (o + 32) * DLD + o + 32, DLD, T, 33, false, 32,
-               -1.f, 0.f, lane);
-  }
-  __syncthreads();
-  // 128: Y[64:, :64] = -Y[64:, 64:] (L[64:, :64] Y[:64, :64]), one 32-block per wave
-  {
-    const int bi = wave >> 1, bj = wave & 1;
-    mfma_block(tb + 32 * bi * 68 + 32 * bj, 68, a + (64 + 32 * bi) * DLD, DLD, y + 32 * bj, DLD,
+  float* const t2 = tb;  // L10 Y00, then L[64:, :64] Y[:64, :64]
+  auto half_product = [&](int bi, int bj) {
+    mfma_block(t2 + 32 * bi * 68 + 32 * bj, 68, a + (64 + 32 * bi) * DLD, DLD, y + 32 * bj, DLD,
                false, 64, 1.f, 0.f, lane);
+  };
+  float* const t32 = a;  // L32 Y22 over the finished L00
+#pragma unroll 1
+  for (int p = 0; p < 4; ++p) {
+    if (wave == 0 || (wave == 1 && p < 2)) {
+      factor_panel(a, y, p, wave, kb, d, info, lane);
+    } else if (p == 1) {
+      if (wave == 2) {
+        upd_block(a, 3, 2, 0, lane);
+        upd_block(a, 3, 3, 0, lane);
+      } else {
+        mfma_block(t2, 33, a + 32 * DLD, DLD, y, DLD, false, 32, 1.f, 0.f, lane);  // L10 Y00
+      }
+    } else if (p == 2) {
+      half_product(wave == 3, wave == 2);
+      if (wave == 3) half_product(1, 1);
+    } else if (p == 3) {
+      if (wave == 1) {
+        mfma_block(t32, DLD, a + 96 * DLD + 64, DLD, y + 64 * DLD + 64, DLD, false, 32, 1.f, 0.f,
+                   lane);
+      } else {  // rows 64 .. 95 of Y's lower left quarter need only Y22
+        const int bj = wave - 2;
+        mfma_block(y + 64 * DLD + 32 * bj, DLD, y + 64 * DLD + 64, DLD, t2 + 32 * bj, 68, false,
+                   32, -1.f, 0.f, lane);
+      }
+    }
     __syncthreads();
-    mfma_block(y + (64 + 32 * bi) * DLD + 32 * bj, DLD, y + (64 + 32 * bi) * DLD + 64, DLD,
-               tb + 32 * bj, 68, false, 64, -1.f, 0.f, lane);
+    // the next panel's block column from panel p, and what else can be
+    if (p == 0) {
+      upd_block(a, wave < 3 ? 1 + wave : 2, wave < 3 ? 1 : 2, 0, lane);
+    } else if (p == 1) {
+      if (wave < 3)
+        upd_block(a, wave == 0 ? 2 : 3, wave < 2 ? 2 : 3, 1, lane);
+      else  // Y10 = -Y11 (L10 Y00)
+        mfma_block(y + 32 * DLD, DLD, y + 32 * DLD + 32, DLD, t2, 33, false, 32, -1.f, 0.f, lane);
+    } else if (wave == 0) {
+      if (p == 2)
+        upd_block(a, 3, 3, 2, lane);
+      else  // Y32 = -Y33 (L32 Y22)
+        mfma_block(y + 96 * DLD + 64, DLD, y + 96 * DLD + 96, DLD, t32, DLD, false, 32, -1.f, 0.f,
+                   lane);
+    }
+    __syncthreads();
   }
+  if (wave < 2)  // rows 96 .. 127: -[Y32 Y33] T2
+    mfma_block(y + 96 * DLD + 32 * wave, DLD, y + 96 * DLD + 64, DLD, t2 + 32 * wave, 68, false,
+               64, -1.f, 0.f, lane);
   __syncthreads();
   if (full) {
 #pragma unroll 4
@@ -300,25 +349,29 @@ __global__ __launch_bounds__(256) void potrf_diag(const float* __restrict__ M, i
   }
 }
 
-// U[i][j] = X[d-1-i][d-1-j] for i <= j, else 0
+// U[i][j] = c_j X[d-1-i][d-1-j] for i <= j, else 0 (X the inverse factor of the normalised M)
 __global__ void reverse_out(const float* __restrict__ X, int64_t ldm, int64_t d,
-                            float* __restrict__ U, int64_t ldu) {
+                            const float* __restrict__ cn, float* __restrict__ U, int64_t ldu) {
   const int64_t i = blockIdx.y;
   for (int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; j < d;
        j += int64_t(gridDim.x) * blockDim.x)
-    U[i * ldu + j] = (j >= i) ? X[(d - 1 - i) * ldm + (d - 1 - j)] : 0.f;
+    U[i * ldu + j] = (j >= i) ? X[(d - 1 - i) * ldm + (d - 1 - j)] * cn[j] : 0.f;
 }
 
 // the same with four columns per thread (d divisible by 4; rows 16-byte aligned)
 __global__ void reverse_out4(const float* __restrict__ X, int64_t ldm, int64_t d,
-                             float* __restrict__ U, int64_t ldu) {
+                             const float* __restrict__ cn, float* __restrict__ U, int64_t ldu) {
   const int64_t i = blockIdx.y;
   for (int64_t j = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) * 4; j < d;
        j += int64_t(gridDim.x) * blockDim.x * 4) {
-    const float4 x = *reinterpret_cast<const float4*>(X + (d - 1 - i) * ldm + (d - 4 - j));
-    *reinterpret_cast<float4*>(U + i * ldu + j) =
-        make_float4(j >= i ? x.w : 0.f, j + 1 >= i ? x.z : 0.f, j + 2 >= i ? x.y : 0.f,
-                    j + 3 >= i ? x.x : 0.f);
+    float4 u = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (j + 3 >= i) {
+      const float4 x = *reinterpret_cast<const float4*>(X + (d - 1 - i) * ldm + (d - 4 - j));
+      const float4 c = *reinterpret_cast<const float4*>(cn + j);
+      u = make_float4(j >= i ? x.w * c.x : 0.f, j + 1 >= i ? x.z * c.y : 0.f,
+                      j + 2 >= i ? x.y * c.z : 0.f, x.x * c.w);
+    }
+    *reinterpret_cast<float4*>(U + i * ldu + j) = u;
   }
 }
 
@@ -327,69 +380,142 @@ int64_t ld_for(int64_t d) { return ((d + 63) / 64) * 64; }
 // split of an n-column block: the first h columns, a multiple of NB, about half
 int64_t split_at(int64_t n) { return (cdiv(n, NB) / 2) * NB; }
 
-// Scratch floats the recursion below needs for an n-column block: a node keeps its product
-// T (r x h) until its last step, while the second child's recursion runs after it.
+int64_t pad(int64_t n, int64_t m) { return cdiv(n, m) * m; }
+
+// A node of n columns whose parts have at least this order runs its products on 16-bit planes: at
+// 768 a 4096 factor takes 2.06 ms, 14336 13.00 and 3000 1.53 (before the leaves below got faster);
+// at 512 2.11, 13.00 and 1.49, at 1024 2.06, 13.39 and 1.56, at 2048 2.17, 14.25 and 1.68. Below,
+// the five launches cost more than the products. (Products on the fp32 matrix cores and, from
+// order 3000, on six bf16 products a term split inside the kernel: 2.47, 22.4 and 1.71 ms; error
+// of U against float64 5.5e-7 and 8.6e-7 at 4096 and 14336, now 4.0e-7 and 7.3e-7.)
+constexpr int64_t FRAG_MIN = 768;
+bool frag_node(int64_t n) {
+  const int64_t h = split_at(n);
+  return h >= FRAG_MIN && n - h >= FRAG_MIN;
+}
+
+// floats of the two planes of a rows x k operand
+int64_t planes(int64_t rows, int64_t k) { return pad(rows, 32) * pad(k, 16); }
+
+// Scratch floats of an n-column block: a node keeps its product T (r x h; as planes of its
+// transpose at a large node) until its last step, while the second child's recursion runs after
+// it.
 int64_t chol_scratch(int64_t n) {
   if (n <= NB) return 0;
   const int64_t h = split_at(n), r = n - h;
-  return std::max(chol_scratch(h), r * h + chol_scratch(r));
+  const int64_t t = frag_node(n) ? planes(h, r) : r * h;
+  return std::max(chol_scratch(h), t + chol_scratch(r));
+}
+// and the planes a large node needs only while it runs (M21 or X22, X11, its transpose, L21)
+int64_t chol_planes(int64_t n) {
+  if (n <= NB || !frag_node(n)) return 0;
+  const int64_t h = split_at(n), r = n - h;
+  return std::max(planes(r, h), planes(r, r)) + 2 * planes(h, h) + planes(r, h);
 }
 
-// Products of at least this many multiply-adds run on the bf16 matrix cores with the six-term
-// split (gemm_f32_split6, as accurate as fp32): the 3584-order and larger products of the top
-// levels of an 8192 or larger factorisation. Below that (2048-order products and smaller, too
-// few 256 x 128 tiles to fill the chip) the fp32 kernels are faster.
-constexpr double SPLIT6_MIN = 3000.0 * 3000.0 * 3000.0;
+struct Chol {
+  float *M, *X, *planes;
+  int64_t ld, d;
+  int* info;
+  hipStream_t s;
+};
 
-bool use_split6(int flags, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
-                const float* B, int64_t ldb) {
-  return double(M) * double(N) * double(K) >= SPLIT6_MIN &&
-         gemm_split6_supports(flags, M, N, K, A, lda, B, ldb);
+struct Planes {
+  uint16_t *h, *l;
+  int64_t ks;
+};
+Planes take_planes(float*& at, int64_t rows, int64_t k) {
+  const int64_t n = planes(rows, k);
+  Planes p{reinterpret_cast<uint16_t*>(at), reinterpret_cast<uint16_t*>(at) + n, pad(k, 16) / 16};
+  at += n;
+  return p;
 }
 
-// one product of the recursion: the split path when it is large enough, else the fp32 kernels
-int chol_gemm(int flags, int64_t M, int64_t N, int64_t K, float alpha, const float* A,
-              int64_t lda, const float* B, int64_t ldb, float beta, float* C, int64_t ldc,
-              hipStream_t s, const char* name) {
-  if (use_split6(flags, M, N, K, A, lda, B, ldb))
-    return gemm_f32_split6(flags, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s, name);
-  return gemm_f32(flags, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s, name);
+// Powers of two that bring each operand's values into the range of fp16: |M| < 4, |L| < 2; X and
+// T = L21 X11 grow as the inverse square root of the smallest eigenvalue of the normalised H~
+// (2^12 there is the square root of the fp32 rounding unit, beyond which fp32 does not factor
+// either). What falls below the smallest fp16 (2^-24) is 2^-28 of a unit diagonal or less.
+constexpr float SC_M = 4096.f, SC_L = 4096.f, SC_X = 16.f, SC_T = 4.f;
+
+int chol_rec(const Chol& c, float* T, int64_t n0, int64_t n);
+
+// The four products of a large node on fp16 planes (gemm_frag.hip): L21 leaves its product as
+// planes, the operand of the two products after it, and T as planes of its transpose.
+int chol_node_frag(const Chol& c, float* T, int64_t n0, int64_t n) {
+  const int64_t h = split_at(n), r = n - h, ld = c.ld;
+  KQ_TRY(chol_rec(c, T, n0, h));
+  const float* M21 = c.M + (n0 + h) * ld + n0;
+  const float* X11 = c.X + n0 * ld + n0;
+  float* X21 = c.X + (n0 + h) * ld + n0;
+  const float* X22 = c.X + (n0 + h) * ld + n0 + h;
+  float* M22 = c.M + (n0 + h) * ld + n0 + h;
+  float* at = c.planes;
+  const Planes pL = take_planes(at, r, h), pX = take_planes(at, h, h),
+               pXt = take_planes(at, h, h);
+  float* at2 = at;
+  const Planes pM = take_planes(at, r, h), pY = take_planes(at2, r, r);  // (the same place)
+  const Planes pT = take_planes(T, h, r);
+  const SplitJob split[3] = {
+      {M21, ld, r, h, SPLIT_FULL, false, SC_M, nullptr, pM.h, pM.l, pM.ks},
+      {X11, ld, h, h, SPLIT_LOWER, false, SC_X, nullptr, pX.h, pX.l, pX.ks},
+      {X11, ld, h, h, SPLIT_LOWER, true, SC_X, nullptr, pXt.h, pXt.l, pXt.ks}};
+  KQ_TRY(split_planes_launch(split, 3, c.s, "chol_split"));
+  // tiles: the K ranges (or, for the lower triangle, the tiles themselves) make the work uneven,
+  // so 256 x 256 tiles only where they come in several rounds of the chip
+  auto tile = [](int64_t tiles256) { return tiles256 >= 2 * int64_t(device_cus()) ? 256 : 128; };
+  const int64_t tr = cdiv(r, 256), th = cdiv(h, 256);
+  FragJob l21{};  // D = X11 M21^T; L21 = D^T
+  l21.Ph = pX.h, l21.Pl = pX.l, l21.pks = pX.ks, l21.Qh = pM.h, l21.Ql = pM.l, l21.qks = pM.ks;
+  l21.M = h, l21.N = r, l21.K = h, l21.flags = FRAG_P_LOWER;
+  l21.alpha = SC_L / (SC_X * SC_M), l21.Oh = pL.h, l21.Ol = pL.l, l21.oks = pL.ks;
+  KQ_TRY(gemm_frag_f16(&l21, 1, tile(tr * th), c.s, "chol_trsm"));
+  FragJob two[2] = {};  // M22 -= L21 L21^T (lower tiles) and T = L21 X11
+  two[0].Ph = two[0].Qh = pL.h, two[0].Pl = two[0].Ql = pL.l, two[0].pks = two[0].qks = pL.ks;
+  two[0].M = two[0].N = r, two[0].K = h, two[0].flags = FRAG_LOWER;
+  two[0].alpha = -1.f / (SC_L * SC_L), two[0].C = M22, two[0].ldc = ld, two[0].add = true;
+  two[1].Ph = pL.h, two[1].Pl = pL.l, two[1].pks = pL.ks;
+  two[1].Qh = pXt.h, two[1].Ql = pXt.l, two[1].qks = pXt.ks;
+  two[1].M = r, two[1].N = h, two[1].K = h, two[1].flags = FRAG_Q_UPPER;
+  two[1].alpha = SC_T / (SC_L * SC_X), two[1].Oh = pT.h, two[1].Ol = pT.l, two[1].oks = pT.ks;
+  KQ_TRY(gemm_frag_f16(two, 2, tile(tr * (tr + 1) / 2 + tr * th), c.s, "chol_syrk_trtri_row"));
+  KQ_TRY(chol_rec(c, T, n0 + h, r));
+  const SplitJob split22{X22, ld, r, r, SPLIT_LOWER, false, SC_X, nullptr, pY.h, pY.l, pY.ks};
+  KQ_TRY(split_planes_launch(&split22, 1, c.s, "chol_split"));
+  FragJob x21{};  // X21 = -X22 T
+  x21.Ph = pY.h, x21.Pl = pY.l, x21.pks = pY.ks, x21.Qh = pT.h, x21.Ql = pT.l, x21.qks = pT.ks;
+  x21.M = r, x21.N = h, x21.K = r, x21.flags = FRAG_P_LOWER;
+  x21.alpha = -1.f / (SC_X * SC_T), x21.C = X21, x21.ldc = ld;
+  return gemm_frag_f16(&x21, 1, tile(tr * th), c.s, "trtri_update");
 }
 
 // L and L^-1 of the block [n0, n0 + n) of M; the lower part of the same block of X receives
-// L^-1 (zeros on the upper part of the diagonal leaves). T is scratch of tcap floats (at least
-// chol_scratch(n)).
-int chol_rec(float* M, float* X, float* T, int64_t tcap, int64_t ld, int64_t n0, int64_t n,
-             int64_t d, int* info, hipStream_t s) {
+// L^-1 (zeros on the upper part of the diagonal leaves). T: scratch of chol_scratch(n) floats.
+int chol_rec(const Chol& c, float* T, int64_t n0, int64_t n) {
+  float *M = c.M, *X = c.X;
+  const int64_t ld = c.ld;
+  hipStream_t s = c.s;
   if (n <= NB)
     return launch("chol_potrf_diag", potrf_diag, dim3(1), dim3(256), 0, s,
-                  static_cast<const float*>(M), ld, n0, int(n), d, X, info);
+                  static_cast<const float*>(M), ld, n0, int(n), c.d, X, c.info);
+  if (frag_node(n)) return chol_node_frag(c, T, n0, n);
   const int64_t h = split_at(n), r = n - h;
-  KQ_REQUIRE(r * h <= tcap, KRONQ_ERR_WORKSPACE, "chol_rec: scratch too small");
-  KQ_TRY(chol_rec(M, X, T, tcap, ld, n0, h, d, info, s));
+  KQ_TRY(chol_rec(c, T, n0, h));
   const float* M21 = M + (n0 + h) * ld + n0;
   const float* X11 = X + n0 * ld + n0;
   float* X21 = X + (n0 + h) * ld + n0;
   float* X22 = X + (n0 + h) * ld + n0 + h;
   float* M22 = M + (n0 + h) * ld + n0 + h;
   // L21 = M21 X11^T (op(B) = X11^T is upper triangular)
-  KQ_TRY(chol_gemm(GEMM_TB | GEMM_OPB_UPPER, r, h, h, 1.f, M21, ld, X11, ld, 0.f, X21, ld, s,
-                   "chol_trsm"));
+  KQ_TRY(gemm_f32(GEMM_TB | GEMM_OPB_UPPER, r, h, h, 1.f, M21, ld, X11, ld, 0.f, X21, ld, s,
+                  "chol_trsm"));
   // M22 -= L21 L21^T (lower tiles only) and T = L21 X11 (X11 lower triangular), in one launch
   // (both need only L21 and X11)
   const GemmProb syrk{GEMM_TB | GEMM_LOWER_C, r, r, h, -1.f, X21, ld, X21, ld, 1.f, M22, ld};
   const GemmProb row{GEMM_B_LOWER, r, h, h, 1.f, X21, ld, X11, ld, 0.f, T, h};
-  if (use_split6(syrk.flags, r, r, h, X21, ld, X21, ld) &&
-      use_split6(row.flags, r, h, h, X21, ld, X11, ld)) {
-    // the syrk's tiles (all of full K) first, the row product's (K ranges of every length)
-    // after them, filling the last round of workgroups
-    KQ_TRY(gemm_f32_split6_dual(syrk, row, s, "chol_syrk_trtri_row"));
-  } else {
-    KQ_TRY(gemm_f32_dual(syrk, row, s, "chol_syrk_trtri_row"));
-  }
-  KQ_TRY(chol_rec(M, X, T + r * h, tcap - r * h, ld, n0 + h, r, d, info, s));
+  KQ_TRY(gemm_f32_dual(syrk, row, s, "chol_syrk_trtri_row"));
+  KQ_TRY(chol_rec(c, T + r * h, n0 + h, r));
   // X21 = -X22 T
-  return chol_gemm(GEMM_A_LOWER, r, h, r, -1.f, X22, ld, T, h, 0.f, X21, ld, s, "trtri_update");
+  return gemm_f32(GEMM_A_LOWER, r, h, r, -1.f, X22, ld, T, h, 0.f, X21, ld, s, "trtri_update");
 }
 
 }  // namespace
@@ -398,7 +524,9 @@ size_t chol_ws_bytes(int64_t d) {
   if (d <= 0) return 0;
   const int64_t ld = ld_for(d);
   return 2 * align256(size_t(d) * ld * sizeof(float)) +
-         align256(size_t(std::max<int64_t>(1, chol_scratch(d))) * sizeof(float)) + 256;
+         align256(size_t(std::max<int64_t>(1, chol_scratch(d))) * sizeof(float)) +
+         align256(size_t(chol_planes(d)) * sizeof(float)) +
+         align256(size_t(d) * sizeof(float)) + 512;
 }
 
 int chol_launch(float* H, int64_t d, int64_t ldh, float damp_rel, float* U, int64_t ldu,
@@ -407,29 +535,30 @@ int chol_launch(float* H, int64_t d, int64_t ldh, float damp_rel, float* U, int6
   Carver cv(ws);
   float* M = cv.take<float>(size_t(d) * ld);
   float* X = cv.take<float>(size_t(d) * ld);
-  const int64_t tcap = std::max<int64_t>(1, chol_scratch(d));
-  float* T = cv.take<float>(size_t(tcap));
+  float* T = cv.take<float>(size_t(std::max<int64_t>(1, chol_scratch(d))));
+  float* pl = cv.take<float>(size_t(chol_planes(d)));
+  float* cn = cv.take<float>(size_t(d));
   float* shift = cv.take<float>(1);
 
-  KQ_TRY(launch("chol_diag_shift", diag_shift, dim3(1), dim3(256), 0, s,
+  KQ_TRY(launch("chol_diag_shift", diag_shift, dim3(1), dim3(1024), 0, s,
                 static_cast<const float*>(H), d, ldh, damp_rel, shift, info));
   KQ_TRY(launch("chol_add_diag", add_diag, dim3(unsigned(cdiv(d, 256))), dim3(256), 0, s, H, d,
-                ldh, static_cast<const float*>(shift)));
+                ldh, static_cast<const float*>(shift), cn));
   const unsigned gx = unsigned(cdiv(d, 256) < 64 ? cdiv(d, 256) : 64);
   const bool v4 = d % 4 == 0 && ldh % 4 == 0 && ldu % 4 == 0 && aligned(H, 16) && aligned(U, 16);
   const unsigned gx4 = unsigned(cdiv(d, 1024) < 64 ? cdiv(d, 1024) : 64);
   if (v4)
     KQ_TRY(launch("chol_reverse_copy", reverse_copy4, dim3(gx4, unsigned(d)), dim3(256), 0, s,
-                  static_cast<const float*>(H), d, ldh, M, ld));
+                  static_cast<const float*>(H), d, ldh, static_cast<const float*>(cn), M, ld));
   else
     KQ_TRY(launch("chol_reverse_copy", reverse_copy, dim3(gx, unsigned(d)), dim3(256), 0, s,
-                  static_cast<const float*>(H), d, ldh, M, ld));
-  KQ_TRY(chol_rec(M, X, T, tcap, ld, 0, d, d, info, s));
+                  static_cast<const float*>(H), d, ldh, static_cast<const float*>(cn), M, ld));
+  KQ_TRY(chol_rec(Chol{M, X, pl, ld, d, info, s}, T, 0, d));
   if (v4)
     return launch("chol_reverse_out", reverse_out4, dim3(gx4, unsigned(d)), dim3(256), 0, s,
-                  static_cast<const float*>(X), ld, d, U, ldu);
+                  static_cast<const float*>(X), ld, d, static_cast<const float*>(cn), U, ldu);
   return launch("chol_reverse_out", reverse_out, dim3(gx, unsigned(d)), dim3(256), 0, s,
-                static_cast<const float*>(X), ld, d, U, ldu);
+                static_cast<const float*>(X), ld, d, static_cast<const float*>(cn), U, ldu);
 }
 
 }  // namespace kq

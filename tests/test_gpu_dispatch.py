@@ -169,3 +169,45 @@ def test_sweep_trailing_products(d_out, d_in, group, drift):
     same = np.all(got["codes"][rows] == ref["codes"], axis=1)
     assert np.mean(got["codes"][rows] == ref["codes"]) > 0.999 and np.mean(same) > 0.9
     assert rel_frob(got["err"][rows][same], ref["err"][same]) < 1e-3
+
+
+# ------------------------------------------------------------------ factor: products on planes
+def _factor(H, damp=0.01):
+    d = H.shape[0]
+    Hd = torch.from_numpy(np.ascontiguousarray(H, dtype=np.float32)).to(DEV)
+    U = torch.full((d, d), float("nan"), device=DEV)
+    info = K.kronq_cholesky_inv(Hd, U, damp)
+    torch.cuda.synchronize()
+    return to_np(U), int(info.item())
+
+
+# the smallest large node (two halves of 768), ragged second halves, nested large nodes, orders
+# that are no multiple of 4 (scalar copies), and a diagonal graded over twelve decades, which the
+# normalisation takes out before the fp16 planes
+@pytest.mark.parametrize("d,graded", [(1535, False), (1536, False), (1700, True), (2331, False),
+                                      (3105, True)])
+def test_factor_planes(d, graded):
+    rng = np.random.default_rng(d)
+    X = rng.standard_normal((2 * d, d))
+    C = X.T @ X / (2 * d)
+    s = 10.0 ** rng.uniform(-6, 6, d) if graded else np.ones(d)
+    H = (C * s[:, None] * s[None, :]).astype(np.float32)
+    note(f"factor d={d} graded={graded}")
+    U, info = _factor(H, 0.0 if graded else 0.01)
+    assert info == 0 and np.array_equal(U, np.triu(U))
+    H64 = H.astype(np.float64) / s[:, None] / s[None, :]
+    ref = O.inverse_cholesky_factor(H64 if graded else O.damp(H64))
+    # fp32 rounding of d-term sums, amplified by the condition number of the normalised matrix
+    cond = np.linalg.cond(H64 if graded else O.damp(H64))
+    assert rel_frob(U * s[None, :], ref) < 4 * 2.0 ** -24 * np.sqrt(d) * cond
+
+
+@pytest.mark.parametrize("d,bad", [(1536, 3), (1536, 1500), (2304, 900)])
+def test_factor_planes_not_positive(d, bad):
+    rng = np.random.default_rng(bad)
+    X = rng.standard_normal((2 * d, d))
+    H = X.T @ X / (2 * d)
+    H[bad, bad] = -1.0
+    note(f"factor d={d} bad={bad}")
+    # the factorisation runs from the last column to the first: the first failure it meets
+    assert _factor(H, 0.0)[1] == bad + 1
