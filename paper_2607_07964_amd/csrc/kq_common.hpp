@@ -220,12 +220,13 @@ int gemm_frag_bf16(const FragJob& j, int tile, hipStream_t s, const char* name);
 int gemm_frag_f16(const FragJob* jobs, int n, int tile, hipStream_t s, const char* name);
 
 // fp16 planes of the fp32 matrix src [rows x cols] (16-byte aligned rows), or of its transpose,
-// times scale or divided by unit[row] (unit[column] of src when trans); powers of two
+// times scale, or divided by unit[row of the planes]; powers of two
 enum SplitTri : int { SPLIT_FULL = 0, SPLIT_LOWER, SPLIT_UPPER, SPLIT_STRICT_UPPER };
 struct SplitJob {
   const float* src;
   int64_t ld, rows, cols;
-  int tri;     // the part of src that is read; zeros elsewhere
+  int tri;     // the part of src that is read; zeros elsewhere (256 x 256 blocks of zeros are left
+               // out: a product of a triangular operand takes its FRAG_* flag)
   bool trans;
   float scale;
   const float* unit;

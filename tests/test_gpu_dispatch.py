@@ -211,3 +211,35 @@ def test_factor_planes_not_positive(d, bad):
     note(f"factor d={d} bad={bad}")
     # the factorisation runs from the last column to the first: the first failure it meets
     assert _factor(H, 0.0)[1] == bad + 1
+
+
+# ---------------------------------------------------------------- drift correction on fp16 planes
+# orders on both sides of the planes' threshold, ragged tiles, padded rows, rows of D and U over
+# many powers of two
+@pytest.mark.parametrize("d,pad", [(1279, 1), (1280, 0), (1444, 0), (1539, 5)])
+def test_gptaq_planes(d, pad):
+    rng = np.random.default_rng(d)
+    U = (np.triu(rng.standard_normal((d, d))) * 2.0 ** rng.integers(-12, 13, (d, 1))).astype(np.float32)
+    D = (rng.standard_normal((d, d)) * 2.0 ** rng.integers(-12, 13, (d, 1))).astype(np.float32)
+    D[d // 3] = 0.0
+    dev = [torch.full((d, d + pad), float("nan"), device=DEV) for _ in range(3)]
+    Dd, Ud, P = (t[:, :d] for t in dev)
+    Dd.copy_(torch.from_numpy(D))
+    Ud.copy_(torch.from_numpy(U))
+    note(f"gptaq planes d={d} pad={pad}")
+    K.kronq_gptaq_correction(Dd, Ud, P, 0.5)
+    torch.cuda.synchronize()
+    p = to_np(P)
+    assert np.all(np.tril(p) == 0.0)
+    D64, U64 = np.triu(D.astype(np.float64), 1), U.astype(np.float64)
+    T = np.triu(D64 @ U64.T, 1)
+    ref = 0.5 * T @ U64
+    # two d-term fp32 sums of operands of 22 bits (2^-22 each) of the terms' sizes; an operand
+    # below 2^-28 of its row's largest value (D, T, U's rows and columns) is good to 2^-38 of that
+    top = lambda a, axis: np.abs(a).max(axis, keepdims=True)
+    size = np.triu(np.abs(D64) @ np.abs(U64).T, 1)
+    eT = (d + 12) * 2.0 ** -24 * size + d * 2.0 ** -37 * top(D64, 1) * top(U64, 1).T
+    eP = (d + 12) * 2.0 ** -24 * size @ np.abs(U64) + d * 2.0 ** -37 * top(T, 1) * top(U64, 0)
+    assert np.all(np.abs(p - ref) <= 0.5 * np.triu(np.triu(eT, 1) @ np.abs(U64) + eP, 1))
+    if pad:
+        assert torch.isnan(dev[2][:, d:]).all()
