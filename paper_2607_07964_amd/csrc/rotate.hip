@@ -9,7 +9,8 @@
 //                 passes fold in (rescale x random sign);
 //   * row pass:   one workgroup per row, the row staged in LDS; multipliers, radix-8/4/2
 //                 butterflies in registers between LDS round trips, optional 28-point mix,
-//                 1/sqrt(m) and output multipliers, written once;
+//                 1/sqrt(m) and output multipliers, written once; with row_pass8 also the first
+//                 three stages along the row axis;
 //   * column pass: transform along the strided (row) axis for a strip of columns: L rows at a
 //                 fixed row stride are staged in LDS and transformed there. An order-m transform
 //                 is split into passes of length <= 512 (H_m = H_m1 (x) H_m2), plus a 28-point pass.
@@ -27,6 +28,7 @@ constexpr int RP_THREADS = 512;
 constexpr int CP_THREADS = 256;
 constexpr int CP_MAXL = 1024;
 constexpr int NORM_ROWS = 16;
+constexpr int NORM_THREADS = 512;
 
 // ----------------------------------------------------------------------------- norms
 template <typename T>
@@ -63,17 +65,29 @@ __device__ __forceinline__ void load8_f32(const float* p, int64_t n, float (&x)[
   }
 }
 
+__device__ __forceinline__ void load4_f32(const float* p, float* x) {
+  const float4 v = *reinterpret_cast<const float4*>(p);
+  x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w;
+}
+__device__ __forceinline__ void load4_f32(const uint16_t* p, float* x) {
+  const uint2 v = *reinterpret_cast<const uint2*>(p);
+  x[0] = __uint_as_float(v.x << 16), x[1] = __uint_as_float(v.x & 0xFFFF0000u);
+  x[2] = __uint_as_float(v.y << 16), x[3] = __uint_as_float(v.y & 0xFFFF0000u);
+}
+
 // Squared column norms (as per-block partials over NORM_ROWS rows) and squared row norms of W.
 // Each thread loads 8 consecutive columns per row with one vector load and keeps the block's
-// row sums and its 8 column sums in registers; row sums are reduced with wave shuffles.
+// row sums and its 8 column sums in registers; row sums are reduced with wave shuffles. Bound by
+// load latency (one block of rows a workgroup): 512 threads and 16-byte stores of the partials, 49
+// us at 4096 x 14336 bf16 (256 threads, 8-byte stores: 69).
 // Squares of bf16 / fp32 values summed over at most NORM_ROWS rows (columns) or one row's
 // share of a thread (rows) in fp32; the partials are stored and combined in fp64.
 template <typename T>
-__global__ __launch_bounds__(256) void w_norms(const T* __restrict__ W, int64_t d_out,
+__global__ __launch_bounds__(NORM_THREADS) void w_norms(const T* __restrict__ W, int64_t d_out,
                                                int64_t d_in, int64_t ldw,
                                                double* __restrict__ col_part,
                                                double* __restrict__ rowsq) {
-  __shared__ float red[4][NORM_ROWS];
+  __shared__ float red[NORM_THREADS / 64][NORM_ROWS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t r0 = int64_t(blockIdx.x) * NORM_ROWS;
   const int nr = int(min(int64_t(NORM_ROWS), d_out - r0));
@@ -84,7 +98,7 @@ __global__ __launch_bounds__(256) void w_norms(const T* __restrict__ W, int64_t 
   // workgroup) loads without bounds branches, all NORM_ROWS loads of a thread in flight
   // together; the sums are taken in the same order either way
   const bool whole = (d_in & 7) == 0 && nr == NORM_ROWS;
-  for (int64_t c0 = int64_t(tid) * 8; c0 < d_in; c0 += 256 * 8) {
+  for (int64_t c0 = int64_t(tid) * 8; c0 < d_in; c0 += NORM_THREADS * 8) {
     float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (whole) {
       float x[NORM_ROWS][8];
@@ -117,9 +131,15 @@ __global__ __launch_bounds__(256) void w_norms(const T* __restrict__ W, int64_t 
       }
     }
     double* cp = col_part + int64_t(blockIdx.x) * d_in + c0;
+    if (whole) {  // (d_in a multiple of 8: 16-byte aligned)
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (c0 + e < d_in) cp[e] = cs[e];
+      for (int e = 0; e < 8; e += 2)
+        *reinterpret_cast<double2*>(cp + e) = make_double2(cs[e], cs[e + 1]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (c0 + e < d_in) cp[e] = cs[e];
+    }
   }
 #pragma unroll
   for (int r = 0; r < NORM_ROWS; ++r) {
@@ -129,9 +149,12 @@ __global__ __launch_bounds__(256) void w_norms(const T* __restrict__ W, int64_t 
     if (lane == 0) red[wave][r] = v;
   }
   __syncthreads();
-  if (tid < nr)
-    rowsq[r0 + tid] = double(red[0][tid]) + double(red[1][tid]) + double(red[2][tid]) +
-                      double(red[3][tid]);
+  if (tid < nr) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < NORM_THREADS / 64; ++w) t += double(red[w][tid]);
+    rowsq[r0 + tid] = t;
+  }
 }
 
 // s = (h / a)^(1/4), 1 when either is zero (or the side is off). Also the multipliers used by
@@ -187,6 +210,71 @@ __global__ void inv_factors(int64_t n, const float* __restrict__ s, const int8_t
 }
 
 // ----------------------------------------------------------------------------- row pass
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+
+// The 28 x 28 factor (or its transpose) as the operand of v_mfma_f32_32x32x2f32: lane l holds
+// Q[l % 32][2 j + l / 32], rows past 28 zero
+struct Mix28 {
+  float a[14];
+  __device__ __forceinline__ void load(const float* __restrict__ q28, int q_trans, int lane) {
+    const int r = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < 14; ++j) {
+      const int k = 2 * j + h, i = r < 28 ? (q_trans ? k * 28 + r : r * 28 + k) : 0;
+      const float v = q28[i];
+      a[j] = r < 28 ? v : 0.f;
+    }
+  }
+};
+
+// A transformed row from LDS: the 28-point mix, multipliers, store. The mix, output a * m + b =
+// sum_k Q[a][k] buf[k * m + b], takes 32 columns b a wave on the fp32 matrix cores: 3.6k cycles a
+// SIMD and row of 14336 (784 FMAs a thread, the rows of Q through the scalar cache or LDS, took
+// 6.3k and waited for Q)
+__device__ __forceinline__ void row_out(const float* buf, float* __restrict__ o, int64_t n,
+                                        int64_t m, const Mix28& mix, bool mixed,
+                                        const float* __restrict__ post_col, float po, int tid) {
+  if (mixed) {
+    const int lane = tid & 63, mi = int(m);
+#pragma unroll 1
+    for (int b0 = (tid >> 6) * 32; b0 < mi; b0 += RP_THREADS / 2) {
+      int h = lane >> 5;
+      asm volatile("" : "+v"(h));  // (16 addresses a tile are not worth registers across the rows)
+      const int b = b0 + (lane & 31);
+      const float* x = buf + (b < mi ? b : mi - 1) + h * mi;
+      f32x16_t acc{};
+#pragma unroll
+      for (int j = 0; j < 14; ++j)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(mix.a[j], x[2 * j * mi], acc, 0, 0, 0);
+      if (b >= mi) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int a = 8 * (r >> 2) + 4 * h + (r & 3);
+        if (a < 28) {
+          const uint32_t c = uint32_t(a * mi + b);
+          float y = acc[r] * po;
+          if (post_col) y *= post_col[c];
+          o[c] = y;
+        }
+      }
+    }
+  } else if ((n & 3) == 0) {
+    for (int64_t c = int64_t(tid) * 4; c < n; c += int64_t(RP_THREADS) * 4) {
+      float4 y = *reinterpret_cast<const float4*>(buf + c);
+      const float4 pc = post_col ? *reinterpret_cast<const float4*>(post_col + c)
+                                 : make_float4(1.f, 1.f, 1.f, 1.f);
+      y.x *= po * pc.x, y.y *= po * pc.y, y.z *= po * pc.z, y.w *= po * pc.w;
+      *reinterpret_cast<float4*>(o + c) = y;
+    }
+  } else {
+    for (int64_t c = tid; c < n; c += RP_THREADS) {
+      float y = buf[c] * po;
+      if (post_col) y *= post_col[c];
+      o[c] = y;
+    }
+  }
+}
+
 // dst[r][c] = post_row[r] * post_col[c] * T(x)[c] with x[c] = pre_row[r] * pre_col[c] * src[r][c]
 // and T = (Q (x) H_m) / sqrt(m) (Q = 28 x 28 or identity), or the identity when transform == 0.
 template <typename T>
@@ -197,14 +285,10 @@ __global__ __launch_bounds__(RP_THREADS) void row_pass(
     int64_t m, const float* __restrict__ q28, int q_trans, float norm) {
   extern __shared__ float smem[];
   float* buf = smem;       // n floats
-  float* qs = smem + n;    // 28 x 28
   const int tid = threadIdx.x;
-  if (transform && q28) {
-    for (int i = tid; i < 28 * 28; i += RP_THREADS) {
-      const int a = i / 28, b = i % 28;
-      qs[i] = q_trans ? q28[b * 28 + a] : q28[i];
-    }
-  }
+  const bool mixed = transform && q28;
+  Mix28 mix;
+  if (mixed) mix.load(q28, q_trans, tid & 63);
   for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
     const float pr = pre_row ? pre_row[r] : 1.f;
     const float po = (post_row ? post_row[r] : 1.f) * norm;
@@ -220,41 +304,7 @@ __global__ __launch_bounds__(RP_THREADS) void row_pass(
       continue;
     }
     __syncthreads();  // previous row finished with buf
-    if (m >= 512) {
-      // whole 512-element chunks (m is a power of two >= 512, n = L m): a wave takes a chunk,
-      // 8 consecutive elements per lane, straight from global memory; the stages of strides
-      // 1, 2, 4 run in registers and those of strides 8 ... 256 across lanes (lane xor 1 ...
-      // 32), so the chunk reaches LDS with its first 9 stages done; the stages of strides
-      // >= 512 follow in LDS
-      const int wave = tid >> 6, lane = tid & 63;
-      for (int64_t c0 = int64_t(wave) * 512 + lane * 8; c0 < n; c0 += int64_t(RP_THREADS) * 8) {
-        float x[8];
-        load8_f32(s + c0, 8, x);
-        if (pre_col) {
-          const float4 p0 = *reinterpret_cast<const float4*>(pre_col + c0);
-          const float4 p1 = *reinterpret_cast<const float4*>(pre_col + c0 + 4);
-          x[0] *= pr * p0.x, x[1] *= pr * p0.y, x[2] *= pr * p0.z, x[3] *= pr * p0.w;
-          x[4] *= pr * p1.x, x[5] *= pr * p1.y, x[6] *= pr * p1.z, x[7] *= pr * p1.w;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) x[e] *= pr;
-        }
-        hadamard_reg<8>(x);
-#pragma unroll
-        for (int j = 0; j < 6; ++j) {
-          const bool upper = (lane >> j) & 1;  // holds the second element of each pair
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float y = __shfl_xor(x[e], 1 << j);
-            x[e] = upper ? y - x[e] : x[e] + y;
-          }
-        }
-        *reinterpret_cast<float4*>(buf + c0) = make_float4(x[0], x[1], x[2], x[3]);
-        *reinterpret_cast<float4*>(buf + c0 + 4) = make_float4(x[4], x[5], x[6], x[7]);
-      }
-      __syncthreads();
-      fwht_lds(buf, n, m, tid, RP_THREADS, 9);
-    } else if ((n & 7) == 0) {  // 16-byte rows (checked by the API): 8 values per vector load
+    if ((n & 7) == 0) {  // 16-byte rows (checked by the API): 8 values per vector load
       for (int64_t c0 = int64_t(tid) * 8; c0 < n; c0 += int64_t(RP_THREADS) * 8) {
         float x[8];
         load8_f32(s + c0, 8, x);
@@ -270,47 +320,190 @@ __global__ __launch_bounds__(RP_THREADS) void row_pass(
         buf[c] = x;
       }
     }
-    if (m < 512) {
-      __syncthreads();
-      fwht_lds(buf, n, m, tid, RP_THREADS);
+    __syncthreads();
+    fwht_lds(buf, n, m, tid, RP_THREADS);
+    row_out(buf, o, n, m, mix, mixed, post_col, po, tid);
+  }
+}
+// Row pass with m >= 512 (n = L m): whole 512-element chunks. A wave takes a chunk, 8 consecutive
+// elements per lane, straight from global memory; the stages of strides 1, 2, 4 run in registers
+// and those of strides 8 ... 256 across lanes, so the chunk reaches LDS with its first 9 stages
+// done; the stages of strides >= 512 follow in LDS. Workgroups stay on the chip and take rows in
+// turn; the first four chunks a wave holds of the next row are loaded while this one is mixed and
+// stored. Bound by HBM where a row leaves room for four workgroups a CU; at 14336 (two) by each
+// workgroup's own sequence of load, butterflies, mix and store.
+// Measured (loads of a row one after another, lane exchanges and Q through LDS, before):
+// 14336 x 14336 fp32 462 us (624), 4096 x 14336 bf16 108 us (169), 8192 x 8192 fp32 123 us (160).
+template <typename T>
+struct Raw8;
+template <>
+struct Raw8<float> {
+  float4 a, b;
+  __device__ __forceinline__ void load(const float* p) {
+    a = *reinterpret_cast<const float4*>(p);
+    b = *reinterpret_cast<const float4*>(p + 4);
+  }
+  __device__ __forceinline__ void get(float (&x)[8]) const {
+    x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w, x[4] = b.x, x[5] = b.y, x[6] = b.z, x[7] = b.w;
+  }
+};
+template <>
+struct Raw8<uint16_t> {
+  uint4 v;
+  __device__ __forceinline__ void load(const uint16_t* p) { v = *reinterpret_cast<const uint4*>(p); }
+  __device__ __forceinline__ void get(float (&x)[8]) const {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x[2 * e] = __uint_as_float(w[e] << 16);
+      x[2 * e + 1] = __uint_as_float(w[e] & 0xFFFF0000u);
     }
-    if (q28) {
-      // output a * m + b = sum_k Q[a][k] buf[k * m + b]: one b per thread, its 28 inputs held in
-      // registers, the rows of Q read as 16-byte broadcasts
-      for (int64_t b = tid; b < m; b += RP_THREADS) {
-        float x[28];
+  }
+};
+
+template <typename T>
+__global__ __launch_bounds__(RP_THREADS, 4) void row_pass512(
+    const T* __restrict__ src, int64_t lds_, float* __restrict__ dst, int64_t ldd, int64_t rows,
+    int64_t n, const float* __restrict__ pre_row, const float* __restrict__ pre_col,
+    const float* __restrict__ post_row, const float* __restrict__ post_col, int64_t m,
+    const float* __restrict__ q28, int q_trans, float norm) {
+  extern __shared__ float smem[];
+  float* buf = smem;  // n floats
+  constexpr int NB = 4, STEP = RP_THREADS * 8;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int64_t c0 = int64_t(tid >> 6) * 512 + lane * 8;
+  const int ni = n > c0 ? int((n - c0 + STEP - 1) / STEP) : 0;  // (uniform over the wave)
+  Raw8<T> next[NB];
+  auto fetch = [&](int64_t r) {
+    const T* p = src + r * lds_ + c0;
 #pragma unroll
-        for (int k = 0; k < 28; ++k) x[k] = buf[k * m + b];
-        for (int a = 0; a < 28; ++a) {
-          const float4* qa = reinterpret_cast<const float4*>(qs + a * 28);
-          float acc = 0.f;
-#pragma unroll
-          for (int k4 = 0; k4 < 7; ++k4) {
-            const float4 q = qa[k4];
-            acc = fmaf(q.x, x[4 * k4], acc);
-            acc = fmaf(q.y, x[4 * k4 + 1], acc);
-            acc = fmaf(q.z, x[4 * k4 + 2], acc);
-            acc = fmaf(q.w, x[4 * k4 + 3], acc);
-          }
-          const int64_t c = a * m + b;
-          float y = acc * po;
-          if (post_col) y *= post_col[c];
-          o[c] = y;
-        }
-      }
-    } else if ((n & 3) == 0) {
-      for (int64_t c = int64_t(tid) * 4; c < n; c += int64_t(RP_THREADS) * 4) {
-        float4 y = *reinterpret_cast<const float4*>(buf + c);
-        const float4 pc = post_col ? *reinterpret_cast<const float4*>(post_col + c)
-                                   : make_float4(1.f, 1.f, 1.f, 1.f);
-        y.x *= po * pc.x, y.y *= po * pc.y, y.z *= po * pc.z, y.w *= po * pc.w;
-        *reinterpret_cast<float4*>(o + c) = y;
-      }
+    for (int i = 0; i < NB; ++i)
+      if (i < ni) next[i].load(p + i * STEP);
+  };
+  auto chunk = [&](const Raw8<T>& w, int64_t c, float pr) {
+    float x[8];
+    w.get(x);
+    if (pre_col) {
+      const float4 p0 = *reinterpret_cast<const float4*>(pre_col + c);
+      const float4 p1 = *reinterpret_cast<const float4*>(pre_col + c + 4);
+      x[0] *= pr * p0.x, x[1] *= pr * p0.y, x[2] *= pr * p0.z, x[3] *= pr * p0.w;
+      x[4] *= pr * p1.x, x[5] *= pr * p1.y, x[6] *= pr * p1.z, x[7] *= pr * p1.w;
     } else {
-      for (int64_t c = tid; c < n; c += RP_THREADS) {
-        float y = buf[c] * po;
-        if (post_col) y *= post_col[c];
-        o[c] = y;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] *= pr;
+    }
+    hadamard_reg<8>(x);
+    hadamard_lanes<8>(x, lane);
+    *reinterpret_cast<float4*>(buf + c) = make_float4(x[0], x[1], x[2], x[3]);
+    *reinterpret_cast<float4*>(buf + c + 4) = make_float4(x[4], x[5], x[6], x[7]);
+  };
+  Mix28 mix;
+  if (q28) mix.load(q28, q_trans, lane);
+  fetch(blockIdx.x);  // (the grid has at most as many workgroups as there are rows)
+  for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
+    const float pr = pre_row ? pre_row[r] : 1.f;
+    const float po = (post_row ? post_row[r] : 1.f) * norm;
+    __syncthreads();  // previous row finished with buf
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if (i < ni) chunk(next[i], c0 + i * STEP, pr);
+    for (int i = NB; i < ni; ++i) {
+      Raw8<T> w;
+      w.load(src + r * lds_ + c0 + i * STEP);
+      chunk(w, c0 + i * STEP, pr);
+    }
+    __syncthreads();
+    if (r + gridDim.x < rows) fetch(r + gridDim.x);
+    fwht_lds(buf, n, m, tid, RP_THREADS, 9);
+    row_out(buf, dst + r * ldd, n, m, mix, q28 != nullptr, post_col, po, tid);
+  }
+}
+
+// Row pass of rows of n = 512 NC elements (no 28-point factor) together with the first three
+// stages along the row axis: eight consecutive rows per group, an H_8 over them in registers, so
+// that one column pass of length d / 8 is left where two were needed. A wave holds 512 columns of
+// the eight rows (all its loads in flight at once); the strides of 512 on run on the way out, four
+// rows of each group at a time through 64 KB of LDS, two workgroups per CU.
+// Bound by HBM like the other passes. (4096 x 4096 fp32, both transforms: a row pass and column
+// passes of 64 and 64 took 39 + 25 + 25 us.)
+template <typename T, int NC>
+__global__ __launch_bounds__(512, 4) void row_pass8(
+    const T* __restrict__ src, int64_t lds_, float* __restrict__ dst, int64_t ldd,
+    const float* __restrict__ pre_row, const float* __restrict__ pre_col,
+    const float* __restrict__ post_row, const float* __restrict__ post_col, float norm) {
+  constexpr int G = 8 / NC, n = 512 * NC;  // groups of eight rows per workgroup
+  __shared__ __attribute__((aligned(16))) float buf[4 * G * n];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave / NC, c0 = (wave % NC) * 512 + lane * 4;
+  const int64_t rbase = int64_t(blockIdx.x) * (8 * G);
+  float x[8][8];  // columns c0 + e and c0 + 256 + e
+  {
+    const T* p = src + (rbase + grp * 8) * lds_ + c0;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      load4_f32(p + r * lds_, x[r]);
+      load4_f32(p + r * lds_ + 256, x[r] + 4);
+    }
+    float pc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) pc[e] = 1.f;
+    if (pre_col) {
+      load4_f32(pre_col + c0, pc);
+      load4_f32(pre_col + c0 + 256, pc + 4);
+    }
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const float pr = pre_row ? pre_row[rbase + grp * 8 + r] : 1.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[r][e] *= pr * pc[e];
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float y[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) y[r] = x[r][e];
+    hadamard_reg<8>(y);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) x[r][e] = y[r];
+  }
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    hadamard_reg<8>(x[r]);
+    hadamard_lanes<8>(x[r], lane);
+  }
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    if (half) __syncthreads();  // the first half was read
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float* v = x[half * 4 + r];
+      float* b = buf + (grp * 4 + r) * n + c0;
+      *reinterpret_cast<float4*>(b) = make_float4(v[0], v[1], v[2], v[3]);
+      *reinterpret_cast<float4*>(b + 256) = make_float4(v[4], v[5], v[6], v[7]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < G; ++it) {  // (row, four columns of the first 512)
+      const int row = (tid + it * 512) >> 7, cc = (tid & 127) * 4;
+      const int64_t gr = rbase + (row >> 2) * 8 + half * 4 + (row & 3);
+      float y[4][NC];
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        const float4 v = *reinterpret_cast<const float4*>(buf + row * n + k * 512 + cc);
+        y[0][k] = v.x, y[1][k] = v.y, y[2][k] = v.z, y[3][k] = v.w;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) hadamard_reg<NC>(y[e]);
+      const float po = (post_row ? post_row[gr] : 1.f) * norm;
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        const float4 pc = post_col ? *reinterpret_cast<const float4*>(post_col + k * 512 + cc)
+                                   : make_float4(1.f, 1.f, 1.f, 1.f);
+        *reinterpret_cast<float4*>(dst + gr * ldd + k * 512 + cc) =
+            make_float4(y[0][k] * (po * pc.x), y[1][k] * (po * pc.y), y[2][k] * (po * pc.z),
+                        y[3][k] * (po * pc.w));
       }
     }
   }
@@ -345,7 +538,7 @@ __global__ __launch_bounds__(NT) void col_pass(const float* __restrict__ src, in
     }
   }
   const int cw4 = CW / 4;
-  int lcw4 = 0;  // CW is a power of 2 (32, 64 or 256): shifts instead of divisions
+  int lcw4 = 0;  // CW is a power of 2 (16 ... 256): shifts instead of divisions
   while ((1 << lcw4) < cw4) ++lcw4;
   // load the L x CW tile: 8 independent float4 loads in flight per thread before they are
   // stored (one workgroup per CU at L = 1024, so latency must be hidden within the thread)
@@ -466,15 +659,27 @@ int launch_row_pass(const void* src, int dtype, int64_t lds_, float* dst, int64_
                     const float* post_row, const float* post_col, bool transform,
                     const RotDim& rd, const float* q28, bool q_trans, hipStream_t s,
                     const char* name) {
-  const size_t shmem = transform ? (size_t(n) + 28 * 28) * sizeof(float) : 0;
-  const unsigned grid = unsigned(rows < 4096 ? rows : 4096);
+  const size_t shmem = transform ? size_t(n) * sizeof(float) : 0;
   const float norm = transform ? float(1.0 / std::sqrt(double(rd.m))) : 1.f;
   const float* q = (transform && rd.has28) ? q28 : nullptr;
+  if (transform && rd.m >= 512) {
+    const int per_cu = shmem <= 40 * 1024 ? 4 : shmem <= 53 * 1024 ? 3 : shmem <= 80 * 1024 ? 2 : 1;
+    const int64_t slots = int64_t(per_cu) * device_cus();
+    const dim3 grid(unsigned(rows < slots ? rows : slots));
+    if (dtype == KRONQ_BF16)
+      return launch(name, row_pass512<uint16_t>, grid, dim3(RP_THREADS), shmem, s,
+                    static_cast<const uint16_t*>(src), lds_, dst, ldd, rows, n, pre_row, pre_col,
+                    post_row, post_col, rd.m, q, int(q_trans), norm);
+    return launch(name, row_pass512<float>, grid, dim3(RP_THREADS), shmem, s,
+                  static_cast<const float*>(src), lds_, dst, ldd, rows, n, pre_row, pre_col,
+                  post_row, post_col, rd.m, q, int(q_trans), norm);
+  }
+  const dim3 grid(unsigned(rows < 4096 ? rows : 4096));
   if (dtype == KRONQ_BF16)
-    return launch(name, row_pass<uint16_t>, dim3(grid), dim3(RP_THREADS), shmem, s,
+    return launch(name, row_pass<uint16_t>, grid, dim3(RP_THREADS), shmem, s,
                   static_cast<const uint16_t*>(src), lds_, dst, ldd, rows, n, pre_row, pre_col,
                   post_row, post_col, int(transform), rd.m, q, int(q_trans), norm);
-  return launch(name, row_pass<float>, dim3(grid), dim3(RP_THREADS), shmem, s,
+  return launch(name, row_pass<float>, grid, dim3(RP_THREADS), shmem, s,
                 static_cast<const float*>(src), lds_, dst, ldd, rows, n, pre_row, pre_col,
                 post_row, post_col, int(transform), rd.m, q, int(q_trans), norm);
 }
@@ -486,8 +691,11 @@ int launch_col_step(const float* src, int64_t lds_, float* dst, int64_t ldd, int
   // and 32 beyond (L = 1024: 1024 x 36 floats + the 28 x 28 factor = 150 KB of LDS, one
   // workgroup per CU, so beyond L = 256 the workgroup has 1024 threads to keep enough loads in
   // flight)
-  const int CW = kind == 1 ? 256 : (L <= 256 ? 64 : 32);
+  int CW = kind == 1 ? 256 : (L <= 256 ? 64 : 32);
   const int64_t n_groups = rows / L;
+  // few strips (small matrices): narrower ones, down to a cache line, as long as CUs are idle
+  // (256 x 256: 15 us with strips of 64 columns, 6.4 with 16)
+  while (kind == 0 && CW > 16 && n_groups * cdiv(cols, CW) * 2 <= device_cus()) CW /= 2;
   const int64_t strips = cdiv(cols, CW);
   const size_t shmem = (size_t(L) * (CW + 4) + 28 * 28) * sizeof(float);
   const float norm = kind == 0 ? float(1.0 / std::sqrt(double(L))) : 1.f;
@@ -531,6 +739,44 @@ int col_transform(const float* src, int64_t lds_, float* dst, int64_t ldd, int64
   return KRONQ_OK;
 }
 
+// Whether a rows x n matrix transformed on both sides takes row_pass8 and one column pass of
+// length rows / 8: where the column transform alone needs two passes (up to 1024 rows need one, so
+// nothing is saved), a row is 4 or 8 chunks of 512, and neither side has the 28-point factor.
+bool fuse8(const RotDim& rrows, const RotDim& rn, int64_t n) {
+  return !rrows.has28 && !rn.has28 && rrows.m >= 2 * CP_MAXL && rrows.m <= 8 * CP_MAXL &&
+         (n == 2048 || n == 4096);
+}
+
+int launch_row_pass8(const void* src, int dtype, int64_t lds_, float* dst, int64_t ldd,
+                     int64_t rows, int64_t n, const float* pre_row, const float* pre_col,
+                     const float* post_row, const float* post_col, hipStream_t s) {
+  const float norm = float(1.0 / std::sqrt(8.0 * double(n)));
+  const dim3 grid(unsigned(rows / (n == 4096 ? 8 : 16))), block(512);
+  if (dtype == KRONQ_BF16)
+    return launch("rot_row_pass", n == 4096 ? row_pass8<uint16_t, 8> : row_pass8<uint16_t, 4>,
+                  grid, block, 0, s, static_cast<const uint16_t*>(src), lds_, dst, ldd, pre_row,
+                  pre_col, post_row, post_col, norm);
+  return launch("rot_row_pass", n == 4096 ? row_pass8<float, 8> : row_pass8<float, 4>, grid, block,
+                0, s, static_cast<const float*>(src), lds_, dst, ldd, pre_row, pre_col, post_row,
+                post_col, norm);
+}
+
+// dst = T_rows diag(pre_row) src diag(pre_col) T_n^T, either transform optional
+int two_sided(const void* src, int dtype, int64_t lds_, float* dst, int64_t ldd, int64_t rows,
+              int64_t n, const float* pre_row, const float* pre_col, bool rot_n, const RotDim& rn,
+              const float* q28_n, bool rot_rows, const RotDim& rrows, const float* q28_rows,
+              hipStream_t s) {
+  if (rot_n && rot_rows && fuse8(rrows, rn, n)) {
+    KQ_TRY(launch_row_pass8(src, dtype, lds_, dst, ldd, rows, n, pre_row, pre_col, nullptr,
+                            nullptr, s));
+    return launch_col_step(dst, ldd, dst, ldd, rows, n, rows / 8, 8, 0, nullptr, false, s);
+  }
+  KQ_TRY(launch_row_pass(src, dtype, lds_, dst, ldd, rows, n, pre_row, pre_col, nullptr, nullptr,
+                         rot_n, rn, q28_n, false, s, "rot_row_pass"));
+  return rot_rows ? col_transform(dst, ldd, dst, ldd, rows, n, rrows, q28_rows, false, s)
+                  : KRONQ_OK;
+}
+
 }  // namespace
 
 // rows of src (B vectors of length n) -> diag(post_col) T diag(pre_col) x, with T the randomised
@@ -565,10 +811,7 @@ int rotate_drift_launch(float* D, int64_t d, int64_t ldd, const float* sx, const
   KQ_TRY(launch("rot_inv_factors", inv_factors, dim3(unsigned(cdiv(d, 256))), dim3(256), 0, s, d,
                 (flags & KRONQ_RESCALE_IN) ? sx : static_cast<const float*>(nullptr),
                 rot ? sign : static_cast<const int8_t*>(nullptr), mh));
-  KQ_TRY(launch_row_pass(D, KRONQ_FP32, ldd, D, ldd, d, d, mh, mh, nullptr, nullptr, rot, r, q28,
-                         false, s, "rot_row_pass"));
-  if (rot) KQ_TRY(col_transform(D, ldd, D, ldd, d, d, r, q28, false, s));
-  return KRONQ_OK;
+  return two_sided(D, KRONQ_FP32, ldd, D, ldd, d, d, mh, mh, rot, r, q28, rot, r, q28, s);
 }
 
 size_t rotate_ws_bytes(int64_t d_out, int64_t d_in) {
@@ -607,6 +850,11 @@ int rotate_launch(const void* W_in, int w_dtype, int64_t ldw_in, float* W, int64
                   s, d_out, static_cast<const float*>(sg), rot_out ? sign_out : nullptr, mw_out));
     const float* src = static_cast<const float*>(W_in);
     int64_t lsrc = ldw_in;
+    if (rot_in && rot_out && fuse8(ro, ri, d_in)) {
+      KQ_TRY(launch_col_step(src, lsrc, W, ldw, d_out, d_in, d_out / 8, 8, 0, nullptr, true, s));
+      return launch_row_pass8(W, KRONQ_FP32, ldw, W, ldw, d_out, d_in, nullptr, nullptr, mw_out,
+                              mw_in, s);
+    }
     if (rot_out) {
       KQ_TRY(col_transform(src, lsrc, W, ldw, d_out, d_in, ro, q28_out, true, s));
       src = W;
@@ -624,10 +872,10 @@ int rotate_launch(const void* W_in, int w_dtype, int64_t ldw_in, float* W, int64
                           ((flags & KRONQ_RESCALE_OUT) && do_w);
   if (need_norms) {
     if (w_dtype == KRONQ_BF16)
-      KQ_TRY(launch("rot_w_norms", w_norms<uint16_t>, dim3(unsigned(nb)), dim3(256), 0, s,
+      KQ_TRY(launch("rot_w_norms", w_norms<uint16_t>, dim3(unsigned(nb)), dim3(NORM_THREADS), 0, s,
                     static_cast<const uint16_t*>(W_in), d_out, d_in, ldw_in, colp, rows));
     else
-      KQ_TRY(launch("rot_w_norms", w_norms<float>, dim3(unsigned(nb)), dim3(256), 0, s,
+      KQ_TRY(launch("rot_w_norms", w_norms<float>, dim3(unsigned(nb)), dim3(NORM_THREADS), 0, s,
                     static_cast<const float*>(W_in), d_out, d_in, ldw_in, colp, rows));
   }
   if (!sx_given)
@@ -646,15 +894,13 @@ int rotate_launch(const void* W_in, int w_dtype, int64_t ldw_in, float* W, int64
                   static_cast<const double*>(rows), rot_out ? sign_out : nullptr,
                   int((flags & KRONQ_RESCALE_OUT) != 0), sg, mw_out, mh_out));
     // W: rescale + signs + V side (row pass), then U side (column pass)
-    KQ_TRY(launch_row_pass(W_in, w_dtype, ldw_in, W, ldw, d_out, d_in, mw_out, mw_in, nullptr,
-                           nullptr, rot_in, ri, q28_in, false, s, "rot_row_pass"));
-    if (rot_out) KQ_TRY(col_transform(W, ldw, W, ldw, d_out, d_in, ro, q28_out, false, s));
+    KQ_TRY(two_sided(W_in, w_dtype, ldw_in, W, ldw, d_out, d_in, mw_out, mw_in, rot_in, ri, q28_in,
+                     rot_out, ro, q28_out, s));
   }
   // H_X <- V S^-1 H_X S^-1 V^T
   if (!sx_given) {
-    KQ_TRY(launch_row_pass(HX, KRONQ_FP32, ldx, HX, ldx, d_in, d_in, mh_in, mh_in, nullptr,
-                           nullptr, rot_in, ri, q28_in, false, s, "rot_row_pass"));
-    if (rot_in) KQ_TRY(col_transform(HX, ldx, HX, ldx, d_in, d_in, ri, q28_in, false, s));
+    KQ_TRY(two_sided(HX, KRONQ_FP32, ldx, HX, ldx, d_in, d_in, mh_in, mh_in, rot_in, ri, q28_in,
+                     rot_in, ri, q28_in, s));
   }
   // H_G <- U S^-1 H_G S^-1 U^T (with a given sg, the multipliers sign / s as side_factors
   // forms them)
@@ -662,9 +908,8 @@ int rotate_launch(const void* W_in, int w_dtype, int64_t ldw_in, float* W, int64
     KQ_TRY(launch("rot_factors", inv_factors, dim3(unsigned(cdiv(d_out, 256))), dim3(256), 0, s,
                   d_out, static_cast<const float*>(sg), rot_out ? sign_out : nullptr, mh_out));
   if (HG && !hx_only && !hg_diag) {
-    KQ_TRY(launch_row_pass(HG, KRONQ_FP32, ldg, HG, ldg, d_out, d_out, mh_out, mh_out, nullptr,
-                           nullptr, rot_out, ro, q28_out, false, s, "rot_row_pass"));
-    if (rot_out) KQ_TRY(col_transform(HG, ldg, HG, ldg, d_out, d_out, ro, q28_out, false, s));
+    KQ_TRY(two_sided(HG, KRONQ_FP32, ldg, HG, ldg, d_out, d_out, mh_out, mh_out, rot_out, ro,
+                     q28_out, rot_out, ro, q28_out, s));
   }
   return KRONQ_OK;
 }

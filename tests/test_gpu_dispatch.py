@@ -4,7 +4,8 @@ import pytest
 import torch
 
 import oracle as O
-from gpu_util import DEV, note, rel_frob, to_np
+import synth
+from gpu_util import DEV, note, rel_frob, rot_device, rot_oracle, to_np
 from paper_2607_07964_amd import kronq as K
 
 pytestmark = pytest.mark.gpu
@@ -243,3 +244,43 @@ def test_gptaq_planes(d, pad):
     assert np.all(np.abs(p - ref) <= 0.5 * np.triu(np.triu(eT, 1) @ np.abs(U64) + eP, 1))
     if pad:
         assert torch.isnan(dev[2][:, d:]).all()
+
+
+# ---------------------------------------------------------------- rotations with a fused H_8
+# both sides of the rule (2048 ... 8192 rows of 2048 or 4096), and its neighbours that keep two
+# column passes (a row of 1024) or take one (1024 rows); W as bf16 and fp32, padded rows
+@pytest.mark.parametrize("d_out,d_in,bf16", [(2048, 4096, True), (4096, 2048, False), (2048, 1024, False),
+                                             (8192, 2048, True), (1024, 4096, True)])
+def test_rotate_fused_rows(d_out, d_in, bf16):
+    rng = np.random.default_rng(d_out + d_in)
+    w = torch.from_numpy(rng.standard_normal((d_out, d_in)).astype(np.float32))
+    w = w.to(torch.bfloat16) if bf16 else w
+    hx, hg = (torch.from_numpy(rng.standard_normal((n, n)).astype(np.float32)) for n in (d_in, d_out))
+    for h in (hx, hg):
+        h += h.T.clone()
+        h.diagonal().copy_(1.0 + torch.from_numpy(rng.random(h.shape[0]).astype(np.float32)))
+    ri, ro = (synth.rotation_params(n, 5, s) for n, s in ((d_in, "in"), (d_out, "out")))
+    rin, rout = rot_device(ri), rot_device(ro)
+    wide = torch.full((d_out, d_in + 8), float("nan"), device=DEV)
+    W, HX, HG = wide[:, :d_in], hx.to(DEV), hg.to(DEV)
+    sx, sg = torch.empty(d_in, device=DEV), torch.empty(d_out, device=DEV)
+    note(f"rotate fused rows {d_out}x{d_in} bf16={bf16}")
+    K.kronq_rotate(w.to(DEV), W, HX, HG, rin.sign, rout.sign, rin.q28, rout.q28, sx, sg, K.BIIP)
+    back = torch.empty(d_out, d_in, device=DEV)
+    K.kronq_rotate(W, back, None, None, rin.sign, rout.sign, rin.q28, rout.q28, sx, sg,
+                   K.BIIP | K.INVERSE)
+    torch.cuda.synchronize()
+    # a butterfly stage adds at most 2^-24 of the norm, the multipliers and norms a few more; a
+    # sampled block's share of the error's norm is within 4 of its share of the norm
+    tol = 4 * (np.log2(d_out) + np.log2(d_in) + 8) * 2.0 ** -24
+    rows, cols = (np.sort(rng.choice(n, 24, replace=False)) for n in (d_out, d_in))
+    sx64, sg64 = to_np(sx).astype(np.float64), to_np(sg).astype(np.float64)
+    V = O.rht_rows(d_in, *rot_oracle(ri), cols)
+    U = O.rht_rows(d_out, *rot_oracle(ro), rows)
+    w64 = w.float().numpy().astype(np.float64)
+    assert rel_frob(to_np(W)[np.ix_(rows, cols)], (U * sg64) @ w64 @ (V * sx64).T) < tol
+    for got, h, t in ((HX, hx, V / sx64), (HG, hg, U / sg64)):
+        idx = cols if got is HX else rows
+        assert rel_frob(to_np(got)[np.ix_(idx, idx)], t @ h.numpy().astype(np.float64) @ t.T) < tol
+    assert rel_frob(to_np(back), w64) < tol
+    assert torch.isnan(wide[:, d_in:]).all()
