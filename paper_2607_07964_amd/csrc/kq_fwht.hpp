@@ -25,12 +25,12 @@ __device__ __forceinline__ float dpp_mov(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, true));
 }
 
-// Six butterfly stages across the lanes of a wave (lane xor 1 ... 32) on N registers a lane (N
-// even). Strides 1 ... 8 take the partner by DPP and x = y -+ x in one FMA (exact); strides 16 and
+// Butterfly stages across the lanes of a wave (lane xor 1 ... 8, then 16 and 32 as far as stages,
+// 4 to 6, goes) on N registers a lane (N even). Strides 1 ... 8 take the partner by DPP and x = y -+ x in one FMA (exact); strides 16 and
 // 32 exchange rows between two registers, add and subtract them, and exchange back. No LDS
 // traffic: as __shfl_xor these stages were half of a row's LDS time.
 template <int N>
-__device__ __forceinline__ void hadamard_lanes(float (&x)[N], int lane) {
+__device__ __forceinline__ void hadamard_lanes(float (&x)[N], int lane, int stages = 6) {
   const float s0 = (lane & 1) ? -1.f : 1.f, s1 = (lane & 2) ? -1.f : 1.f;
   const float s2 = (lane & 4) ? -1.f : 1.f, s3 = (lane & 8) ? -1.f : 1.f;
 #pragma unroll
@@ -56,11 +56,12 @@ __device__ __forceinline__ void hadamard_lanes(float (&x)[N], int lane) {
         __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
   };
+  if (stages < 5) return;
 #pragma unroll
-  for (int e = 0; e < N; e += 2) {
-    pair(x[e], x[e + 1], swap16);
-    pair(x[e], x[e + 1], swap32);
-  }
+  for (int e = 0; e < N; e += 2) pair(x[e], x[e + 1], swap16);
+  if (stages < 6) return;
+#pragma unroll
+  for (int e = 0; e < N; e += 2) pair(x[e], x[e + 1], swap32);
 }
 
 // One group of up to 3 butterfly stages (strides h, 2h, 4h; h = 2^lgh) over a buffer of n

@@ -325,10 +325,10 @@ __global__ __launch_bounds__(RP_THREADS) void row_pass(
     row_out(buf, o, n, m, mix, mixed, post_col, po, tid);
   }
 }
-// Row pass with m >= 512 (n = L m): whole 512-element chunks. A wave takes a chunk, 8 consecutive
-// elements per lane, straight from global memory; the stages of strides 1, 2, 4 run in registers
-// and those of strides 8 ... 256 across lanes, so the chunk reaches LDS with its first 9 stages
-// done; the stages of strides >= 512 follow in LDS. Workgroups stay on the chip and take rows in
+// Row pass with m >= 128 and n = L m a multiple of 512: whole 512-element chunks. A wave takes a
+// chunk, 8 consecutive elements per lane, straight from global memory; the stages of strides 1, 2,
+// 4 run in registers and those of strides 8 ... 256 across lanes, so the chunk reaches LDS with its
+// first 9 stages (or all) done; the stages of strides >= 512 follow in LDS. Workgroups stay on the chip and take rows in
 // turn; the first four chunks a wave holds of the next row are loaded while this one is mixed and
 // stored. Bound by HBM where a row leaves room for four workgroups a CU; at 14336 (two) by each
 // workgroup's own sequence of load, butterflies, mix and store.
@@ -370,6 +370,7 @@ __global__ __launch_bounds__(RP_THREADS, 4) void row_pass512(
   extern __shared__ float smem[];
   float* buf = smem;  // n floats
   constexpr int NB = 4, STEP = RP_THREADS * 8;
+  const int lg9 = m >= 512 ? 9 : m == 256 ? 8 : 7;  // stages done before LDS
   const int tid = threadIdx.x, lane = tid & 63;
   const int64_t c0 = int64_t(tid >> 6) * 512 + lane * 8;
   const int ni = n > c0 ? int((n - c0 + STEP - 1) / STEP) : 0;  // (uniform over the wave)
@@ -393,7 +394,7 @@ __global__ __launch_bounds__(RP_THREADS, 4) void row_pass512(
       for (int e = 0; e < 8; ++e) x[e] *= pr;
     }
     hadamard_reg<8>(x);
-    hadamard_lanes<8>(x, lane);
+    hadamard_lanes<8>(x, lane, lg9 - 3);
     *reinterpret_cast<float4*>(buf + c) = make_float4(x[0], x[1], x[2], x[3]);
     *reinterpret_cast<float4*>(buf + c + 4) = make_float4(x[4], x[5], x[6], x[7]);
   };
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(RP_THREADS, 4) void row_pass512(
     }
     __syncthreads();
     if (r + gridDim.x < rows) fetch(r + gridDim.x);
-    fwht_lds(buf, n, m, tid, RP_THREADS, 9);
+    fwht_lds(buf, n, m, tid, RP_THREADS, lg9);
     row_out(buf, dst + r * ldd, n, m, mix, q28 != nullptr, post_col, po, tid);
   }
 }
@@ -662,7 +663,7 @@ int launch_row_pass(const void* src, int dtype, int64_t lds_, float* dst, int64_
   const size_t shmem = transform ? size_t(n) * sizeof(float) : 0;
   const float norm = transform ? float(1.0 / std::sqrt(double(rd.m))) : 1.f;
   const float* q = (transform && rd.has28) ? q28 : nullptr;
-  if (transform && rd.m >= 512) {
+  if (transform && rd.m >= 128 && n % 512 == 0) {
     const int per_cu = shmem <= 40 * 1024 ? 4 : shmem <= 53 * 1024 ? 3 : shmem <= 80 * 1024 ? 2 : 1;
     const int64_t slots = int64_t(per_cu) * device_cus();
     const dim3 grid(unsigned(rows < slots ? rows : slots));
