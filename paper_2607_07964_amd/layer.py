@@ -155,24 +155,26 @@ def solve(st: LayerState, bits: int, damp: float = 0.01, alpha: Optional[float] 
     sweep(st, bits, alpha)
 
 
-# Share of the compute units left free beside the H_G covariance in the two-stream schedule, for
-# the factorisation's and the sweep's latency-bound kernels (a covariance workgroup holds its CU
-# for a whole tile, so uncapped it starves them: the 8B q_proj takes 14.7 ms per layer uncapped,
-# 11.5 ms on half the chip). The covariance loses less than the CUs it gives up, its clock
-# being power-limited on the full chip: on half the chip the q_proj H_G takes 5.5-6.1 ms instead
-# of 4.1 ms. Half the chip where the factorisation is not much shorter than that covariance; an
-# eighth where H_G outlasts factorisation and sweep many times over (70B up_proj, d = 28672
-# against d = 8192: 238.7 ms per layer on 7/8 of the chip, 242.9 ms on 3/4, 247.7 ms on one
-# stream, 262.5 ms uncapped). The estimate uses rough rates: 1.1 PFLOP/s for a covariance,
-# 20 TFLOP/s for the factorisation.
-FACTOR_SHARE = 0.5
-FACTOR_SHARE_SHORT = 0.125
+# CUs the H_G covariance holds in the two-stream schedule; the rest is left to the factorisation's
+# and the sweep's latency-bound kernels (a covariance workgroup holds its CU for a whole tile, so
+# uncapped it starves them). Both sides should end together, so the share follows their times, from
+# rough rates: 1.1 PFLOP/s for a covariance on the whole chip; for the other side 75 us per 128
+# columns (a leaf's chain and a block of the sweep) and 300 TFLOP/s for the large products. Between
+# 3/8 (fewer CUs do not shorten the other side) and 3/4 of the chip; 7/8 where H_G outlasts the
+# other side many times over. Measured, ms per layer:
+#   4096 x 4096, 262144 tokens: 128 CUs 10.28, 160 9.48, 192 9.18, 208 9.77, uncapped 11.16, on one
+#     stream 11.95;  65536 tokens: 32 6.43, 64 4.38, 96 4.35, 128 4.50, 192 4.65, one stream 5.48
+#   4096 x 14336 (d_out x d_in): 64 65.28, 96 64.49, 128 64.94, 192 67.36, one stream 66.33
+#   14336 x 4096: 192 57.48, 224 55.14, 240 56.49, uncapped 57.77, one stream 56.35
+#   28672 x 8192, 131072 tokens: 192 127.63, 224 122.26, 248 124.26, uncapped 122.59
+COV_SHARE_MIN, COV_SHARE_MAX, COV_SHARE_LONG = 0.375, 0.75, 0.875
 # The drift statistic, first on the second stream (before H_G), holds 13/16 of the chip and
 # leaves the rest to the H_X transform and the factorisation's first leaves and products: at
-# q_proj with the drift correction, 18.49-18.56 ms per layer on 208 CUs against 18.85-18.93
-# on 192 and 224, 19.28-19.33 on 176, 20.73-20.75 on 128 and 19.61-19.70 uncapped.
+# q_proj with the drift correction, 16.99 ms per layer on 208 CUs against 17.34 on 192, 17.11 on
+# 224, 17.77 on 176 and 18.98 on 144.
 DRIFT_SHARE = 13.0 / 16.0
-# Measured alternatives (q_proj, alternating with this schedule in one run): H_G started
+# Measured alternatives (q_proj, alternating with this schedule in one run, H_G on 128 CUs beside
+# a slower factorisation and sweep): H_G started
 # right after H_X with W transformed on the current stream, 11.58 against 11.40 ms; W on a third
 # stream with H_G starting once S_X exists, 11.12 against 11.06 ms; W on the current stream
 # with H_G starting once S_X exists, 11.18 against 11.10 ms; diag(H_G) beside the H_X
@@ -184,10 +186,11 @@ DRIFT_SHARE = 13.0 / 16.0
 def _cov_cus(device, n_tokens: int, d_out: int, d_in: int) -> int:
     """CUs the H_G covariance may hold beside the factorisation and the sweep."""
     t_cov = float(n_tokens) * d_out * d_out / 1.1e15
-    t_factor = (2.0 / 3.0) * float(d_in) ** 3 / 2.0e13
-    share = FACTOR_SHARE if t_factor >= 0.25 * t_cov else FACTOR_SHARE_SHORT
+    t_solve = d_in / 128.0 * 75e-6 + (2.0 / 3.0 * float(d_in) ** 3 + d_out * float(d_in) ** 2) / 3e14
+    share = COV_SHARE_LONG if t_cov > 4.0 * t_solve else \
+        min(COV_SHARE_MAX, max(COV_SHARE_MIN, 0.8 * t_cov / t_solve))
     cus = torch.cuda.get_device_properties(device).multi_processor_count
-    return max(8, int(cus * (1.0 - share)))
+    return max(8, int(cus * share))
 
 
 def schedule(st: LayerState, n_tokens: int, overlap: bool = True,
