@@ -195,8 +195,6 @@ def online_bench(args, spec, dev) -> int:
     # algorithmic HBM bytes of the GEMV kernel: packed codes, scales and zeros, x' and y'
     gbytes = d_out * d_in * bits / 8 + 2 * 4 * d_out * (d_in // group) + 4 * d_in + 4 * d_out
     achieved = gbytes / (gemv_ms * 1e-3) / 1e9
-    int_path = bits in (2, 4)  # the GEMV on integer dot products; 3- and 8-bit codes use fp32
-    gemv_kernel = "online_gemv_p" if int_path else "online_gemv"  # one vector: persistent
     print(f"[bench] online matvec {ms * 1e3:.2f} us (GEMV kernel {gemv_ms * 1e3:.2f} us), "
           f"dense bf16 GEMV {dense_ms * 1e3:.2f} us", file=sys.stderr, flush=True)
     out = {
@@ -204,15 +202,14 @@ def online_bench(args, spec, dev) -> int:
                   "packed-code GEMV, batch 1)",
         "value": round(ms * 1e3, 3), "unit": "us", "n_gpus": 1, "steps": reps, "warmup": warm,
         "ms_per_step": round(ms, 6), "higher_is_better": False, "scaling": "weak",
-        "vs_baseline": None, "dtype": (f"u{bits} codes, i8 dot products (21-bit fixed-point "
-                                        f"activations) with fp32 combine" if int_path else
-                                        f"u{bits} codes, fp32 arithmetic"), "data": "synthetic",
+        "vs_baseline": None, "dtype": f"u{bits} codes, i8 matrix products (four byte digits "
+                                       f"per activation) with fp32 combine", "data": "synthetic",
         "config": {"workload": f"{spec.name} W {d_out}x{d_in}, {bits}-bit, group {group}, "
                                f"decode batch 1", "d_out": d_out, "d_in": d_in, "bits": bits,
                    "group": group, "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": 8000.0,
                      "unit": "GB/s", "frac": round(achieved / 8000.0, 4), "traffic": None,
-                     "kernel": gemv_kernel,
+                     "kernel": "online_gemv_mfma",
                      "launches": g_n,
                      "avg_launch_ms": round(gemv_ms, 6)},
         "dense_bf16_gemv_us": round(dense_ms * 1e3, 3),

@@ -121,7 +121,7 @@ int kronq_version(void);
  * d = d_out). The full symmetric d x d matrix is written. Calls can be chained over token
  * chunks with beta = 1. beta = 0 never reads H (NaNs in it do not propagate).
  *   A     device, dtype KRONQ_BF16 (products exact in fp32, fp32 accumulation on MFMA) or
- *         KRONQ_FP32 (fp32 FMA); rows of lda elements; A and lda*elem_size 16-byte aligned.
+ *         KRONQ_FP32 (fp32 matrix products); rows of lda elements; A and lda*elem_size 16-byte aligned.
  *   H     device fp32 [d x ldh], ldh >= d.
  *   n_rows may be 0 (then H <- beta * H). */
 int kronq_accumulate_cov(const void* A, int dtype, int64_t n_rows, int64_t d, int64_t lda,
@@ -261,7 +261,8 @@ int kronq_cholesky_inv(float* H, int64_t d, int64_t ldh, float damp_rel, float* 
 /* ---- 4b. drift correction (Prop. 1 eq. kronq_update; Alg. 2 third line) ------------------
  * P = alpha ((D U^T) . M_U) U with U from kronq_cholesky_inv (the paper's L is U^T) and M_U the
  * strictly upper mask; P is strictly upper triangular (zeros on and below the diagonal are
- * written). Row p of P is alpha D[p, p+1:] inv(H~[p+1:, p+1:]). fp32 products, 2 d^3 / 3 flops.
+ * written). Row p of P is alpha D[p, p+1:] inv(H~[p+1:, p+1:]). Products of
+ * fp32 accuracy, 2 d^3 / 3 flops.
  *   D  device fp32 [d x ldd]: the transformed drift statistic (kronq_rotate_drift).
  *   U  device fp32 [d x ldu], upper.   P  device fp32 [d x ldp]; must not alias D or U.
  *   All 16-byte aligned with leading dimensions divisible by 4. Workspace: KRONQ_OP_GPTAQ. */

@@ -187,16 +187,12 @@ __device__ __forceinline__ void frag_tile(const FragJob& J, const Tiles& T, int 
   const uint16_t* src1 = wave == 0 ? J.Ph : wave == 1 ? J.Pl : wave == 2 ? J.Qh : J.Ql;
   const uint16_t* src2 = wave == 0 ? J.P2h : wave == 1 ? J.P2l : wave == 2 ? J.Q2h : J.Q2l;
   const int64_t origin = (r0 >> 5) * ks * 512;
-  // an upper Q's tiles end together: k runs down, so that those that share an operand are at the
-  // same k at the same time
-  const bool down = (J.flags & (FRAG_Q_UPPER | FRAG_P_UPPER)) == FRAG_Q_UPPER;
-  const int64_t step = down ? -512 : 512;
-  src1 += origin + ((kbeg >> 4) + (down ? n1 - 1 : 0)) * 512;
+  src1 += origin + (kbeg >> 4) * 512;
   if (J.K2 > 0) src2 += origin;
   const uint32_t lo8 = uint32_t(lane) * 8;
   auto issue = [&](int st, int buf) {
     const int sc = st < nst ? st : nst - 1;  // past the end: the last stage again, never read
-    const uint16_t* p = sc < n1 ? src1 + sc * step : src2 + int64_t(sc - n1) * 512;
+    const uint16_t* p = sc < n1 ? src1 + int64_t(sc) * 512 : src2 + int64_t(sc - n1) * 512;
     uint32_t* dst = lds + buf * STAGE + wave * PLANE;
 #pragma unroll
     for (int g = 0; g < G; ++g)

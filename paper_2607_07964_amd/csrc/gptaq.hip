@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void col_max(const float* __restrict__ U, int6
 }
 
 // (whole correction, fp32 matrix cores against planes: 74 against 82 us at d = 1024, 116 against
-// 101 at 1536, 177 against 123 at 2048, 694 against 335 at 4096; the planes' error against 64 bits
+// 101 at 1536, 177 against 123 at 2048, 694 against 337 at 4096; the planes' error against 64 bits
 // is the smaller one from 1024 on)
 constexpr int64_t PLANES_MIN = 1280;
 
