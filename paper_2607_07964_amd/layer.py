@@ -183,10 +183,25 @@ DRIFT_SHARE = 13.0 / 16.0
 # stream before the factorisation: 20.8 against 20.1 ms.
 
 
-def _cov_cus(device, n_tokens: int, d_out: int, d_in: int) -> int:
-    """CUs the H_G covariance may hold beside the factorisation and the sweep."""
+def _times(n_tokens: int, d_out: int, d_in: int):
+    """Rough seconds of the H_G covariance on the whole chip and of factorisation and sweep."""
     t_cov = float(n_tokens) * d_out * d_out / 1.1e15
     t_solve = d_in / 128.0 * 75e-6 + (2.0 / 3.0 * float(d_in) ** 3 + d_out * float(d_in) ** 2) / 3e14
+    return t_cov, t_solve
+
+
+def _cov_late(n_tokens: int, d_out: int, d_in: int) -> bool:
+    """Whether the H_G covariance waits for the transforms of H_X and W. A long H_G is slowed for
+    its whole time when it starts beside them: its workgroups then no longer read the same tokens
+    at the same time through an XCD's cache (28672 x 8192, 262144 tokens: 225.9 ms per layer after
+    the transforms, 236.5 beside them; 14336 x 4096 56.9 and 56.8). A short one starts at once."""
+    t_cov, t_solve = _times(n_tokens, d_out, d_in)
+    return t_cov > 4.0 * t_solve
+
+
+def _cov_cus(device, n_tokens: int, d_out: int, d_in: int) -> int:
+    """CUs the H_G covariance may hold beside the factorisation and the sweep."""
+    t_cov, t_solve = _times(n_tokens, d_out, d_in)
     share = COV_SHARE_LONG if t_cov > 4.0 * t_solve else \
         min(COV_SHARE_MAX, max(COV_SHARE_MIN, 0.8 * t_cov / t_solve))
     cus = torch.cuda.get_device_properties(device).multi_processor_count
@@ -227,7 +242,8 @@ def quantize_layer(st: LayerState, X, G, W0, rin: RotParams, rout: RotParams, bi
     With ``overlap`` diag(H_G) and H_X come first, then the work is split over two streams: the
     current stream rotates H_X, transforms W, factors H_X and runs the sweep; the second stream
     takes (the drift statistic and) the H_G covariance on ``cov_cus`` CUs (None: the policy of
-    _cov_cus; 0: no cap) as soon as H_X is formed, whose traces and rotation end the layer. The
+    _cov_cus; 0: no cap) as soon as H_X is formed (a long one after W's transform, see _cov_late),
+    whose traces and rotation end the layer. The
     current stream waits for the second at the end. The two schedules differ only in how the
     capped H_G covariance splits the tokens into slices (its sums in another order)."""
     drift = dX is not None
@@ -266,8 +282,10 @@ def quantize_layer(st: LayerState, X, G, W0, rin: RotParams, rout: RotParams, bi
             ev_d.record(st.side)
         # the H_G covariance leaves part of the chip to the factorisation's and the sweep's
         # latency-bound kernels (a covariance workgroup holds its CU for a whole tile)
-        K.kronq_accumulate_cov_limited(G, st.HG, cov_cus, 1.0, 0.0, st.ws_cov_g)
-        K.kronq_traces(None, st.HG, st.tr_pre)
+        late = _cov_late(G.shape[0], st.d_out, st.d_in)
+        if not late:
+            K.kronq_accumulate_cov_limited(G, st.HG, cov_cus, 1.0, 0.0, st.ws_cov_g)
+            K.kronq_traces(None, st.HG, st.tr_pre)
     K.kronq_rotate(W0, None, st.HX, None, rin.sign, None, rin.q28, None, st.sx, st.sg,
                    flags | K.HX_ONLY, st.ws_rot)
     K.kronq_traces(st.HX, None, st.tr_post)
@@ -279,6 +297,9 @@ def quantize_layer(st: LayerState, X, G, W0, rin: RotParams, rout: RotParams, bi
         # the H_G transform uses S_G from W's transform, and the same rotation workspace (the
         # event is recorded above, before this wait is enqueued)
         st.side.wait_event(ev_w)
+        if late:
+            K.kronq_accumulate_cov_limited(G, st.HG, cov_cus, 1.0, 0.0, st.ws_cov_g)
+            K.kronq_traces(None, st.HG, st.tr_pre)
         K.kronq_rotate(None, None, None, st.HG, rin.sign, rout.sign, rin.q28, rout.q28, st.sx,
                        st.sg, flags | K.SX_GIVEN | K.SG_GIVEN, st.ws_rot)
         K.kronq_traces(None, st.HG, st.tr_post)
