@@ -13,10 +13,10 @@
 //        X21 = -X22 T                     (over L21).
 //      Leaves of at most 128 columns are factored and inverted in LDS by one workgroup; every
 //      other step is a product with a long K: on the fp32 matrix cores, and from order FRAG_MIN
-//      on fp16 planes, three products a term (gemm_frag.hip; fp32 values have 24 significant
-//      bits, the planes 23, and the accumulation in fp32 decides the error of both). Three
-//      dependent launches per split (five with planes): the chain of small ones, not the flops,
-//      sets the time at d = 4096;
+//      on fp16 planes, three products a term (gemm_frag.hip): an operand keeps 23 significant bits
+//      down to 2^-16 of its row's largest value and is good to 2^-39 of that below, and the sums in
+//      fp32 decide the error, as in an fp32 product. Three dependent launches per split (nine with
+//      planes): the chain of small ones, not the flops, sets the time at d = 4096;
 //   3. U[i][j] = c_j X[d-1-i][d-1-j] for i <= j, 0 below the diagonal.
 // A non-positive pivot sets *info to its 1-based column in the original order (first failure).
 #include <algorithm>
@@ -63,19 +63,21 @@ __global__ __launch_bounds__(1024) void diag_shift(const float* __restrict__ H, 
 }
 
 // the damped diagonal, and the power of two c_i = 2^-floor(e / 2), e its exponent, that brings it
-// into [1, 4) (1 for an entry that is not positive and finite)
+// into [1, 4) (1 for an entry that is not positive and finite); the large nodes' maxima start at 0
 __global__ void add_diag(float* __restrict__ H, int64_t d, int64_t ldh,
-                         const float* __restrict__ shift, float* __restrict__ cn) {
+                         const float* __restrict__ shift, float* __restrict__ cn,
+                         float* __restrict__ mx, int64_t n_mx) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= d) return;
+  for (int64_t e = i; e < n_mx; e += d) mx[e] = 0.f;
   const float v = H[i * ldh + i] + *shift;
   H[i * ldh + i] = v;
   cn[i] = v > 0.f && v <= 3.0e38f ? ldexpf(1.f, -(ilogbf(v) >> 1)) : 1.f;
 }
 
 // M[i][j] = c_i' c_j' H[i'][j'], i' = d-1-i, j' = d-1-j: reversed, and normalised to a diagonal in
-// [1, 4) (exact: powers of two). Then |M[i][j]| < 4 and |L[i][j]| < 2, which the 16-bit planes of
-// the large products rely on.
+// [1, 4) (exact: powers of two), so that the columns of X11 and X22, whose rows the planes scale
+// as wholes, do not differ with the channels' sizes.
 __global__ void reverse_copy(const float* __restrict__ H, int64_t d, int64_t ldh,
                              const float* __restrict__ cn, float* __restrict__ M, int64_t ldm) {
   const int64_t i = blockIdx.y;
@@ -383,11 +385,12 @@ int64_t split_at(int64_t n) { return (cdiv(n, NB) / 2) * NB; }
 int64_t pad(int64_t n, int64_t m) { return cdiv(n, m) * m; }
 
 // A node of n columns whose parts have at least this order runs its products on 16-bit planes: at
-// 768 a 4096 factor takes 2.06 ms, 14336 13.00 and 3000 1.53 (before the leaves below got faster);
-// at 512 2.11, 13.00 and 1.49, at 1024 2.06, 13.39 and 1.56, at 2048 2.17, 14.25 and 1.68. Below,
-// the five launches cost more than the products. (Products on the fp32 matrix cores and, from
-// order 3000, on six bf16 products a term split inside the kernel: 2.47, 22.4 and 1.71 ms; error
-// of U against float64 5.5e-7 and 8.6e-7 at 4096 and 14336, now 4.0e-7 and 7.3e-7.)
+// 768 a factor of order 3000 takes 1.42 ms, 4096 1.93, 8192 4.85 and 14336 12.97; at 512 1.40, 2.06,
+// 5.13 and 13.01, at 1024 1.44, 1.93, 4.86 and 13.15, at 2048 1.53, 1.99, 4.96 and 13.83. Below, the
+// nine launches cost more than the products. (Products on the fp32 matrix cores and, from order
+// 3000, on six bf16 products a term split inside the kernel: 1.71 ms at 3000, 2.47 at 4096 and 22.4
+// at 14336, the 4096 and 14336 with slower leaves; error of U against float64 5.5e-7 and 8.6e-7 at
+// 4096 and 14336, now 3.6e-7 and 6.3e-7.)
 constexpr int64_t FRAG_MIN = 768;
 bool frag_node(int64_t n) {
   const int64_t h = split_at(n);
@@ -406,11 +409,18 @@ int64_t chol_scratch(int64_t n) {
   const int64_t t = frag_node(n) ? planes(h, r) : r * h;
   return std::max(chol_scratch(h), t + chol_scratch(r));
 }
-// and the planes a large node needs only while it runs (M21 or X22, X11, its transpose, L21)
+// the planes a large node needs only while it runs (M21 or X22, X11, its transpose, L21)
 int64_t chol_planes(int64_t n) {
   if (n <= NB || !frag_node(n)) return 0;
   const int64_t h = split_at(n), r = n - h;
   return std::max(planes(r, h), planes(r, r)) + 2 * planes(h, h) + planes(r, h);
+}
+// and the largest values of their rows, of each node its own: M21, L21, X22 (r rows), X11, its
+// transpose, T^T (h)
+int64_t chol_maxima(int64_t n) {
+  if (n <= NB || !frag_node(n)) return 0;
+  const int64_t h = split_at(n);
+  return 3 * n + chol_maxima(h) + chol_maxima(n - h);
 }
 
 struct Chol {
@@ -420,86 +430,106 @@ struct Chol {
   hipStream_t s;
 };
 
+// the two planes of an operand and the largest values of their rows
 struct Planes {
   uint16_t *h, *l;
   int64_t ks;
+  float* max;
 };
-Planes take_planes(float*& at, int64_t rows, int64_t k) {
+Planes take_planes(float*& at, int64_t rows, int64_t k, float*& mx) {
   const int64_t n = planes(rows, k);
-  Planes p{reinterpret_cast<uint16_t*>(at), reinterpret_cast<uint16_t*>(at) + n, pad(k, 16) / 16};
+  Planes p{reinterpret_cast<uint16_t*>(at), reinterpret_cast<uint16_t*>(at) + n, pad(k, 16) / 16,
+           mx};
   at += n;
+  mx += rows;
   return p;
 }
+SplitJob split_job(const float* src, int64_t ld, int64_t rows, int64_t cols, int tri, bool trans,
+                   const Planes& p) {
+  return SplitJob{src, ld, rows, cols, tri, trans, p.max, p.h, p.l, p.ks};
+}
+FragJob frag_job(const Planes& P, const Planes& Q, int64_t M, int64_t N, int64_t K, int flags,
+                 float alpha, float* C, int64_t ldc) {
+  FragJob j{};
+  j.Ph = P.h, j.Pl = P.l, j.pks = P.ks, j.pmax = P.max;
+  j.Qh = Q.h, j.Ql = Q.l, j.qks = Q.ks, j.qmax = Q.max;
+  j.M = M, j.N = N, j.K = K, j.flags = flags, j.alpha = alpha, j.C = C, j.ldc = ldc;
+  return j;
+}
 
-// Powers of two that bring each operand's values into the range of fp16: |M| < 4, |L| < 2; X and
-// T = L21 X11 grow as the inverse square root of the smallest eigenvalue of the normalised H~
-// (2^12 there is the square root of the fp32 rounding unit, beyond which fp32 does not factor
-// either). What falls below the smallest fp16 (2^-24) is 2^-28 of a unit diagonal or less.
-constexpr float SC_M = 4096.f, SC_L = 4096.f, SC_X = 16.f, SC_T = 4.f;
+int chol_rec(const Chol& c, float* T, float*& mx, int64_t n0, int64_t n);
 
-int chol_rec(const Chol& c, float* T, int64_t n0, int64_t n);
-
-// The four products of a large node on fp16 planes (gemm_frag.hip): L21 leaves its product as
-// planes, the operand of the two products after it, and T as planes of its transpose.
-int chol_node_frag(const Chol& c, float* T, int64_t n0, int64_t n) {
+// The four products of a large node on fp16 planes (gemm_frag.hip). Every row of an operand is
+// scaled by its own largest value: those of L21 and T = L21 X11 are small where the two parts
+// hardly depend on each other, and X grows as the inverse square root of the smallest eigenvalue,
+// which no fixed power of two covers. So L21 and T, whose largest values only the finished product
+// knows, go through fp32 at X21's place, which nothing else uses before the last step. (A power of
+// two per matrix, L21 and T leaving their products as planes: X overflowed from 4095 on, and a
+// coupling of 1e-4 left X21 good to 4e-5 where it is now good to 4e-7. It took 1.85 ms at 4096 and
+// 12.12 at 14336; twelve more launches of 5 to 8 us at 4096, and the reads for the largest values, are
+// the difference to now.)
+int chol_node_frag(const Chol& c, float* T, float*& mx, int64_t n0, int64_t n) {
   const int64_t h = split_at(n), r = n - h, ld = c.ld;
-  KQ_TRY(chol_rec(c, T, n0, h));
+  KQ_TRY(chol_rec(c, T, mx, n0, h));
   const float* M21 = c.M + (n0 + h) * ld + n0;
   const float* X11 = c.X + n0 * ld + n0;
   float* X21 = c.X + (n0 + h) * ld + n0;
   const float* X22 = c.X + (n0 + h) * ld + n0 + h;
   float* M22 = c.M + (n0 + h) * ld + n0 + h;
   float* at = c.planes;
-  const Planes pL = take_planes(at, r, h), pX = take_planes(at, h, h),
-               pXt = take_planes(at, h, h);
+  const Planes pL = take_planes(at, r, h, mx), pX = take_planes(at, h, h, mx),
+               pXt = take_planes(at, h, h, mx);
   float* at2 = at;
-  const Planes pM = take_planes(at, r, h), pY = take_planes(at2, r, r);  // (the same place)
-  const Planes pT = take_planes(T, h, r);
-  const SplitJob split[3] = {
-      {M21, ld, r, h, SPLIT_FULL, false, SC_M, nullptr, pM.h, pM.l, pM.ks},
-      {X11, ld, h, h, SPLIT_LOWER, false, SC_X, nullptr, pX.h, pX.l, pX.ks},
-      {X11, ld, h, h, SPLIT_LOWER, true, SC_X, nullptr, pXt.h, pXt.l, pXt.ks}};
-  KQ_TRY(split_planes_launch(split, 3, c.s, "chol_split"));
+  const Planes pM = take_planes(at, r, h, mx), pY = take_planes(at2, r, r, mx);  // (the same place)
+  const Planes pT = take_planes(T, h, r, mx);
   // tiles: the K ranges (or, for the lower triangle, the tiles themselves) make the work uneven,
   // so 256 x 256 tiles only where they come in several rounds of the chip
   auto tile = [](int64_t tiles256) { return tiles256 >= 2 * int64_t(device_cus()) ? 256 : 128; };
   const int64_t tr = cdiv(r, 256), th = cdiv(h, 256);
-  FragJob l21{};  // D = X11 M21^T; L21 = D^T
-  l21.Ph = pX.h, l21.Pl = pX.l, l21.pks = pX.ks, l21.Qh = pM.h, l21.Ql = pM.l, l21.qks = pM.ks;
-  l21.M = h, l21.N = r, l21.K = h, l21.flags = FRAG_P_LOWER;
-  l21.alpha = SC_L / (SC_X * SC_M), l21.Oh = pL.h, l21.Ol = pL.l, l21.oks = pL.ks;
+  const AbsMaxJob top[2] = {{M21, ld, r, h, TRI_FULL, pM.max, nullptr},
+                            {X11, ld, h, h, TRI_LOWER, pX.max, pXt.max}};
+  KQ_TRY(abs_max_launch(top, 2, c.s, "chol_split"));
+  const SplitJob split[3] = {split_job(M21, ld, r, h, TRI_FULL, false, pM),
+                             split_job(X11, ld, h, h, TRI_LOWER, false, pX),
+                             split_job(X11, ld, h, h, TRI_LOWER, true, pXt)};
+  KQ_TRY(split_planes_launch(split, 3, c.s, "chol_split"));
+  // L21 = M21 X11^T
+  FragJob l21 = frag_job(pM, pX, r, h, h, FRAG_Q_LOWER, 1.f, X21, ld);
+  l21.rmax = pL.max;
   KQ_TRY(gemm_frag_f16(&l21, 1, tile(tr * th), c.s, "chol_trsm"));
-  FragJob two[2] = {};  // M22 -= L21 L21^T (lower tiles) and T = L21 X11
-  two[0].Ph = two[0].Qh = pL.h, two[0].Pl = two[0].Ql = pL.l, two[0].pks = two[0].qks = pL.ks;
-  two[0].M = two[0].N = r, two[0].K = h, two[0].flags = FRAG_LOWER;
-  two[0].alpha = -1.f / (SC_L * SC_L), two[0].C = M22, two[0].ldc = ld, two[0].add = true;
-  two[1].Ph = pL.h, two[1].Pl = pL.l, two[1].pks = pL.ks;
-  two[1].Qh = pXt.h, two[1].Ql = pXt.l, two[1].qks = pXt.ks;
-  two[1].M = r, two[1].N = h, two[1].K = h, two[1].flags = FRAG_Q_UPPER;
-  two[1].alpha = SC_T / (SC_L * SC_X), two[1].Oh = pT.h, two[1].Ol = pT.l, two[1].oks = pT.ks;
+  const SplitJob split_l = split_job(X21, ld, r, h, TRI_FULL, false, pL);
+  KQ_TRY(split_planes_launch(&split_l, 1, c.s, "chol_split"));
+  // M22 -= L21 L21^T (lower tiles) and T = L21 X11
+  FragJob two[2] = {frag_job(pL, pL, r, r, h, FRAG_LOWER, -1.f, M22, ld),
+                    frag_job(pL, pXt, r, h, h, FRAG_Q_UPPER, 1.f, X21, ld)};
+  two[0].add = true;
+  two[1].cmax = pT.max;
   KQ_TRY(gemm_frag_f16(two, 2, tile(tr * (tr + 1) / 2 + tr * th), c.s, "chol_syrk_trtri_row"));
-  KQ_TRY(chol_rec(c, T, n0 + h, r));
-  const SplitJob split22{X22, ld, r, r, SPLIT_LOWER, false, SC_X, nullptr, pY.h, pY.l, pY.ks};
+  const SplitJob split_t = split_job(X21, ld, r, h, TRI_FULL, true, pT);
+  KQ_TRY(split_planes_launch(&split_t, 1, c.s, "chol_split"));
+  KQ_TRY(chol_rec(c, T, mx, n0 + h, r));
+  const AbsMaxJob top22{X22, ld, r, r, TRI_LOWER, pY.max, nullptr};
+  KQ_TRY(abs_max_launch(&top22, 1, c.s, "chol_split"));
+  const SplitJob split22 = split_job(X22, ld, r, r, TRI_LOWER, false, pY);
   KQ_TRY(split_planes_launch(&split22, 1, c.s, "chol_split"));
-  FragJob x21{};  // X21 = -X22 T
-  x21.Ph = pY.h, x21.Pl = pY.l, x21.pks = pY.ks, x21.Qh = pT.h, x21.Ql = pT.l, x21.qks = pT.ks;
-  x21.M = r, x21.N = h, x21.K = r, x21.flags = FRAG_P_LOWER;
-  x21.alpha = -1.f / (SC_X * SC_T), x21.C = X21, x21.ldc = ld;
+  // X21 = -X22 T
+  const FragJob x21 = frag_job(pY, pT, r, h, r, FRAG_P_LOWER, -1.f, X21, ld);
   return gemm_frag_f16(&x21, 1, tile(tr * th), c.s, "trtri_update");
 }
 
 // L and L^-1 of the block [n0, n0 + n) of M; the lower part of the same block of X receives
-// L^-1 (zeros on the upper part of the diagonal leaves). T: scratch of chol_scratch(n) floats.
-int chol_rec(const Chol& c, float* T, int64_t n0, int64_t n) {
+// L^-1 (zeros on the upper part of the diagonal leaves). T: scratch of chol_scratch(n) floats; mx:
+// the zeros that the large nodes take their maxima from.
+int chol_rec(const Chol& c, float* T, float*& mx, int64_t n0, int64_t n) {
   float *M = c.M, *X = c.X;
   const int64_t ld = c.ld;
   hipStream_t s = c.s;
   if (n <= NB)
     return launch("chol_potrf_diag", potrf_diag, dim3(1), dim3(256), 0, s,
                   static_cast<const float*>(M), ld, n0, int(n), c.d, X, c.info);
-  if (frag_node(n)) return chol_node_frag(c, T, n0, n);
+  if (frag_node(n)) return chol_node_frag(c, T, mx, n0, n);
   const int64_t h = split_at(n), r = n - h;
-  KQ_TRY(chol_rec(c, T, n0, h));
+  KQ_TRY(chol_rec(c, T, mx, n0, h));
   const float* M21 = M + (n0 + h) * ld + n0;
   const float* X11 = X + n0 * ld + n0;
   float* X21 = X + (n0 + h) * ld + n0;
@@ -513,7 +543,7 @@ int chol_rec(const Chol& c, float* T, int64_t n0, int64_t n) {
   const GemmProb syrk{GEMM_TB | GEMM_LOWER_C, r, r, h, -1.f, X21, ld, X21, ld, 1.f, M22, ld};
   const GemmProb row{GEMM_B_LOWER, r, h, h, 1.f, X21, ld, X11, ld, 0.f, T, h};
   KQ_TRY(gemm_f32_dual(syrk, row, s, "chol_syrk_trtri_row"));
-  KQ_TRY(chol_rec(c, T + r * h, n0 + h, r));
+  KQ_TRY(chol_rec(c, T + r * h, mx, n0 + h, r));
   // X21 = -X22 T
   return gemm_f32(GEMM_A_LOWER, r, h, r, -1.f, X22, ld, T, h, 0.f, X21, ld, s, "trtri_update");
 }
@@ -526,6 +556,7 @@ size_t chol_ws_bytes(int64_t d) {
   return 2 * align256(size_t(d) * ld * sizeof(float)) +
          align256(size_t(std::max<int64_t>(1, chol_scratch(d))) * sizeof(float)) +
          align256(size_t(chol_planes(d)) * sizeof(float)) +
+         align256(size_t(chol_maxima(d)) * sizeof(float)) +
          align256(size_t(d) * sizeof(float)) + 512;
 }
 
@@ -537,13 +568,14 @@ int chol_launch(float* H, int64_t d, int64_t ldh, float damp_rel, float* U, int6
   float* X = cv.take<float>(size_t(d) * ld);
   float* T = cv.take<float>(size_t(std::max<int64_t>(1, chol_scratch(d))));
   float* pl = cv.take<float>(size_t(chol_planes(d)));
+  float* mx = cv.take<float>(size_t(chol_maxima(d)));
   float* cn = cv.take<float>(size_t(d));
   float* shift = cv.take<float>(1);
 
   KQ_TRY(launch("chol_diag_shift", diag_shift, dim3(1), dim3(1024), 0, s,
                 static_cast<const float*>(H), d, ldh, damp_rel, shift, info));
   KQ_TRY(launch("chol_add_diag", add_diag, dim3(unsigned(cdiv(d, 256))), dim3(256), 0, s, H, d,
-                ldh, static_cast<const float*>(shift), cn));
+                ldh, static_cast<const float*>(shift), cn, mx, chol_maxima(d)));
   const unsigned gx = unsigned(cdiv(d, 256) < 64 ? cdiv(d, 256) : 64);
   const bool v4 = d % 4 == 0 && ldh % 4 == 0 && ldu % 4 == 0 && aligned(H, 16) && aligned(U, 16);
   const unsigned gx4 = unsigned(cdiv(d, 1024) < 64 ? cdiv(d, 1024) : 64);
@@ -553,7 +585,7 @@ int chol_launch(float* H, int64_t d, int64_t ldh, float damp_rel, float* U, int6
   else
     KQ_TRY(launch("chol_reverse_copy", reverse_copy, dim3(gx, unsigned(d)), dim3(256), 0, s,
                   static_cast<const float*>(H), d, ldh, static_cast<const float*>(cn), M, ld));
-  KQ_TRY(chol_rec(Chol{M, X, pl, ld, d, info, s}, T, 0, d));
+  KQ_TRY(chol_rec(Chol{M, X, pl, ld, d, info, s}, T, mx, 0, d));
   if (v4)
     return launch("chol_reverse_out", reverse_out4, dim3(gx4, unsigned(d)), dim3(256), 0, s,
                   static_cast<const float*>(X), ld, d, static_cast<const float*>(cn), U, ldu);

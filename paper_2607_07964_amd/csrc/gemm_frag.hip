@@ -5,11 +5,12 @@
 //   bf16 planes: x = bf16(x) + bf16(x - bf16(x)), the dropped parts ~2^-16 of each product. The
 //     OBS trailing updates W += (-E) U (and, with the drift correction, + X P as a second K range
 //     of the same product).
-//   fp16 planes: 23 significant bits (what is left out is below 2^-23 of the value, the dropped
-//     product of the low parts of the same order), so the accumulation in fp32 dominates the
-//     error as it does in an fp32 GEMM. For values scaled into range: the large products of the
-//     factorisation (normalised to a unit diagonal) and of the drift correction (a power of two
-//     per row).
+//   fp16 planes: each row of an operand divided by a power of two of its own that brings its
+//     largest value into [2^14, 2^15) (plane_unit). 23 significant bits down to 2^-16 of that
+//     (what is left out is below 2^-23 of the value, the dropped product of the low parts of the
+//     same order), below it the row is good to 2^-39 of its largest value, so the accumulation in
+//     fp32 dominates the error as it does in an fp32 GEMM. For the large products of the
+//     factorisation and of the drift correction.
 // Kernel: a (64 WT) x (64 WT) tile per workgroup of 4 waves (WT = 4: 256 x 256, one workgroup per
 // CU; WT = 2: 128 x 128, two), each wave (32 WT) x (32 WT) in accumulators. K advances 16 at a
 // time through a ring of four LDS stages filled by global_load_lds (a wave loads one plane of one
@@ -33,6 +34,7 @@
 #include <utility>
 
 #include "kq_common.hpp"
+#include "kq_fwht.hpp"
 
 namespace kq {
 namespace {
@@ -43,6 +45,7 @@ typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
 #define KQ_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 
 template <int N>
@@ -82,33 +85,146 @@ __host__ __device__ inline int deal_blocks(int nw, int nd) {
   return 8 * ((nw + 7) / 8) * (8 * (nd / 8) + nd % 8);
 }
 
-// one 32 x 32 block of a tile at (m, n): C[m][n], or planes of D^T (row n, k = m: four
-// consecutive m a lane and register quad)
+// The power of two that divides mx (a largest absolute value) into [2^14, 2^15), the upper end of
+// fp16; 1 for none, and never below 2^-120 (its inverse has to be finite).
+__device__ __forceinline__ float plane_unit(float mx) {
+  const int e = int(__float_as_uint(mx) >> 23);  // (mx >= 0)
+  return mx > 0.f && e < 255 ? __uint_as_float(uint32_t(e > 21 ? e - 14 : 7) << 23) : 1.f;
+}
+
+// *p = max(*p, v) for v >= 0 (non-negative floats compare as their bits)
+__device__ __forceinline__ void raise(float* p, float v) {
+  atomicMax(reinterpret_cast<unsigned*>(p), __float_as_uint(v));
+}
+
+// Stores of a tile of fp16 planes: a wave brings 32 rows of its blocks into row order through LDS of its own (lw,
+// rows of S floats) and then takes them in a loop, four columns a lane. Bound by the code's own
+// way into the instruction cache, it being run once: with every value stored from its accumulator
+// the loop-free form of this (2900 instructions at WT = 2, 14000 at WT = 4) took longer.
+template <int WT>
+struct Stores {
+  static constexpr int S = 32 * WT + 8;      // (rows r and r + 4 in different banks)
+  static constexpr int LPR = 8 * WT;         // lanes per row
+  static constexpr int RPI = 64 / LPR;       // rows at a time
+};
+
+// Rows [m, m + 32), columns [n, n + 32 WT), with the units of the planes' rows (pu, qu, in LDS, from
+// the first row and column on); the rows' largest values go to rmax, this lane's columns' to cm.
+template <int WT>
+__device__ __forceinline__ void store_rows(const FragJob& J, const float* lw, int64_t m, int64_t n,
+                                           int lane, const float* pu, const float* qu,
+                                           float (&cm)[4]) {
+  using L = Stores<WT>;
+  const int c = 4 * (lane % L::LPR), sub = lane / L::LPR;
+  const int64_t gn = n + c;
+  const int left = int(J.N - gn < 4 ? (J.N > gn ? J.N - gn : 0) : 4);  // columns that exist
+  const int rows = int(J.M - m < 32 ? (J.M > m ? J.M - m : 0) : 32);
+  float4 q = *reinterpret_cast<const float4*>(qu + c);
+  q.x *= J.alpha, q.y *= J.alpha, q.z *= J.alpha, q.w *= J.alpha;
+  // (FRAG_UPPER: only columns past the row count for the maxima)
+  const int diag = J.flags & FRAG_UPPER ? int(m - gn) : -64;
+  const bool want = J.rmax || J.cmax;
+  auto value = [&](int row) {
+    float4 v = *reinterpret_cast<const float4*>(lw + row * L::S + c);
+    const float p = pu[row];
+    v.x = q.x * v.x * p, v.y = q.y * v.y * p, v.z = q.z * v.z * p, v.w = q.w * v.w * p;
+    return v;
+  };
+  auto largest = [&](int row, const float4& v, int cols) {  // (every lane comes here)
+    const int k = row < rows ? diag + row : 64;  // column k and those before do not count
+    const float a0 = cols > 0 && k < 0 ? fabsf(v.x) : 0.f;
+    const float a1 = cols > 1 && k < 1 ? fabsf(v.y) : 0.f;
+    const float a2 = cols > 2 && k < 2 ? fabsf(v.z) : 0.f;
+    const float a3 = cols > 3 && k < 3 ? fabsf(v.w) : 0.f;
+    cm[0] = fmaxf(cm[0], a0), cm[1] = fmaxf(cm[1], a1);
+    cm[2] = fmaxf(cm[2], a2), cm[3] = fmaxf(cm[3], a3);
+    float r = fmaxf(fmaxf(a0, a1), fmaxf(a2, a3));
+    r = fmaxf(r, dpp_mov<0xB1>(r));  // over each 16 lanes: within quads,
+    r = fmaxf(r, dpp_mov<0x4E>(r));
+    r = fmaxf(r, dpp_mov<0x141>(r));  // halves mirrored, rows mirrored
+    r = fmaxf(r, dpp_mov<0x140>(r));
+    if (J.rmax && (lane & 15) == 0 && row < rows) raise(J.rmax + m + row, r);
+  };
+  constexpr int U = 4;
+#pragma unroll 1
+  for (int i0 = 0; i0 < 32 / L::RPI; i0 += U) {
+    float4 old[U];
+    if (J.add) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int row = (i0 + u) * L::RPI + sub;
+        if (row < rows && left == 4)
+          old[u] = *reinterpret_cast<const float4*>(J.C + (m + row) * J.ldc + gn);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int row = (i0 + u) * L::RPI + sub;
+      float4 v = value(row);
+      if (J.add) v.x += old[u].x, v.y += old[u].y, v.z += old[u].z, v.w += old[u].w;
+      if (row < rows && left == 4)
+        *reinterpret_cast<float4*>(J.C + (m + row) * J.ldc + gn) = v;
+      if (want) largest(row, v, left == 4 ? 4 : 0);
+    }
+  }
+  if ((J.N & 3) && n + 32 * WT > J.N) {  // (uniform) the last one to three columns
+#pragma unroll 1
+    for (int i = 0; i < 32 / L::RPI; ++i) {
+      const int row = i * L::RPI + sub;
+      float4 v = value(row);
+      float* o = J.C + (m + row) * J.ldc + gn;
+      if (row < rows && left < 4) {
+        if (left > 0) v.x = *o = J.add ? *o + v.x : v.x;
+        if (left > 1) v.y = o[1] = J.add ? o[1] + v.y : v.y;
+        if (left > 2) v.z = o[2] = J.add ? o[2] + v.z : v.z;
+      }
+      if (want) largest(row, v, left < 4 ? left : 0);
+    }
+  }
+}
+
+// the rows of blocks one after another (an index sequence: a plain loop of this size is not
+// unrolled, and the accumulators would go through scratch)
+template <int WT, int... I>
+__device__ __forceinline__ void store_f16(std::integer_sequence<int, I...>, const FragJob& J,
+                                          const f32x16_t (&acc)[WT][WT], float* lw, int64_t m,
+                                          int64_t n, int lane, const float* pu, const float* qu) {
+  using L = Stores<WT>;
+  float cm[4] = {};
+  auto rows = [&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_wave_barrier();  // (LDS of one wave: its accesses are in order)
+    float* w = lw + 4 * (lane >> 5) * L::S + (lane & 31);
+#pragma unroll
+    for (int j = 0; j < WT; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) w[(8 * (r >> 2) + (r & 3)) * L::S + 32 * j] = acc[i][j][r];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    store_rows<WT>(J, lw, m + 32 * i, n, lane, pu + 32 * i, qu, cm);
+  };
+  (rows(std::integral_constant<int, I>{}), ...);
+  if (J.cmax) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float v = cm[k];
+#pragma unroll
+      for (int o = L::LPR; o < 64; o <<= 1) v = fmaxf(v, __shfl_xor(v, o));
+      const int64_t gn = n + 4 * (lane % L::LPR) + k;
+      if (lane < L::LPR && gn < J.N) raise(J.cmax + gn, v);
+    }
+  }
+}
+
+// one 32 x 32 block of a tile of bf16 planes at (m, n), straight from the accumulators: the
+// additions to C want many loads in flight
 __device__ __forceinline__ void store_block(const FragJob& J, const f32x16_t& acc, int64_t m,
                                             int64_t n, int lane) {
   const int64_t gm0 = m + 4 * (lane >> 5), gn = n + (lane & 31);
-  if (J.Oh) {
-    if (gn >= ((J.N + 31) & ~int64_t(31))) return;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int64_t gm = gm0 + 8 * q;
-      if (gm >= J.oks * 16) continue;
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = gm + e < J.M ? J.alpha * acc[4 * q + e] : 0.f;
-      uint32_t h[2], l[2];
-      split_f16(v[0], v[1], h[0], l[0]);
-      split_f16(v[2], v[3], h[1], l[1]);
-      const int64_t f = split_frag_index(gn, gm, J.oks);
-      *reinterpret_cast<uint2*>(J.Oh + f) = make_uint2(h[0], h[1]);
-      *reinterpret_cast<uint2*>(J.Ol + f) = make_uint2(l[0], l[1]);
-    }
-    return;
-  }
   if (gn >= J.N) return;
-  const float an = J.qunit ? J.alpha * J.qunit[gn] : J.alpha;
   float* c = J.C + gm0 * J.ldc + gn;
-  if (m + 32 <= J.M && !J.punit) {  // uniform: every row of the block exists
+  if (m + 32 <= J.M) {  // uniform: every row of the block exists
     float old[16];
     if (J.add) {
 #pragma unroll
@@ -116,26 +232,22 @@ __device__ __forceinline__ void store_block(const FragJob& J, const f32x16_t& ac
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-      c[(8 * (r >> 2) + (r & 3)) * J.ldc] = J.add ? old[r] + an * acc[r] : an * acc[r];
+      c[(8 * (r >> 2) + (r & 3)) * J.ldc] = J.add ? old[r] + J.alpha * acc[r] : J.alpha * acc[r];
     return;
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const int64_t gm = gm0 + 8 * (r >> 2) + (r & 3);
-    if (gm < J.M) {
+    if (gm0 + 8 * (r >> 2) + (r & 3) < J.M) {
       float* e = c + (8 * (r >> 2) + (r & 3)) * J.ldc;
-      const float x = J.punit ? an * acc[r] * J.punit[gm] : an * acc[r];
-      *e = J.add ? *e + x : x;
+      *e = J.add ? *e + J.alpha * acc[r] : J.alpha * acc[r];
     }
   }
 }
 
-// the blocks one after another (an index sequence: a plain loop of this size is not unrolled, and
-// the accumulators would go through scratch)
 template <int WT, int... I>
-__device__ __forceinline__ void store_all(std::integer_sequence<int, I...>, const FragJob& J,
-                                          const f32x16_t (&acc)[WT][WT], int64_t m, int64_t n,
-                                          int lane) {
+__device__ __forceinline__ void store_bf16(std::integer_sequence<int, I...>, const FragJob& J,
+                                           const f32x16_t (&acc)[WT][WT], int64_t m, int64_t n,
+                                           int lane) {
   (store_block(J, acc[I / WT][I % WT], m + 32 * (I / WT), n + 32 * (I % WT), lane), ...);
 }
 
@@ -144,6 +256,7 @@ __device__ __forceinline__ void frag_tile(const FragJob& J, const Tiles& T, int 
                                           uint32_t* lds) {
   constexpr int TM = 64 * WT, G = TM / 32, R = 4;
   constexpr int PLANE = G * 256, STAGE = 4 * PLANE;  // dwords
+  static_assert(4 * 32 * Stores<WT>::S + 2 * TM <= R * STAGE, "the stores' rows and units");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nw = T.by_n ? T.nt_n : T.nt_m, nd = T.by_n ? T.nt_m : T.nt_n;
@@ -178,7 +291,8 @@ __device__ __forceinline__ void frag_tile(const FragJob& J, const Tiles& T, int 
   if (J.flags & FRAG_P_UPPER) kbeg = kbeg > m0 ? kbeg : m0;            // P[m][k] = 0, k < m
   if (J.flags & FRAG_Q_UPPER) kbeg = kbeg > n0 ? kbeg : n0;            // Q[n][k] = 0, k < n
   const int n1 = kend > kbeg ? int((kend - kbeg + 15) / 16) : 0;
-  const int nst = n1 + int(J.K2 / 16);  // the second pair's K range follows the first's
+  // the second pair's K range follows the first's; there is a stage (see frag_launch)
+  const int nst = n1 + int(J.K2 / 16);
 
   // this wave loads one plane of one operand
   const bool isq = wave >= 2;
@@ -252,27 +366,52 @@ __device__ __forceinline__ void frag_tile(const FragJob& J, const Tiles& T, int 
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
-  if (nst > 0) {
+  // the largest values behind the units of the tile's rows, then its columns (for the stores)
+  const bool scaled = F16 && J.pmax;
+  float top[TM / 128] = {};
+  if (scaled) {
 #pragma unroll
-    for (int p = 0; p < R; ++p) issue(p, p);
-    wait_vm<2 * G>();
-    asm volatile("s_barrier" ::: "memory");
-    frags(0, 0);
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    int s = 0;
-    for (; s + R <= nst; s += R) {
-      body(std::integral_constant<int, 0>{}, s);
-      body(std::integral_constant<int, 1>{}, s + 1);
-      body(std::integral_constant<int, 2>{}, s + 2);
-      body(std::integral_constant<int, 3>{}, s + 3);
+    for (int i = 0; i < TM / 128; ++i) {
+      const int e = tid + 256 * i;
+      const int64_t m = m0 + e < J.M ? m0 + e : J.M - 1;
+      const int64_t n = n0 + e - TM < J.N ? n0 + e - TM : J.N - 1;
+      top[i] = *(e < TM ? J.pmax + m : J.qmax + n);
     }
-    if (s < nst) body(std::integral_constant<int, 0>{}, s);
-    if (s + 1 < nst) body(std::integral_constant<int, 1>{}, s + 1);
-    if (s + 2 < nst) body(std::integral_constant<int, 2>{}, s + 2);
-    wait_vm<0>();
   }
-  store_all<WT>(std::make_integer_sequence<int, WT * WT>{}, J, acc, m0 + wm * WT * 32,
-                n0 + wn * WT * 32, lane);
+#pragma unroll
+  for (int p = 0; p < R; ++p) issue(p, p);
+  wait_vm<2 * G>();
+  asm volatile("s_barrier" ::: "memory");
+  frags(0, 0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  int s = 0;
+  for (; s + R <= nst; s += R) {
+    body(std::integral_constant<int, 0>{}, s);
+    body(std::integral_constant<int, 1>{}, s + 1);
+    body(std::integral_constant<int, 2>{}, s + 2);
+    body(std::integral_constant<int, 3>{}, s + 3);
+  }
+  if (s < nst) body(std::integral_constant<int, 0>{}, s);
+  if (s + 1 < nst) body(std::integral_constant<int, 1>{}, s + 1);
+  if (s + 2 < nst) body(std::integral_constant<int, 2>{}, s + 2);
+  wait_vm<0>();
+  int el = threadIdx.x;
+  asm volatile("" : "+v"(el));  // (the stores' addresses are formed here, not held over the loop)
+  const int64_t mw = m0 + wm * WT * 32, nw0 = n0 + wn * WT * 32;
+  if constexpr (F16) {
+    asm volatile("s_barrier" ::: "memory");  // the ring is free: no wave's loads are on their way
+    float* const rows32 = reinterpret_cast<float*>(lds);
+    float* const units = rows32 + 4 * 32 * Stores<WT>::S;  // (in the ring: the compiler makes
+    // every read of an LDS array wait for the loads into it once the kernel has a second array)
+#pragma unroll
+    for (int i = 0; i < TM / 128; ++i) units[el + 256 * i] = scaled ? plane_unit(top[i]) : 1.f;
+    __syncthreads();
+    store_f16<WT>(std::make_integer_sequence<int, WT>{}, J, acc,
+                  rows32 + wave * 32 * Stores<WT>::S, mw, nw0, el & 63, units + wm * WT * 32,
+                  units + TM + wn * WT * 32);
+  } else {
+    store_bf16<WT>(std::make_integer_sequence<int, WT * WT>{}, J, acc, mw, nw0, el & 63);
+  }
 }
 
 // one or two independent products (the first one's workgroups first)
@@ -294,6 +433,102 @@ Tiles deal(const FragJob& J, int tm) {
   return t;
 }
 
+// the differences r - c of the elements (r, c) that count
+__device__ __forceinline__ void tri_range(int tri, int& lo, int& hi) {
+  lo = tri == TRI_LOWER ? 0 : -0x40000000;
+  hi = tri == TRI_UPPER ? 0 : tri == TRI_STRICT_UPPER ? -1 : 0x40000000;
+}
+
+// four values of row r from column c on (a whole vector, or what the row has left)
+__device__ __forceinline__ void load4(const float* p, int64_t c, int64_t cols, float (&x)[4]) {
+  if (c + 4 <= cols) {
+    const float4 v = *reinterpret_cast<const float4*>(p + c);
+    x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w;
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = c + k < cols ? p[c + k] : 0.f;
+  }
+}
+
+// Largest absolute values of the rows and columns: 32 x 256 tiles, a wave on 8 rows with all its
+// loads in flight, one atomic per row and column of a tile. (Values compare as their bits; of a
+// row with a NaN it is the NaN.)
+__global__ __launch_bounds__(256) void abs_max(AbsMaxJob j0, AbsMaxJob j1) {
+  constexpr int R = 8;
+  __shared__ uint32_t red[4][256];
+  const AbsMaxJob& J = blockIdx.z == 0 ? j0 : j1;
+  const int64_t r0 = int64_t(blockIdx.y) * 4 * R, c0 = int64_t(blockIdx.x) * 256;
+  if (r0 >= J.rows || c0 >= J.cols) return;
+  const bool upper = J.tri == TRI_UPPER || J.tri == TRI_STRICT_UPPER;
+  if (J.tri == TRI_LOWER && c0 > r0 + 4 * R - 1) return;
+  if (upper && r0 > c0 + 255) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t rw = r0 + R * wave;
+  const int left = int(J.rows - rw < R ? J.rows - rw : R);  // rows that exist (may be negative)
+  // (a ragged last tile: lanes at and past the edge take the last four columns, some of them twice)
+  const int64_t c = c0 + 4 * lane < J.cols - 4 ? c0 + 4 * lane : J.cols - 4;
+  const float* p = J.src + (left > 0 ? rw : J.rows - 1) * J.ld + c;
+  f32x4u_t x[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+    x[i] = *reinterpret_cast<const f32x4u_t*>(p + int64_t(i < left ? i : left > 0 ? left - 1 : 0) *
+                                                      J.ld);
+  uint32_t v[R][4], cm[4] = {};
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[i][k] = __float_as_uint(x[i][k]) & 0x7FFFFFFFu;
+  // the part that counts, where the tile is not all of it (uniform)
+  if (J.tri != TRI_FULL && (upper ? r0 + 4 * R > c0 : c0 + 256 > r0)) {
+    int lo, hi;
+    tri_range(J.tri, lo, hi);
+    const int d0 = int(rw - c);
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (d0 + i - k < lo || d0 + i - k > hi) v[i][k] = 0;
+  }
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    if (i >= left) v[i][0] = v[i][1] = v[i][2] = v[i][3] = 0;  // (uniform)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cm[k] = max(cm[k], v[i][k]);
+  }
+  if (J.rmax) {
+    // over the lanes: half of the rows change hands at each of three steps, then one row is left
+    uint32_t m[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) m[i] = max(max(v[i][0], v[i][1]), max(v[i][2], v[i][3]));
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1)
+#pragma unroll
+      for (int k = 0; k < o; ++k) {
+        const uint32_t keep = lane & o ? m[k + o] : m[k], give = lane & o ? m[k] : m[k + o];
+        m[k] = max(keep, uint32_t(__shfl_xor(int(give), o)));
+      }
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) m[0] = max(m[0], uint32_t(__shfl_xor(int(m[0]), o)));
+    if (lane < left && lane < R) atomicMax(reinterpret_cast<unsigned*>(J.rmax + rw + lane), m[0]);
+  }
+  if (J.cmax) {  // (uniform over the workgroup)
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (c + k >= c0) red[wave][c + k - c0] = cm[k];  // (the same value where taken twice)
+    __syncthreads();
+    if (c0 + tid < J.cols)
+      atomicMax(reinterpret_cast<unsigned*>(J.cmax + c0 + tid),
+                max(max(red[0][tid], red[1][tid]), max(red[2][tid], red[3][tid])));
+  }
+}
+
+__global__ void clear_floats(float* __restrict__ p, int64_t n) {
+  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
+       i += int64_t(gridDim.x) * blockDim.x)
+    p[i] = 0.f;
+}
+
 // planes of src (or of its transpose): 64 x 64 tiles through LDS, 16-byte loads and stores
 __global__ __launch_bounds__(256) void split_planes(SplitJob j0, SplitJob j1, SplitJob j2) {
   __shared__ float t[64][65];
@@ -305,41 +540,39 @@ __global__ __launch_bounds__(256) void split_planes(SplitJob j0, SplitJob j1, Sp
     return;
   }
   // whole 256 x 256 blocks of zeros are outside every tile's K range
-  if (J.tri == SPLIT_LOWER && c0 > (r0 | 255)) return;
-  if ((J.tri == SPLIT_UPPER || J.tri == SPLIT_STRICT_UPPER) && r0 > (c0 | 255)) return;
+  if (J.tri == TRI_LOWER && c0 > (r0 | 255)) return;
+  if ((J.tri == TRI_UPPER || J.tri == TRI_STRICT_UPPER) && r0 > (c0 | 255)) return;
   const int tid = threadIdx.x, q = (tid & 15) * 4, rr = tid >> 4;
+  int lo, hi;
+  tri_range(J.tri, lo, hi);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int64_t r = r0 + rr + 16 * i, c = c0 + q;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (r < J.rows && c < J.cols) v = *reinterpret_cast<const float4*>(J.src + r * J.ld + c);
-    // the factor of the plane values: a constant, or the inverse of the row's (column's) unit
-    const float fr = J.unit && !J.trans ? 1.f / J.unit[r < J.rows ? r : 0] : J.scale;
-    float x[4] = {v.x, v.y, v.z, v.w};
+    float x[4] = {};
+    if (r < J.rows) load4(J.src + r * J.ld, c, J.cols, x);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const bool in = r < J.rows && c + k < J.cols && !(J.tri == SPLIT_LOWER && c + k > r) &&
-                      !(J.tri == SPLIT_UPPER && c + k < r) &&
-                      !(J.tri == SPLIT_STRICT_UPPER && c + k <= r);
-      const float f = J.unit && J.trans ? 1.f / J.unit[c + k < J.cols ? c + k : 0] : fr;
-      t[rr + 16 * i][q + k] = in ? x[k] * f : 0.f;
+      const int d = int(r - c) - k;
+      t[rr + 16 * i][q + k] = d >= lo && d <= hi ? x[k] : 0.f;
     }
   }
   __syncthreads();
   const int64_t n0 = J.trans ? c0 : r0, k0 = J.trans ? r0 : c0;
-  const int64_t nrows = ((J.trans ? J.cols : J.rows) + 31) & ~int64_t(31);
+  const int64_t rows = J.trans ? J.cols : J.rows;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int e = tid + 256 * i, nn = (e & 31) + 32 * (e >> 8), kk = ((e >> 5) & 7) * 8;
-    if (n0 + nn >= nrows || k0 + kk >= J.ks * 16) continue;
+    const int64_t n = n0 + nn;
+    if (n >= ((rows + 31) & ~int64_t(31)) || k0 + kk >= J.ks * 16) continue;
+    const float inv = 1.f / plane_unit(J.max[n < rows ? n : rows - 1]);
     uint32_t h[4], l[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const float a = J.trans ? t[kk + 2 * c][nn] : t[nn][kk + 2 * c];
       const float b = J.trans ? t[kk + 2 * c + 1][nn] : t[nn][kk + 2 * c + 1];
-      split_f16(a, b, h[c], l[c]);
+      split_f16(a * inv, b * inv, h[c], l[c]);
     }
-    const int64_t f = split_frag_index(n0 + nn, k0 + kk, J.ks);
+    const int64_t f = split_frag_index(n, k0 + kk, J.ks);
     *reinterpret_cast<uint4*>(J.Oh + f) = make_uint4(h[0], h[1], h[2], h[3]);
     *reinterpret_cast<uint4*>(J.Ol + f) = make_uint4(l[0], l[1], l[2], l[3]);
   }
@@ -352,6 +585,10 @@ int frag_launch(const FragJob* jobs, int n, int tile, hipStream_t s, const char*
     const FragJob& J = a.j[i] = jobs[i];
     KQ_REQUIRE(J.K2 % 16 == 0 && (J.K2 == 0 || J.K % 16 == 0), KRONQ_ERR_INVALID_ARG,
                "gemm_frag: K ranges of a two-part product must be multiples of 16");
+    // every tile that is not skipped has a K range that is not empty
+    KQ_REQUIRE(J.M > 0 && J.N > 0 && J.K + J.K2 > 0 && (!(J.flags & FRAG_P_UPPER) || J.M <= J.K) &&
+                   (!(J.flags & FRAG_Q_UPPER) || J.N <= J.K),
+               KRONQ_ERR_INVALID_ARG, "gemm_frag: empty product");
     a.t[i] = deal(J, tile);
   }
   const dim3 grid(unsigned(a.t[0].blocks + a.t[1].blocks));
@@ -366,6 +603,20 @@ int gemm_frag_bf16(const FragJob& j, int tile, hipStream_t s, const char* name) 
 }
 int gemm_frag_f16(const FragJob* jobs, int n, int tile, hipStream_t s, const char* name) {
   return frag_launch<true>(jobs, n, tile, s, name);
+}
+
+int abs_max_launch(const AbsMaxJob* jobs, int n, hipStream_t s, const char* name) {
+  for (int i = 0; i < n; ++i)
+    KQ_REQUIRE(jobs[i].cols >= 4, KRONQ_ERR_INVALID_ARG, "abs_max: fewer than four columns");
+  const int64_t r = std::max(jobs[0].rows, jobs[n - 1].rows);
+  const int64_t c = std::max(jobs[0].cols, jobs[n - 1].cols);
+  return launch(name, abs_max, dim3(unsigned(cdiv(c, 256)), unsigned(cdiv(r, 32)), unsigned(n)),
+                dim3(256), 0, s, jobs[0], jobs[n - 1]);
+}
+
+int clear_launch(float* p, int64_t n, hipStream_t s, const char* name) {
+  const int64_t g = cdiv(n, 256);
+  return launch(name, clear_floats, dim3(unsigned(g < 256 ? g : 256)), dim3(256), 0, s, p, n);
 }
 
 int split_planes_launch(const SplitJob* jobs, int n, hipStream_t s, const char* name) {

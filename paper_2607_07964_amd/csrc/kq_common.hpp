@@ -195,8 +195,10 @@ enum FragFlags : int {
 };
 // D = alpha P Q^T (+ P2 Q2^T over K2): P [M x K] and Q [N x K] as planes (pks, qks: 16-k units per
 // 32-row group, the planes' rows padded to whole groups and K to whole units with zeros).
-// C[m][n] = D (or += D with add), times punit[m] qunit[n] when given; or, with Oh (fp16 planes
-// only), the planes of D^T: row n, k = m, oks units per group.
+// C[m][n] = D (or += D with add). Planes whose rows were divided by plane_unit of their largest
+// values (split_planes) have these in pmax and qmax, and C is multiplied by both units. rmax[m]
+// and cmax[n], when given, are raised to the largest |C| of the row and the column (with
+// FRAG_UPPER: of the part n > m).
 struct FragJob {
   const uint16_t *Ph, *Pl;
   int64_t pks;
@@ -210,26 +212,38 @@ struct FragJob {
   float* C;
   int64_t ldc;
   bool add;
-  const float *punit, *qunit;
-  uint16_t *Oh, *Ol;
-  int64_t oks;
+  const float *pmax, *qmax;
+  float *rmax, *cmax;
 };
 // tile: 256 or 128
 int gemm_frag_bf16(const FragJob& j, int tile, hipStream_t s, const char* name);
 // one or two independent products in one launch
 int gemm_frag_f16(const FragJob* jobs, int n, int tile, hipStream_t s, const char* name);
 
+// The part of a matrix that counts
+enum Tri : int { TRI_FULL = 0, TRI_LOWER, TRI_UPPER, TRI_STRICT_UPPER };
+// rmax[r] and cmax[c] (when given; zeros beforehand) raised to the largest absolute values of the
+// rows and columns of the fp32 matrix src (16-byte aligned rows)
+struct AbsMaxJob {
+  const float* src;
+  int64_t ld, rows, cols;
+  int tri;
+  float *rmax, *cmax;
+};
+// one or two matrices in one launch
+int abs_max_launch(const AbsMaxJob* jobs, int n, hipStream_t s, const char* name);
+// p[0, n) = 0
+int clear_launch(float* p, int64_t n, hipStream_t s, const char* name);
+
 // fp16 planes of the fp32 matrix src [rows x cols] (16-byte aligned rows), or of its transpose,
-// times scale, or divided by unit[row of the planes]; powers of two
-enum SplitTri : int { SPLIT_FULL = 0, SPLIT_LOWER, SPLIT_UPPER, SPLIT_STRICT_UPPER };
+// each row of the planes divided by plane_unit of its largest absolute value
 struct SplitJob {
   const float* src;
   int64_t ld, rows, cols;
-  int tri;     // the part of src that is read; zeros elsewhere (256 x 256 blocks of zeros are left
-               // out: a product of a triangular operand takes its FRAG_* flag)
+  int tri;     // zeros elsewhere (256 x 256 blocks of zeros are left out: a product of a
+               // triangular operand takes its FRAG_* flag)
   bool trans;
-  float scale;
-  const float* unit;
+  const float* max;  // one per row of the planes
   uint16_t *Oh, *Ol;
   int64_t ks;  // 16-k units per 32-row group of the planes
 };

@@ -7,6 +7,7 @@ import oracle as O
 import synth
 from gpu_util import DEV, note, rel_frob, rot_device, rot_oracle, to_np
 from paper_2607_07964_amd import kronq as K
+from test_plane_products import PLANE_TOL
 
 pytestmark = pytest.mark.gpu
 
@@ -173,6 +174,11 @@ def test_sweep_trailing_products(d_out, d_in, group, drift):
 
 
 # ------------------------------------------------------------------ factor: products on planes
+def _split_at(d):
+    """Columns of the first part of an order-d node, which starts at the last column."""
+    return -(-d // 128) // 2 * 128
+
+
 def _factor(H, damp=0.01):
     d = H.shape[0]
     Hd = torch.from_numpy(np.ascontiguousarray(H, dtype=np.float32)).to(DEV)
@@ -198,9 +204,75 @@ def test_factor_planes(d, graded):
     assert info == 0 and np.array_equal(U, np.triu(U))
     H64 = H.astype(np.float64) / s[:, None] / s[None, :]
     ref = O.inverse_cholesky_factor(H64 if graded else O.damp(H64))
-    # fp32 rounding of d-term sums, amplified by the condition number of the normalised matrix
-    cond = np.linalg.cond(H64 if graded else O.damp(H64))
-    assert rel_frob(U * s[None, :], ref) < 4 * 2.0 ** -24 * np.sqrt(d) * cond
+    # (test_plane_products.py: what these products leave, and that a lost low plane is 40 times it)
+    got = U * s[None, :]
+    r = d - _split_at(d)
+    assert rel_frob(got, ref) < PLANE_TOL
+    assert rel_frob(got[:r, r:], ref[:r, r:]) < PLANE_TOL
+
+
+# two parts that hardly depend on each other: the block of U between them is small beside the
+# diagonal, and as accurate as the rest
+@pytest.mark.parametrize("sigma", [2e-3, 1e-4, 1e-6])
+def test_factor_planes_weak_coupling(sigma):
+    d = 1536
+    rng = np.random.default_rng(3)
+    A = np.triu(rng.standard_normal((d, d)) * sigma, 1)
+    H = (np.eye(d) + A + A.T).astype(np.float32)
+    note(f"factor weak coupling {sigma}")
+    U, info = _factor(H, 0.0)
+    ref = O.inverse_cholesky_factor(H.astype(np.float64))
+    r = d - _split_at(d)
+    assert info == 0 and rel_frob(U, ref) < PLANE_TOL
+    assert rel_frob(U[:r, r:], ref[:r, r:]) < PLANE_TOL
+
+
+# Three channels [[1, 1, 1/2], [1, 1 + 2^-22, 1/2 + 2^-12], [1/2, 1/2 + 2^-12, 1/2 + 2^-22]] in an
+# identity, damp 0: every step of the elimination is exact in fp32 (pivots 1, 2^-22, 2^-22) and the
+# inverse factor has entries up to 2^21. In either half of the two parts, and in both.
+@pytest.mark.parametrize("at", [(10, 200, 700), (800, 1000, 1500), (10, 900, 1400),
+                                (10, 700, 1400)])
+def test_factor_planes_wide_inverse(at):
+    d = 1536
+    trio = np.array([[1, 1, 0.5], [1, 1 + 2.0 ** -22, 0.5 + 2.0 ** -12],
+                     [0.5, 0.5 + 2.0 ** -12, 0.5 + 2.0 ** -22]])
+    idx = d - 1 - np.array(at)  # (the factorisation runs from the last column to the first)
+    H = np.eye(d, dtype=np.float32)
+    H[np.ix_(idx, idx)] = trio
+    assert np.array_equal(H[np.ix_(idx, idx)].astype(np.float64), trio)
+    L = np.linalg.cholesky(trio)
+    X = np.zeros((3, 3))
+    for j in range(3):  # L X = I by forward substitution
+        for i in range(j, 3):
+            X[i, j] = ((i == j) - L[i, :i] @ X[:i, j]) / L[i, i]
+    ref = np.eye(d)
+    ref[np.ix_(idx, idx)] = X
+    note(f"factor wide inverse {at}")
+    U, info = _factor(H, 0.0)
+    assert info == 0 and np.abs(X).max() >= 2.0 ** 21
+    np.testing.assert_allclose(U, ref, rtol=1e-6, atol=0)
+
+
+def test_factor_planes_ragged_256_tiles():
+    """An order whose large products all take 256-edge tiles, with ragged last rows (its parts are
+    5760 and 5740): U H~ U^T is the identity."""
+    d = 11500
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    X = torch.randn(2 * d, d, generator=g, device=DEV)
+    H = X.T @ X / (2 * d)
+    del X
+    U = torch.full((d, d), float("nan"), device=DEV)
+    note(f"factor 256 tiles d={d}")
+    info = K.kronq_cholesky_inv(H, U, 0.01)  # (H becomes H~)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    U64 = U.double()
+    R = U64 @ H.double() @ U64.T
+    R.diagonal().sub_(1.0)
+    # a relative error e of U leaves 2 e |U| |H~| |U| at most, a low plane lost 100 times it
+    assert float(R.norm() / d ** 0.5) < 4 * PLANE_TOL and float(R.abs().max()) < 4 * PLANE_TOL
+    assert not torch.tril(U, -1).any()
 
 
 @pytest.mark.parametrize("d,bad", [(1536, 3), (1536, 1500), (2304, 900)])
@@ -235,15 +307,36 @@ def test_gptaq_planes(d, pad):
     D64, U64 = np.triu(D.astype(np.float64), 1), U.astype(np.float64)
     T = np.triu(D64 @ U64.T, 1)
     ref = 0.5 * T @ U64
-    # two d-term fp32 sums of operands of 22 bits (2^-22 each) of the terms' sizes; an operand
-    # below 2^-28 of its row's largest value (D, T, U's rows and columns) is good to 2^-38 of that
+    # two d-term fp32 sums of operands of 23 bits (2^-23 each) of the terms' sizes; an operand below
+    # 2^-16 of its row's largest value (D, T, U's rows and columns) is good to 2^-39 of that
     top = lambda a, axis: np.abs(a).max(axis, keepdims=True)
     size = np.triu(np.abs(D64) @ np.abs(U64).T, 1)
-    eT = (d + 12) * 2.0 ** -24 * size + d * 2.0 ** -37 * top(D64, 1) * top(U64, 1).T
-    eP = (d + 12) * 2.0 ** -24 * size @ np.abs(U64) + d * 2.0 ** -37 * top(T, 1) * top(U64, 0)
+    eT = (d + 12) * 2.0 ** -24 * size + d * 2.0 ** -38 * top(D64, 1) * top(U64, 1).T
+    eP = (d + 12) * 2.0 ** -24 * size @ np.abs(U64) + d * 2.0 ** -38 * top(T, 1) * top(U64, 0)
     assert np.all(np.abs(p - ref) <= 0.5 * np.triu(np.triu(eT, 1) @ np.abs(U64) + eP, 1))
     if pad:
         assert torch.isnan(dev[2][:, d:]).all()
+
+
+def test_gptaq_planes_ragged_256_tiles():
+    """The 256-edge tiles of both products, with a ragged last tile; sampled rows in 64 bits."""
+    d = 8004
+    g = torch.Generator(device=DEV)
+    g.manual_seed(2)
+    U = torch.randn(d, d, generator=g, device=DEV).mul_(d ** -0.5).triu_()
+    U.diagonal().add_(1.0)
+    D = torch.randn(d, d, generator=g, device=DEV)
+    P = torch.full((d, d), float("nan"), device=DEV)
+    note(f"gptaq 256 tiles d={d}")
+    K.kronq_gptaq_correction(D, U, P, 1.0)
+    torch.cuda.synchronize()
+    assert not torch.tril(P).any()
+    rows = torch.tensor([0, 1, 255, 256, 4095, 5000, 7679, 7680, 7935, 7936, 8001, 8002], device=DEV)
+    keep = torch.arange(d, device=DEV)[None, :] > rows[:, None]
+    T = (D[rows].double() @ U.double().T) * keep
+    ref = (T @ U.double()) * keep
+    err = (P[rows].double() - ref).norm(dim=1) / ref.norm(dim=1)
+    assert float(err.max()) < PLANE_TOL  # (a low plane lost: 2e-4)
 
 
 # ---------------------------------------------------------------- rotations with a fused H_8
