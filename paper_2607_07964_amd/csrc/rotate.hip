@@ -687,7 +687,7 @@ int launch_row_pass(const void* src, int dtype, int64_t lds_, float* dst, int64_
 
 int launch_col_step(const float* src, int64_t lds_, float* dst, int64_t ldd, int64_t rows,
                     int64_t cols, int64_t L, int64_t n_lo, int kind, const float* q28,
-                    bool q_trans, hipStream_t s) {
+                    bool q_trans, hipStream_t s, float norm = 0.f) {
   // strips of CW columns: 28-point mix 256 (one column per thread), FWHT 64 up to L = 256
   // and 32 beyond (L = 1024: 1024 x 36 floats + the 28 x 28 factor = 150 KB of LDS, one
   // workgroup per CU, so beyond L = 256 the workgroup has 1024 threads to keep enough loads in
@@ -699,7 +699,7 @@ int launch_col_step(const float* src, int64_t lds_, float* dst, int64_t ldd, int
   while (kind == 0 && CW > 16 && n_groups * cdiv(cols, CW) * 2 <= device_cus()) CW /= 2;
   const int64_t strips = cdiv(cols, CW);
   const size_t shmem = (size_t(L) * (CW + 4) + 28 * 28) * sizeof(float);
-  const float norm = kind == 0 ? float(1.0 / std::sqrt(double(L))) : 1.f;
+  if (norm == 0.f) norm = kind == 0 ? float(1.0 / std::sqrt(double(L))) : 1.f;
   const char* name = kind == 0 ? "fwht_col" : "mix28_col";
   const dim3 grid(unsigned(n_groups * strips));
   if (kind == 0 && L > 256)
@@ -748,10 +748,17 @@ bool fuse8(const RotDim& rrows, const RotDim& rn, int64_t n) {
          (n == 2048 || n == 4096);
 }
 
+// The factor 1 / sqrt(rows n) of the two passes: the row pass takes a power of two, the column pass
+// the rest, so that it is exact (or rounded once) whatever the split of the stages.
+float row8_norm(int64_t n) { return n == 4096 ? 0x1p-8f : 0x1p-7f; }
+float col8_norm(int64_t rows, int64_t n) {
+  return float(1.0 / std::sqrt(double(rows) * double(n)) / double(row8_norm(n)));
+}
+
 int launch_row_pass8(const void* src, int dtype, int64_t lds_, float* dst, int64_t ldd,
                      int64_t rows, int64_t n, const float* pre_row, const float* pre_col,
                      const float* post_row, const float* post_col, hipStream_t s) {
-  const float norm = float(1.0 / std::sqrt(8.0 * double(n)));
+  const float norm = row8_norm(n);
   const dim3 grid(unsigned(rows / (n == 4096 ? 8 : 16))), block(512);
   if (dtype == KRONQ_BF16)
     return launch("rot_row_pass", n == 4096 ? row_pass8<uint16_t, 8> : row_pass8<uint16_t, 4>,
@@ -770,7 +777,8 @@ int two_sided(const void* src, int dtype, int64_t lds_, float* dst, int64_t ldd,
   if (rot_n && rot_rows && fuse8(rrows, rn, n)) {
     KQ_TRY(launch_row_pass8(src, dtype, lds_, dst, ldd, rows, n, pre_row, pre_col, nullptr,
                             nullptr, s));
-    return launch_col_step(dst, ldd, dst, ldd, rows, n, rows / 8, 8, 0, nullptr, false, s);
+    return launch_col_step(dst, ldd, dst, ldd, rows, n, rows / 8, 8, 0, nullptr, false, s,
+                           col8_norm(rows, n));
   }
   KQ_TRY(launch_row_pass(src, dtype, lds_, dst, ldd, rows, n, pre_row, pre_col, nullptr, nullptr,
                          rot_n, rn, q28_n, false, s, "rot_row_pass"));
@@ -852,7 +860,8 @@ int rotate_launch(const void* W_in, int w_dtype, int64_t ldw_in, float* W, int64
     const float* src = static_cast<const float*>(W_in);
     int64_t lsrc = ldw_in;
     if (rot_in && rot_out && fuse8(ro, ri, d_in)) {
-      KQ_TRY(launch_col_step(src, lsrc, W, ldw, d_out, d_in, d_out / 8, 8, 0, nullptr, true, s));
+      KQ_TRY(launch_col_step(src, lsrc, W, ldw, d_out, d_in, d_out / 8, 8, 0, nullptr, true, s,
+                             col8_norm(d_out, d_in)));
       return launch_row_pass8(W, KRONQ_FP32, ldw, W, ldw, d_out, d_in, nullptr, nullptr, mw_out,
                               mw_in, s);
     }

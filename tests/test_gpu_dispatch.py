@@ -377,3 +377,28 @@ def test_rotate_fused_rows(d_out, d_in, bf16):
         assert rel_frob(to_np(got)[np.ix_(idx, idx)], t @ h.numpy().astype(np.float64) @ t.T) < tol
     assert rel_frob(to_np(back), w64) < tol
     assert torch.isnan(wide[:, d_in:]).all()
+
+
+# Whole numbers without rescaling: every sum is exact in fp32, and so is the factor 1 / sqrt(d_out
+# d_in) where it is a power of two, however the passes share it; the results have no error at all.
+@pytest.mark.parametrize("d_out,d_in", [(4096, 4096), (2048, 2048), (8192, 2048), (1024, 4096)])
+def test_rotate_exact_norm(d_out, d_in):
+    rng = np.random.default_rng(d_out + d_in)
+    w = rng.integers(-7, 9, size=(d_out, d_in)).astype(np.float32)
+    ri, ro = (synth.rotation_params(n, 5, s) for n, s in ((d_in, "in"), (d_out, "out")))
+    rin, rout = rot_device(ri), rot_device(ro)
+    one_in, one_out = torch.ones(d_in, device=DEV), torch.ones(d_out, device=DEV)
+    HX, W = torch.eye(d_in, device=DEV), torch.empty(d_out, d_in, device=DEV)
+    note(f"rotate exact norm {d_out}x{d_in}")
+    wd = torch.from_numpy(w).to(DEV)
+    flags = K.ROT_IN | K.ROT_OUT
+    K.kronq_rotate(wd, W, HX, None, rin.sign, rout.sign, rin.q28, rout.q28, one_in, one_out, flags)
+    back = torch.empty_like(W)
+    K.kronq_rotate(wd, back, None, None, rin.sign, rout.sign, rin.q28, rout.q28, one_in, one_out,
+                   flags | K.INVERSE)
+    torch.cuda.synchronize()
+    rows, cols = (np.sort(rng.choice(n, 24, replace=False)) for n in (d_out, d_in))
+    V, U = (np.rint(O.rht_matrix(n, *rot_oracle(r)) * np.sqrt(n)) for n, r in ((d_in, ri), (d_out, ro)))
+    w64, norm = w.astype(np.float64), np.sqrt(d_out * d_in)
+    assert np.array_equal(to_np(W)[np.ix_(rows, cols)], U[rows] @ w64 @ V[cols].T / norm)
+    assert np.array_equal(to_np(back)[np.ix_(rows, cols)], U[:, rows].T @ w64 @ V[:, cols] / norm)
