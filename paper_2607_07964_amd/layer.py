@@ -165,8 +165,10 @@ def solve(st: LayerState, bits: int, damp: float = 0.01, alpha: Optional[float] 
 #   4096 x 4096, 262144 tokens: 128 CUs 10.28, 160 9.48, 192 9.18, 208 9.77, uncapped 11.16, on one
 #     stream 11.95;  65536 tokens: 32 6.43, 64 4.38, 96 4.35, 128 4.50, 192 4.65, one stream 5.48
 #   4096 x 14336 (d_out x d_in): 64 65.28, 96 64.49, 128 64.94, 192 67.36, one stream 66.33
-#   14336 x 4096: 192 57.48, 224 55.14, 240 56.49, uncapped 57.77, one stream 56.35
-#   28672 x 8192, 131072 tokens: 192 127.63, 224 122.26, 248 124.26, uncapped 122.59
+#   14336 x 4096, 65536 tokens: 224 17.3, one stream 19.5; 14336 x 8192, 131072: 192 40.9, 224 40.2,
+#     one stream 44.5
+#   28672 x 8192, 131072 tokens: 224 121.9, 248 123.9, one stream 124.0
+# (from 15 times on: one stream, see _one_stream)
 COV_SHARE_MIN, COV_SHARE_MAX, COV_SHARE_LONG = 0.375, 0.75, 0.875
 # The drift statistic, first on the second stream (before H_G), holds 13/16 of the chip and
 # leaves the rest to the H_X transform and the factorisation's first leaves and products: at
@@ -193,10 +195,22 @@ def _times(n_tokens: int, d_out: int, d_in: int):
 def _cov_late(n_tokens: int, d_out: int, d_in: int) -> bool:
     """Whether the H_G covariance waits for the transforms of H_X and W. A long H_G is slowed for
     its whole time when it starts beside them: its workgroups then no longer read the same tokens
-    at the same time through an XCD's cache (28672 x 8192, 262144 tokens: 225.9 ms per layer after
-    the transforms, 236.5 beside them; 14336 x 4096 56.9 and 56.8). A short one starts at once."""
+    at the same time through an XCD's cache (28672 x 8192, 131072 tokens: 121.9 ms per layer after
+    the transforms, 126.2 beside them; 14336 x 4096, 262144: 57.3 and 57.5). A short one starts at
+    once."""
     t_cov, t_solve = _times(n_tokens, d_out, d_in)
     return t_cov > 4.0 * t_solve
+
+
+def _one_stream(n_tokens: int, d_out: int, d_in: int) -> bool:
+    """Whether the layer runs on one stream: beside an H_G that outlasts the other side more than
+    15 times there is less to gain than the eighth of the chip costs it.
+    ms per layer on one stream and on two (both alternating on one machine), by that ratio:
+    28672 x 8192, 131072 tokens (7.9) 114.8 and 112.5, 196608 (11.9) 160.1 and 160.3, 262144 (15.8)
+    203.6 and 205.9; 14336 x 4096 (14.6) 53.0 and 52.6; 14336 x 3584 (17.4) 51.7 and 54.2; 28672 x
+    4096 (23.6) 185.3 and 191.7; 14336 x 2048 (34) 47.9 and 49.1; 8192 x 1024 (25) 16.6 and 16.4."""
+    t_cov, t_solve = _times(n_tokens, d_out, d_in)
+    return t_cov > 15.0 * t_solve
 
 
 def _cov_cus(device, n_tokens: int, d_out: int, d_in: int) -> int:
@@ -211,7 +225,8 @@ def _cov_cus(device, n_tokens: int, d_out: int, d_in: int) -> int:
 def schedule(st: LayerState, n_tokens: int, overlap: bool = True,
              cov_cus: Optional[int] = None) -> str:
     """The schedule quantize_layer takes for this layer."""
-    if not overlap:
+    if not overlap or (cov_cus is None and st.D is None
+                       and _one_stream(n_tokens, st.d_out, st.d_in)):
         return "one stream"
     if cov_cus is None:
         cov_cus = _cov_cus(st.HG.device, n_tokens, st.d_out, st.d_in)
@@ -239,7 +254,8 @@ def quantize_layer(st: LayerState, X, G, W0, rin: RotParams, rout: RotParams, bi
 
     S_G needs only diag(H_G), which one read of G gives (kronq_cov_diag), so W is rescaled and
     rotated without waiting for the H_G covariance, and the sweep never waits for it either.
-    With ``overlap`` diag(H_G) and H_X come first, then the work is split over two streams: the
+    With ``overlap`` (unless ``cov_cus`` is None and H_G outlasts all else, see _one_stream)
+    diag(H_G) and H_X come first, then the work is split over two streams: the
     current stream rotates H_X, transforms W, factors H_X and runs the sweep; the second stream
     takes (the drift statistic and) the H_G covariance on ``cov_cus`` CUs (None: the policy of
     _cov_cus; 0: no cap) as soon as H_X is formed (a long one after W's transform, see _cov_late),
@@ -250,6 +266,7 @@ def quantize_layer(st: LayerState, X, G, W0, rin: RotParams, rout: RotParams, bi
     if drift and st.D is None:
         raise ValueError("the drift correction needs LayerState.allocate(..., drift=True)")
     if overlap and cov_cus is None:
+        overlap = drift or not _one_stream(G.shape[0], st.d_out, st.d_in)
         cov_cus = _cov_cus(st.HG.device, G.shape[0], st.d_out, st.d_in)
     if not overlap:
         K.kronq_cov_diag(G, st.hgd, st.ws_diag)
