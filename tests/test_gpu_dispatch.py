@@ -57,8 +57,7 @@ def test_online_gemv_widths(d_out, d_in, group, batch, bits):
     x[:, ::97] *= 50.0  # outliers set their group's exponent
     note(f"gemv {d_out}x{d_in} group={group} batch={batch} bits={bits}")
     packed = K.kronq_pack_codes(torch.from_numpy(codes).to(DEV), bits)
-    if d_in * bits // 32 % 4:
-        pytest.skip("rows of packed codes are not 16-byte aligned")
+    assert d_in * bits // 32 % 4 == 0  # whole 16-byte units, as the call asks
     y = K.kronq_online_matvec(packed, torch.from_numpy(scales).to(DEV),
                               torch.from_numpy(zeros).to(DEV), bits, group, d_in, None, None, None,
                               None, torch.from_numpy(x).to(DEV), flags=0)
@@ -377,6 +376,40 @@ def test_rotate_fused_rows(d_out, d_in, bf16):
         assert rel_frob(to_np(got)[np.ix_(idx, idx)], t @ h.numpy().astype(np.float64) @ t.T) < tol
     assert rel_frob(to_np(back), w64) < tol
     assert torch.isnan(wide[:, d_in:]).all()
+
+
+# ------------------------------------------- rotations whose lane stages end before 512 elements
+# rows of 28 * 128 and 28 * 256 (seven and eight stages in the lanes), one and several rows a
+# workgroup, W as bf16 and fp32, both directions
+@pytest.mark.parametrize("d_out,d_in,bf16", [(64, 3584, True), (2048, 3584, False), (256, 7168, True),
+                                             (3584, 128, False)])
+def test_rotate_short_lane_stages(d_out, d_in, bf16):
+    rng = np.random.default_rng(d_out + d_in)
+    w = torch.from_numpy(rng.standard_normal((d_out, d_in)).astype(np.float32))
+    w = w.to(torch.bfloat16) if bf16 else w
+    ri, ro = (synth.rotation_params(n, 5, s) for n, s in ((d_in, "in"), (d_out, "out")))
+    rin, rout = rot_device(ri), rot_device(ro)
+    X = rng.standard_normal((32, max(d_in, d_out)))
+    hx, hg = ((X[:, :n].T @ X[:, :n] / 32 + np.eye(n)).astype(np.float32) for n in (d_in, d_out))
+    W, HX, HG = torch.empty(d_out, d_in, device=DEV), *(torch.from_numpy(h).to(DEV) for h in (hx, hg))
+    sx, sg = torch.empty(d_in, device=DEV), torch.empty(d_out, device=DEV)
+    note(f"rotate short lane stages {d_out}x{d_in} bf16={bf16}")
+    K.kronq_rotate(w.to(DEV), W, HX, HG, rin.sign, rout.sign, rin.q28, rout.q28, sx, sg, K.BIIP)
+    back = torch.empty(d_out, d_in, device=DEV)
+    K.kronq_rotate(W, back, None, None, rin.sign, rout.sign, rin.q28, rout.q28, sx, sg,
+                   K.BIIP | K.INVERSE)
+    torch.cuda.synchronize()
+    # as above; the 28-point mix adds the rounding of 28-term sums
+    tol = 4 * (np.log2(d_out) + np.log2(d_in) + 8 + 2 * np.sqrt(28)) * 2.0 ** -24
+    rows, cols = (np.sort(rng.choice(n, 24, replace=False)) for n in (d_out, d_in))
+    sx64, sg64 = to_np(sx).astype(np.float64), to_np(sg).astype(np.float64)
+    V = O.rht_rows(d_in, *rot_oracle(ri), cols)
+    U = O.rht_rows(d_out, *rot_oracle(ro), rows)
+    w64 = w.float().numpy().astype(np.float64)
+    assert rel_frob(to_np(W)[np.ix_(rows, cols)], (U * sg64) @ w64 @ (V * sx64).T) < tol
+    for got, h, t, idx in ((HX, hx, V / sx64, cols), (HG, hg, U / sg64, rows)):
+        assert rel_frob(to_np(got)[np.ix_(idx, idx)], t @ h.astype(np.float64) @ t.T) < tol
+    assert rel_frob(to_np(back), w64) < tol
 
 
 # Whole numbers without rescaling: every sum is exact in fp32, and so is the factor 1 / sqrt(d_out
