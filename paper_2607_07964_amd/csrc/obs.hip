@@ -471,7 +471,8 @@ struct SweepArgs {
 
 // One lazy group for RG x 32 rows per workgroup, four waves per 32 rows. RG = 2 halves the LDS a
 // row takes (the U block is shared), so that a CU holds 128 rows: taken when RG = 1 would need
-// more than two workgroups a CU (see obs_launch).
+// more than two workgroups a CU (see obs_launch). (RG = 2 without P has 128 registers: five values
+// go to scratch once a launch and come back once a block, none in the quads.)
 template <bool DRIFT, int RG>
 __global__ __launch_bounds__(256 * RG, DRIFT ? RG : 2 * RG) void obs_sweep(SweepArgs g) {
   __shared__ __attribute__((aligned(16))) float ub[UTILES * 1024];
@@ -599,15 +600,13 @@ int lazy_blocks(int64_t d_in, int group) {
 
 int obs_group_ok(int64_t d_in, int group) { return lazy_blocks(d_in, group); }
 
-// the split errors (and pre-quantisation values) and the split U^T (and P^T), in fragment order;
-// without P never less than four planes of U's size, which a caller may count on
+// the split errors (and pre-quantisation values) and the split U^T (and P^T), in fragment order
 size_t obs_ws_bytes(int64_t d_out, int64_t d_in, bool drift) {
   if (d_out <= 0 || d_in <= 0) return 0;
   const size_t rows = size_t(cdiv(d_out, 32) * 32);
   const size_t one = 2 * align256(rows * size_t(d_in) * sizeof(uint16_t)) +
                      2 * align256(size_t(d_in) * size_t(d_in) * sizeof(uint16_t));
-  const size_t floor = drift ? 0 : 4 * align256(size_t(d_in) * size_t(d_in) * sizeof(uint16_t));
-  return std::max((drift ? 2 : 1) * one, floor) + 256;
+  return (drift ? 2 : 1) * one + 256;
 }
 
 int obs_launch(float* W, int64_t d_out, int64_t d_in, int64_t ldw, const float* U, int64_t ldu,
@@ -637,9 +636,9 @@ int obs_launch(float* W, int64_t d_out, int64_t d_in, int64_t ldw, const float* 
     a.Pfh = pfh, a.Pfl = pfl;
   }
   // 32 rows a workgroup while the chip holds all of them (two workgroups per CU, one with the
-  // drift correction's P block), else 64. Measured (whole solve): 4096 x 4096 757 us with 32
-  // rows, 910 with 64; 14336 x 4096 1592 and 1662; 28672 x 8192 10.57 and 10.32 ms; with P 4096 x
-  // 4096 1.98 and 2.15 ms, 14336 x 4096 3.74 and 3.32 ms.
+  // drift correction's P block), else 64. Measured (whole solve, 32 rows and 64): 4096 x 4096 694
+  // and 835 us; 4096 x 14336 4.23 and 4.65 ms; 14336 x 4096 1414 and 1421 us; 28672 x 8192 7.76 and
+  // 7.22 ms; with P 4096 x 4096 1159 and 1372 us, 14336 x 4096 2720 and 2285 us.
   a.cus = device_cus();
   const int64_t g32 = cdiv(d_out, 32);
   const int rg = g32 <= int64_t(a.cus) * (drift ? 1 : 2) ? 1 : 2;
