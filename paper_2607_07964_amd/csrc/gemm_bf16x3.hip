@@ -6,8 +6,8 @@
 // a second product W_blk P[blk, rest] in the same pass. Both operands are kept in MFMA-fragment
 // order (split_frag_index): the sweep writes its errors (negated) that way, split_transpose the
 // rows of U^T.
-//   * TM x TM output tile per workgroup (TM = 128 or 64), 4 waves in a 2 x 2 grid, each wave
-//     (TM/2) x (TM/2) = up to 2 x 2 MFMA blocks of 32 x 32 with fp32 accumulators.
+//   * 64 x 64 output tile per workgroup, 4 waves in a 2 x 2 grid, each wave one 32 x 32 MFMA block
+//     with fp32 accumulators: for outputs too small for the 128 x 128 tiles of gemm_frag.hip.
 //   * K advances 32 at a time, first over the K of the first pair, then over the second's,
 //     through two LDS stages (one barrier per stage): the next stage is fetched into registers
 //     during the current stage's MFMAs and written to the other buffer. LDS rows are padded to 80
@@ -28,69 +28,48 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int BK = 32;      // K per stage
 constexpr int RS = 40;      // LDS row stride in bf16 (32 + 8 pad = 80 bytes)
 
-template <int TM>
+constexpr int TM = 64;
+
 __global__ __launch_bounds__(256, 2) void gemm3_frag_add(int64_t M, int64_t N, FragPair p1,
                                                          FragPair p2, float* __restrict__ C,
                                                          int64_t ldc) {
-  constexpr int NB = TM / 64;               // 32 x 32 blocks per wave edge (1 or 2)
-  constexpr int V = TM * BK / 8 / 256;      // 16-byte chunks of each array per thread per stage
   __shared__ __attribute__((aligned(16))) uint16_t sA[2][2][TM * RS], sB[2][2][TM * RS];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave & 1, wn = wave >> 1, l32 = lane & 31, lhi = lane >> 5;
   const int64_t m0 = int64_t(blockIdx.y) * TM, n0 = int64_t(blockIdx.x) * TM;
-  // this thread's 16-byte chunks: row r_v of the tile, k offset kc_v within the stage, 32
-  // consecutive threads on the 32 rows of a fragment (512 contiguous bytes)
-  int64_t ra[V], rb[V];
-  int kc[V], so[V];
-#pragma unroll
-  for (int v = 0; v < V; ++v) {
-    const int e = tid + 256 * v, r = (e >> 7) * 32 + (e & 31);
-    kc[v] = ((e >> 5) & 3) * 8;
-    ra[v] = m0 + r < M ? m0 + r : M - 1;
-    rb[v] = n0 + r < N ? n0 + r : N - 1;
-    so[v] = r * RS + kc[v];
-  }
-  u32x4_t rah[V], ral[V], rbh[V], rbl[V];
-  f32x16_t acc[NB][NB];
-#pragma unroll
-  for (int a = 0; a < NB; ++a)
-#pragma unroll
-    for (int b = 0; b < NB; ++b) acc[a][b] = f32x16_t{};
+  // this thread's 16-byte chunk of each array per stage: row r of the tile, k offset kc within the
+  // stage, 32 consecutive threads on the 32 rows of a fragment (512 contiguous bytes)
+  const int r = (tid >> 7) * 32 + (tid & 31), kc = ((tid >> 5) & 3) * 8, so = r * RS + kc;
+  const int64_t ra = m0 + r < M ? m0 + r : M - 1, rb = n0 + r < N ? n0 + r : N - 1;
+  u32x4_t rah, ral, rbh, rbl;
+  f32x16_t acc = {};
   // this lane's elements of the C tile (in the accumulator layout), requested first so that
   // their latency hides behind the whole K loop instead of ending the tile
-  float cin[NB][NB][16];
+  const int64_t gm0 = m0 + wm * 32 + 4 * lhi, gn = n0 + wn * 32 + l32;
+  float cin[16];
 #pragma unroll
-  for (int bi = 0; bi < NB; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < NB; ++bj)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t gm = m0 + wm * (TM / 2) + bi * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
-        const int64_t gn = n0 + wn * (TM / 2) + bj * 32 + l32;
-        cin[bi][bj][r] = (gm < M && gn < N) ? C[gm * ldc + gn] : 0.f;
-      }
+  for (int e = 0; e < 16; ++e) {
+    const int64_t gm = gm0 + 8 * (e >> 2) + (e & 3);
+    cin[e] = (gm < M && gn < N) ? C[gm * ldc + gn] : 0.f;
+  }
   const int n1 = int(p1.K / BK), nst = n1 + int(p2.K / BK);  // even: K is a multiple of 64
   // stage st of the concatenated K: the first pair for st < n1, else the second
   auto fetch = [&](int st) {
     const FragPair& p = st < n1 ? p1 : p2;
     const int64_t k0 = int64_t(st < n1 ? st : st - n1) * BK;
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-      const int64_t a = split_frag_index(ra[v], k0 + kc[v], p.aks);
-      const int64_t b = split_frag_index(rb[v], k0 + kc[v], p.bks);
-      rah[v] = *reinterpret_cast<const u32x4_t*>(p.Ah + a);
-      ral[v] = *reinterpret_cast<const u32x4_t*>(p.Al + a);
-      rbh[v] = *reinterpret_cast<const u32x4_t*>(p.Bh + b);
-      rbl[v] = *reinterpret_cast<const u32x4_t*>(p.Bl + b);
-    }
+    const int64_t a = split_frag_index(ra, k0 + kc, p.aks);
+    const int64_t b = split_frag_index(rb, k0 + kc, p.bks);
+    rah = *reinterpret_cast<const u32x4_t*>(p.Ah + a);
+    ral = *reinterpret_cast<const u32x4_t*>(p.Al + a);
+    rbh = *reinterpret_cast<const u32x4_t*>(p.Bh + b);
+    rbl = *reinterpret_cast<const u32x4_t*>(p.Bl + b);
   };
-#define KQ_STASH(b)                                                          \
-  _Pragma("unroll") for (int v = 0; v < V; ++v) {                            \
-    *reinterpret_cast<u32x4_t*>(&sA[b][0][so[v]]) = rah[v];                    \
-    *reinterpret_cast<u32x4_t*>(&sA[b][1][so[v]]) = ral[v];                    \
-    *reinterpret_cast<u32x4_t*>(&sB[b][0][so[v]]) = rbh[v];                    \
-    *reinterpret_cast<u32x4_t*>(&sB[b][1][so[v]]) = rbl[v];                    \
-  }
+  auto stash = [&](int b) {
+    *reinterpret_cast<u32x4_t*>(&sA[b][0][so]) = rah;
+    *reinterpret_cast<u32x4_t*>(&sA[b][1][so]) = ral;
+    *reinterpret_cast<u32x4_t*>(&sB[b][0][so]) = rbh;
+    *reinterpret_cast<u32x4_t*>(&sB[b][1][so]) = rbl;
+  };
   // one stage from buffer B (compile-time), while the next stage (clamped to the last one at
   // the end: a harmless reload) is fetched into registers and then written to the other buffer
   auto stage = [&](auto bc, int st) {
@@ -99,44 +78,29 @@ __global__ __launch_bounds__(256, 2) void gemm3_frag_add(int64_t M, int64_t N, F
     fetch(st + 1 < nst ? st + 1 : st);
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) {
-      const int kc = ks * 16 + 8 * lhi;  // this lane's 8 k of the 16
-      bf16x8_t ah[NB], al[NB], bh[NB], bl[NB];
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int m = wm * (TM / 2) + i * 32 + l32, n = wn * (TM / 2) + i * 32 + l32;
-        ah[i] = *reinterpret_cast<const bf16x8_t*>(&sA[B][0][m * RS + kc]);
-        al[i] = *reinterpret_cast<const bf16x8_t*>(&sA[B][1][m * RS + kc]);
-        bh[i] = *reinterpret_cast<const bf16x8_t*>(&sB[B][0][n * RS + kc]);
-        bl[i] = *reinterpret_cast<const bf16x8_t*>(&sB[B][1][n * RS + kc]);
-      }
-#pragma unroll
-      for (int bi = 0; bi < NB; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < NB; ++bj) {
-          acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[bi], bh[bj], acc[bi][bj], 0, 0, 0);
-          acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[bi], bl[bj], acc[bi][bj], 0, 0, 0);
-          acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[bi], bh[bj], acc[bi][bj], 0, 0, 0);
-        }
+      const int k = ks * 16 + 8 * lhi;  // this lane's 8 k of the 16
+      const int m = wm * 32 + l32, n = wn * 32 + l32;
+      const bf16x8_t ah = *reinterpret_cast<const bf16x8_t*>(&sA[B][0][m * RS + k]);
+      const bf16x8_t al = *reinterpret_cast<const bf16x8_t*>(&sA[B][1][m * RS + k]);
+      const bf16x8_t bh = *reinterpret_cast<const bf16x8_t*>(&sB[B][0][n * RS + k]);
+      const bf16x8_t bl = *reinterpret_cast<const bf16x8_t*>(&sB[B][1][n * RS + k]);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
     }
-    KQ_STASH(1 - B)
+    stash(1 - B);
   };
   fetch(0);
-  KQ_STASH(0)
+  stash(0);
   for (int st = 0; st < nst; st += 2) {
     stage(std::integral_constant<int, 0>{}, st);
     stage(std::integral_constant<int, 1>{}, st + 1);
   }
-#undef KQ_STASH
 #pragma unroll
-  for (int bi = 0; bi < NB; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < NB; ++bj)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t gm = m0 + wm * (TM / 2) + bi * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
-        const int64_t gn = n0 + wn * (TM / 2) + bj * 32 + l32;
-        if (gm < M && gn < N) C[gm * ldc + gn] = cin[bi][bj][r] + acc[bi][bj][r];
-      }
+  for (int e = 0; e < 16; ++e) {
+    const int64_t gm = gm0 + 8 * (e >> 2) + (e & 3);
+    if (gm < M && gn < N) C[gm * ldc + gn] = cin[e] + acc[e];
+  }
 }
 
 // Fh[n][k] + Fl[n][k] = U[k][n], the bf16 split of U^T in MFMA-fragment order, 64 x 64 tiles
@@ -206,7 +170,7 @@ int gemm_frag_add(int64_t M, int64_t N, const FragPair& p1, const FragPair& p2, 
     j.alpha = 1.f, j.C = C, j.ldc = ldc, j.add = true;
     return gemm_frag_bf16(j, tile, s, name);
   }
-  return launch(name, gemm3_frag_add<64>, dim3(unsigned(cdiv(N, 64)), unsigned(cdiv(M, 64))),
+  return launch(name, gemm3_frag_add, dim3(unsigned(cdiv(N, 64)), unsigned(cdiv(M, 64))),
                 dim3(256), 0, s, M, N, p1, p2, C, ldc);
 }
 
