@@ -5,6 +5,9 @@
 // second product) divided by a power of two that brings its largest value below 2^15: a value keeps
 // 23 bits down to 2^-16 of its row's largest and is good to 2^-39 of that below (10 bits are left at
 // 2^-29). Below that order, on the fp32 matrix cores.
+// Measured (d = 4096): products 110 + 109 us on 128 x 128 tiles, bound by their operands' L2 traffic
+// and the uneven K ranges; splits 49, largest values 16, the cleared triangle 10 us. (Both products
+// on the fp32 matrix cores: 374 + 287 us.)
 #include "kq_common.hpp"
 
 namespace kq {

@@ -13,7 +13,7 @@
 //                 three stages along the row axis;
 //   * column pass: transform along the strided (row) axis for a strip of columns: L rows at a
 //                 fixed row stride are staged in LDS and transformed there. An order-m transform
-//                 is split into passes of length <= 512 (H_m = H_m1 (x) H_m2), plus a 28-point pass.
+//                 is split into passes of length <= 1024 (H_m = H_m1 (x) H_m2), plus a 28-point pass.
 // Forward: W <- U S_G W S_X V^T; H_X <- V S_X^-1 H_X S_X^-1 V^T; H_G <- U S_G^-1 H_G S_G^-1 U^T.
 // Inverse (W only): W <- S_G^-1 U^T W V S_X^-1 (column pass with Q28^T, then the row pass).
 #include <cmath>
