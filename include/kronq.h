@@ -261,8 +261,9 @@ int kronq_cholesky_inv(float* H, int64_t d, int64_t ldh, float damp_rel, float* 
 /* ---- 4b. drift correction (Prop. 1 eq. kronq_update; Alg. 2 third line) ------------------
  * P = alpha ((D U^T) . M_U) U with U from kronq_cholesky_inv (the paper's L is U^T) and M_U the
  * strictly upper mask; P is strictly upper triangular (zeros on and below the diagonal are
- * written). Row p of P is alpha D[p, p+1:] inv(H~[p+1:, p+1:]). Products of
- * fp32 accuracy, 2 d^3 / 3 flops.
+ * written). Row p of P is alpha D[p, p+1:] inv(H~[p+1:, p+1:]). 2 d^3 / 3 flops;
+ * fp32 products, from d = 1280 of operands of 23 bits with fp32 sums: an entry far below its row's
+ * largest (once U's columns are of one size) is good to 2^-39 of that.
  *   D  device fp32 [d x ldd]: the transformed drift statistic (kronq_rotate_drift).
  *   U  device fp32 [d x ldu], upper.   P  device fp32 [d x ldp]; must not alias D or U.
  *   All 16-byte aligned with leading dimensions divisible by 4. Workspace: KRONQ_OP_GPTAQ. */

@@ -446,7 +446,7 @@ Planes take_planes(float*& at, int64_t rows, int64_t k, float*& mx) {
 }
 SplitJob split_job(const float* src, int64_t ld, int64_t rows, int64_t cols, int tri, bool trans,
                    const Planes& p) {
-  return SplitJob{src, ld, rows, cols, tri, trans, p.max, p.h, p.l, p.ks};
+  return SplitJob{src, ld, rows, cols, tri, trans, p.max, p.h, p.l, p.ks, {}};
 }
 FragJob frag_job(const Planes& P, const Planes& Q, int64_t M, int64_t N, int64_t K, int flags,
                  float alpha, float* C, int64_t ldc) {
@@ -486,8 +486,8 @@ int chol_node_frag(const Chol& c, float* T, float*& mx, int64_t n0, int64_t n) {
   // so 256 x 256 tiles only where they come in several rounds of the chip
   auto tile = [](int64_t tiles256) { return tiles256 >= 2 * int64_t(device_cus()) ? 256 : 128; };
   const int64_t tr = cdiv(r, 256), th = cdiv(h, 256);
-  const AbsMaxJob top[2] = {{M21, ld, r, h, TRI_FULL, pM.max, nullptr},
-                            {X11, ld, h, h, TRI_LOWER, pX.max, pXt.max}};
+  const AbsMaxJob top[2] = {{M21, ld, r, h, TRI_FULL, pM.max, nullptr, {}},
+                            {X11, ld, h, h, TRI_LOWER, pX.max, pXt.max, {}}};
   KQ_TRY(abs_max_launch(top, 2, c.s, "chol_split"));
   const SplitJob split[3] = {split_job(M21, ld, r, h, TRI_FULL, false, pM),
                              split_job(X11, ld, h, h, TRI_LOWER, false, pX),
@@ -508,7 +508,7 @@ int chol_node_frag(const Chol& c, float* T, float*& mx, int64_t n0, int64_t n) {
   const SplitJob split_t = split_job(X21, ld, r, h, TRI_FULL, true, pT);
   KQ_TRY(split_planes_launch(&split_t, 1, c.s, "chol_split"));
   KQ_TRY(chol_rec(c, T, mx, n0 + h, r));
-  const AbsMaxJob top22{X22, ld, r, r, TRI_LOWER, pY.max, nullptr};
+  const AbsMaxJob top22{X22, ld, r, r, TRI_LOWER, pY.max, nullptr, {}};
   KQ_TRY(abs_max_launch(&top22, 1, c.s, "chol_split"));
   const SplitJob split22 = split_job(X22, ld, r, r, TRI_LOWER, false, pY);
   KQ_TRY(split_planes_launch(&split22, 1, c.s, "chol_split"));

@@ -450,6 +450,12 @@ __device__ __forceinline__ void load4(const float* p, int64_t c, int64_t cols, f
   }
 }
 
+// the factor of column c
+__device__ __forceinline__ float col_factor(const ColScale& s, int64_t c) {
+  const float u = plane_unit(s.max[c]);
+  return s.inverse ? 1.f / u : u;
+}
+
 // Largest absolute values of the rows and columns: 32 x 256 tiles, a wave on 8 rows with all its
 // loads in flight, one atomic per row and column of a tile. (Values compare as their bits; of a
 // row with a NaN it is the NaN.)
@@ -499,8 +505,20 @@ __global__ __launch_bounds__(256) void abs_max(AbsMaxJob j0, AbsMaxJob j1) {
   if (J.rmax) {
     // over the lanes: half of the rows change hands at each of three steps, then one row is left
     uint32_t m[R];
+    float cf[4] = {};
+    if (J.scale.max) {
 #pragma unroll
-    for (int i = 0; i < R; ++i) m[i] = max(max(v[i][0], v[i][1]), max(v[i][2], v[i][3]));
+      for (int k = 0; k < 4; ++k) cf[k] = col_factor(J.scale, c + k);
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      if (J.scale.max) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          v[i][k] = __float_as_uint(__uint_as_float(v[i][k]) * cf[k]);
+      }
+      m[i] = max(max(v[i][0], v[i][1]), max(v[i][2], v[i][3]));
+    }
 #pragma unroll
     for (int o = 4; o > 0; o >>= 1)
 #pragma unroll
@@ -550,6 +568,10 @@ __global__ __launch_bounds__(256) void split_planes(SplitJob j0, SplitJob j1, Sp
     const int64_t r = r0 + rr + 16 * i, c = c0 + q;
     float x[4] = {};
     if (r < J.rows) load4(J.src + r * J.ld, c, J.cols, x);
+    if (J.scale.max) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] *= col_factor(J.scale, c + k < J.cols ? c + k : J.cols - 1);
+    }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int d = int(r - c) - k;

@@ -4,9 +4,10 @@
 // PLANES_MIN both run on fp16 planes (gemm_frag.hip), every row of an operand (U's columns in the
 // second product) divided by a power of two that brings its largest value below 2^15: a value keeps
 // 23 bits down to 2^-16 of its row's largest and is good to 2^-39 of that below (10 bits are left at
-// 2^-29). Below that order, on the fp32 matrix cores.
+// 2^-29); for the first product U's columns are brought to one size first. Below that order, on the
+// fp32 matrix cores.
 // Measured (d = 4096): products 110 + 109 us on 128 x 128 tiles, bound by their operands' L2 traffic
-// and the uneven K ranges; splits 49, largest values 16, the cleared triangle 10 us. (Both products
+// and the uneven K ranges; splits 49, largest values 28, the cleared triangle 10 us. (Both products
 // on the fp32 matrix cores: 374 + 287 us.)
 #include "kq_common.hpp"
 
@@ -26,9 +27,9 @@ __global__ void clear_lower4(float* __restrict__ M, int64_t d, int64_t ld) {
   }
 }
 
-// (whole correction, fp32 matrix cores against planes: 76 and 76 us at d = 1024, 92 and 80 at 1280,
-// 114 and 87 at 1536, 165 and 105 at 2048, 653 and 320 at 4096; error against 64 bits 4.9e-7 and
-// 3.2e-7 at 1024, 9.7e-7 and 6.2e-7 at 4096)
+// (whole correction, fp32 matrix cores against planes: 92 and 92 us at d = 1280, 114 and 94 at 1536,
+// 165 and 121 at 2048, 653 and 333 at 4096; error against 64 bits 5.4e-7 and 3.5e-7 at 1280, 9.7e-7
+// and 6.2e-7 at 4096, the same with channels of sizes over eight decades)
 constexpr int64_t PLANES_MIN = 1280;
 
 int64_t t_ld(int64_t d) { return cdiv(d, 64) * 64; }
@@ -70,19 +71,25 @@ int gptaq_launch(const float* D, int64_t d, int64_t ldd, const float* U, int64_t
   // with 128 x 128, 603 with 256 x 256)
   const int tile = t256 >= 2 * int64_t(device_cus()) ? 256 : 128;
   KQ_TRY(clear_launch(md, 4 * d, s, "gptaq_split"));
-  const AbsMaxJob top[2] = {{D, ldd, d, d, TRI_STRICT_UPPER, md, nullptr},
-                            {U, ldu, d, d, TRI_UPPER, mu, mc}};
+  // T sums over channels k that D[m][k] grows with and U[n][k] falls with: U's columns are brought
+  // to one size and D's take the inverse factors, or the small channels would drop out of the
+  // planes of D's rows and the large ones out of U's. (T and U's rows are of one size over k.)
+  const AbsMaxJob cols{U, ldu, d, d, TRI_UPPER, nullptr, mc, {}};
+  KQ_TRY(abs_max_launch(&cols, 1, s, "gptaq_split"));
+  const ColScale up{mc, false}, down{mc, true};
+  const AbsMaxJob top[2] = {{D, ldd, d, d, TRI_STRICT_UPPER, md, nullptr, up},
+                            {U, ldu, d, d, TRI_UPPER, mu, nullptr, down}};
   KQ_TRY(abs_max_launch(top, 2, s, "gptaq_split"));
-  const SplitJob s1[2] = {{D, ldd, d, d, TRI_STRICT_UPPER, false, md, ah, al, ks},
-                          {U, ldu, d, d, TRI_UPPER, false, mu, bh, bl, ks}};
+  const SplitJob s1[2] = {{D, ldd, d, d, TRI_STRICT_UPPER, false, md, ah, al, ks, up},
+                          {U, ldu, d, d, TRI_UPPER, false, mu, bh, bl, ks, down}};
   KQ_TRY(split_planes_launch(s1, 2, s, "gptaq_split"));
   FragJob j{};  // T[m][n] = sum_k D[m][k] U[n][k], n >= m (by tiles), so k > m for T's kept part
   j.Ph = ah, j.Pl = al, j.Qh = bh, j.Ql = bl, j.pks = j.qks = ks;
   j.M = j.N = j.K = d, j.flags = FRAG_Q_UPPER | FRAG_UPPER, j.alpha = 1.f;
   j.C = T, j.ldc = ldt, j.pmax = md, j.qmax = mu, j.rmax = mt;
   KQ_TRY(gemm_frag_f16(&j, 1, tile, s, "gptaq_d_ut"));
-  const SplitJob s2[2] = {{T, ldt, d, d, TRI_STRICT_UPPER, false, mt, ah, al, ks},
-                          {U, ldu, d, d, TRI_UPPER, true, mc, bh, bl, ks}};
+  const SplitJob s2[2] = {{T, ldt, d, d, TRI_STRICT_UPPER, false, mt, ah, al, ks, {}},
+                          {U, ldu, d, d, TRI_UPPER, true, mc, bh, bl, ks, {}}};
   KQ_TRY(split_planes_launch(s2, 2, s, "gptaq_split"));
   j.flags = FRAG_P_UPPER | FRAG_Q_LOWER | FRAG_UPPER, j.alpha = alpha;  // P[m][n], k in (m, n]
   j.C = P, j.ldc = ldp, j.pmax = mt, j.qmax = mc, j.rmax = nullptr;

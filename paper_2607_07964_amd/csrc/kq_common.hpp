@@ -220,6 +220,14 @@ int gemm_frag_bf16(const FragJob& j, int tile, hipStream_t s, const char* name);
 // one or two independent products in one launch
 int gemm_frag_f16(const FragJob* jobs, int n, int tile, hipStream_t s, const char* name);
 
+// A factor per column for a matrix read by rows: plane_unit of max[column], or its inverse
+// (powers of two; none where max is NULL). Both operands of a product sum over these columns, so
+// that one takes the factors and the other their inverses.
+struct ColScale {
+  const float* max;
+  bool inverse;
+};
+
 // The part of a matrix that counts
 enum Tri : int { TRI_FULL = 0, TRI_LOWER, TRI_UPPER, TRI_STRICT_UPPER };
 // rmax[r] and cmax[c] (when given; zeros beforehand) raised to the largest absolute values of the
@@ -229,14 +237,15 @@ struct AbsMaxJob {
   int64_t ld, rows, cols;
   int tri;
   float *rmax, *cmax;
+  ColScale scale;  // of the values that rmax sees (cmax: as they are)
 };
 // one or two matrices in one launch
 int abs_max_launch(const AbsMaxJob* jobs, int n, hipStream_t s, const char* name);
 // p[0, n) = 0
 int clear_launch(float* p, int64_t n, hipStream_t s, const char* name);
 
-// fp16 planes of the fp32 matrix src [rows x cols] (16-byte aligned rows), or of its transpose,
-// each row of the planes divided by plane_unit of its largest absolute value
+// fp16 planes of the fp32 matrix src [rows x cols] (16-byte aligned rows; times scale), or of its
+// transpose (no scale), each row of the planes divided by plane_unit of its largest absolute value
 struct SplitJob {
   const float* src;
   int64_t ld, rows, cols;
@@ -246,6 +255,7 @@ struct SplitJob {
   const float* max;  // one per row of the planes
   uint16_t *Oh, *Ol;
   int64_t ks;  // 16-k units per 32-row group of the planes
+  ColScale scale;
 };
 // up to three matrices in one launch
 int split_planes_launch(const SplitJob* jobs, int n, hipStream_t s, const char* name);

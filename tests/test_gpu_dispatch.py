@@ -307,14 +307,38 @@ def test_gptaq_planes(d, pad):
     T = np.triu(D64 @ U64.T, 1)
     ref = 0.5 * T @ U64
     # two d-term fp32 sums of operands of 23 bits (2^-23 each) of the terms' sizes; an operand below
-    # 2^-16 of its row's largest value (D, T, U's rows and columns) is good to 2^-39 of that
+    # 2^-16 of its row's largest value (D and U with U's columns brought to one size, T, U's
+    # columns) is good to 2^-39 of that (sizes to a power of two: a factor of two)
     top = lambda a, axis: np.abs(a).max(axis, keepdims=True)
+    c = top(U64, 0)
     size = np.triu(np.abs(D64) @ np.abs(U64).T, 1)
-    eT = (d + 12) * 2.0 ** -24 * size + d * 2.0 ** -38 * top(D64, 1) * top(U64, 1).T
+    eT = (d + 12) * 2.0 ** -24 * size + d * 2.0 ** -37 * top(D64 * c, 1) * top(U64 / c, 1).T
     eP = (d + 12) * 2.0 ** -24 * size @ np.abs(U64) + d * 2.0 ** -38 * top(T, 1) * top(U64, 0)
     assert np.all(np.abs(p - ref) <= 0.5 * np.triu(np.triu(eT, 1) @ np.abs(U64) + eP, 1))
     if pad:
         assert torch.isnan(dev[2][:, d:]).all()
+
+
+@pytest.mark.parametrize("d", [1279, 1280, 1539])
+def test_gptaq_planes_graded_channels(d):
+    """Channels of sizes over eight decades, as without the rescaling: D grows with both of its
+    channels, U falls with its column's. P[p, n] is s_p / s_n times that of equal channels."""
+    rng = np.random.default_rng(d)
+    s = 10.0 ** rng.uniform(-4, 4, d)
+    X = rng.standard_normal((2 * d, d))
+    U = (O.inverse_cholesky_factor(O.damp(X.T @ X / (2 * d))) / s[None, :]).astype(np.float32)
+    D = (rng.standard_normal((d, d)) * 0.1 * s[:, None] * s[None, :]).astype(np.float32)
+    P = torch.empty(d, -(-d // 4) * 4, device=DEV)[:, :d]
+    dev = [torch.zeros(d, -(-d // 4) * 4, device=DEV)[:, :d] for _ in range(2)]
+    for t, a in zip(dev, (D, U)):
+        t.copy_(torch.from_numpy(a))
+    note(f"gptaq graded channels d={d}")
+    K.kronq_gptaq_correction(dev[0], dev[1], P, 1.0)
+    torch.cuda.synchronize()
+    ref = np.triu(np.triu(D.astype(np.float64) @ U.astype(np.float64).T, 1) @ U, 1)
+    w = s[None, :] / s[:, None]
+    # (fp32 products leave 5e-7; the planes without factors per channel leave 1e-4)
+    assert rel_frob(to_np(P) * w, ref * w) < PLANE_TOL
 
 
 def test_gptaq_planes_ragged_256_tiles():
