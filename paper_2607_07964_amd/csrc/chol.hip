@@ -387,10 +387,11 @@ int64_t pad(int64_t n, int64_t m) { return cdiv(n, m) * m; }
 // A node of n columns whose parts have at least this order runs its products on 16-bit planes: at
 // 768 a factor of order 3000 takes 1.42 ms, 4096 1.93, 8192 4.85 and 14336 12.97; at 512 1.40, 2.06,
 // 5.13 and 13.01, at 1024 1.44, 1.93, 4.86 and 13.15, at 2048 1.53, 1.99, 4.96 and 13.83. Below, the
-// nine launches cost more than the products. (Products on the fp32 matrix cores and, from order
-// 3000, on six bf16 products a term split inside the kernel: 1.71 ms at 3000, 2.47 at 4096 and 22.4
-// at 14336, the 4096 and 14336 with slower leaves; error of U against float64 5.5e-7 and 8.6e-7 at
-// 4096 and 14336, now 3.6e-7 and 6.3e-7.)
+// nine launches cost more than the products. (Beside H_G on the rest of the chip, 4096 x 4096 layers
+// of 262144 and 65536 tokens: 9.10 and 4.48 ms with 768, 9.22 and 4.54 with 1536. Products on the
+// fp32 matrix cores and, from order 3000, on six bf16 products a term split inside the kernel: 1.71
+// ms at 3000, 2.47 at 4096 and 22.4 at 14336, with slower leaves; error of U against float64 5.5e-7
+// and 8.6e-7 at 4096 and 14336, now 3.6e-7 and 6.3e-7.)
 constexpr int64_t FRAG_MIN = 768;
 bool frag_node(int64_t n) {
   const int64_t h = split_at(n);
@@ -466,8 +467,8 @@ int chol_rec(const Chol& c, float* T, float*& mx, int64_t n0, int64_t n);
 // knows, go through fp32 at X21's place, which nothing else uses before the last step. (A power of
 // two per matrix, L21 and T leaving their products as planes: X overflowed from 4095 on, and a
 // coupling of 1e-4 left X21 good to 4e-5 where it is now good to 4e-7. It took 1.85 ms at 4096 and
-// 12.12 at 14336; twelve more launches of 5 to 8 us at 4096, and the reads for the largest values, are
-// the difference to now.)
+// 12.12 at 14336; twelve more launches of 5 to 8 us at 4096, and the reads for the largest values,
+// are the difference to now.)
 int chol_node_frag(const Chol& c, float* T, float*& mx, int64_t n0, int64_t n) {
   const int64_t h = split_at(n), r = n - h, ld = c.ld;
   KQ_TRY(chol_rec(c, T, mx, n0, h));

@@ -638,7 +638,9 @@ int obs_launch(float* W, int64_t d_out, int64_t d_in, int64_t ldw, const float* 
   // 32 rows a workgroup while the chip holds all of them (two workgroups per CU, one with the
   // drift correction's P block), else 64. Measured (whole solve, 32 rows and 64): 4096 x 4096 694
   // and 835 us; 4096 x 14336 4.23 and 4.65 ms; 14336 x 4096 1414 and 1421 us; 28672 x 8192 7.76 and
-  // 7.22 ms; with P 4096 x 4096 1159 and 1372 us, 14336 x 4096 2720 and 2285 us.
+  // 7.22 ms; with P 4096 x 4096 1159 and 1372 us, 14336 x 4096 2720 and 2285 us. Beside H_G on the
+  // rest of the chip, whole layers: 4096 x 4096 with 262144 tokens 9.10 and 9.19 ms, with 65536 4.48
+  // and 4.64, 14336 x 4096 with 65536 16.74 and 16.84.
   a.cus = device_cus();
   const int64_t g32 = cdiv(d_out, 32);
   const int rg = g32 <= int64_t(a.cus) * (drift ? 1 : 2) ? 1 : 2;
