@@ -195,13 +195,14 @@ __device__ __forceinline__ void store_f16(std::integer_sequence<int, I...>, cons
   auto rows = [&](auto ic) {
     constexpr int i = decltype(ic)::value;
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_wave_barrier();  // (LDS of one wave: its accesses are in order)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (LDS of one wave: its accesses are
+    __builtin_amdgcn_wave_barrier();                        // done in order)
     float* w = lw + 4 * (lane >> 5) * L::S + (lane & 31);
 #pragma unroll
     for (int j = 0; j < WT; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) w[(8 * (r >> 2) + (r & 3)) * L::S + 32 * j] = acc[i][j][r];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     store_rows<WT>(J, lw, m + 32 * i, n, lane, pu + 32 * i, qu, cm);
   };
