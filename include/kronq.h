@@ -330,6 +330,9 @@ int kronq_online_factors(const float* s, const int8_t* sign, int64_t d, float* m
  *   q28_in, q28_out  as for kronq_rotate, required when that side rotates a 28 * 2^k dimension.
  *   x       device [batch x ldx], KRONQ_BF16 or KRONQ_FP32, 16-byte aligned rows.
  *   y       device fp32 [batch x ldy], 16-byte aligned, ldy % 4 == 0.
+ * T_in diag(mul_in) x is held as 30-bit fixed point with one exponent per 128 columns (an element
+ * below 2^-6 of their largest has fewer than 24 bits); the sums over 128 columns are exact, those
+ * of the groups fp32.
  *   1 <= batch <= 4, batch * d_in <= 32768, d_out <= 32768. Workspace: KRONQ_OP_ONLINE. */
 int kronq_online_matvec(const uint32_t* packed, int64_t ldp, const float* scales,
                         const float* zeros, int64_t ldsz, int bits, int group, int64_t d_out,
